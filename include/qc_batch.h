@@ -29,19 +29,22 @@ enum {
 /*
  * Plan a batch.
  *   graphs     host, qc_graph[n_graphs] created with qc_graph_create; the batch
- *              uses their resident buffers (distance matrix, histograms,
- *              potentials, weights), so a graph must not be used elsewhere
+ *              uses their resident buffers (histograms, potentials,
+ *              weights), so a graph must not be used elsewhere
  *              while a batch run is in flight, and must outlive the batch.
  *              A graph may be in several batches, used one after another:
- *              a later batch's planning can give it another BFS launch
+ *              a later batch's planning can give a graph with integer
+ *              weights another BFS launch
  *              shape, and a run (of any batch, or a plain call) that finds
  *              the graph's packed edges in another shape's form waits for
  *              the device to drain and uploads them again (host to device,
  *              once per switch).
- *              A graph appears at most once. The batch computes each
- *              graph's distances into a matrix the graph's handle owns
- *              (allocated here when the handle has none), never into a
- *              caller's buffer an earlier qc_distances call was given; that
+ *              A graph appears at most once. The distances of every pair
+ *              are counted into the histograms by the search itself, without
+ *              a distance matrix; a graph with integer weights takes its
+ *              histograms from a matrix its handle owns
+ *              (allocated here when the handle has none), never
+ *              a caller's buffer an earlier qc_distances call was given; that
  *              owned matrix becomes the graph's resident matrix.
  *   n_graphs   1 <= n_graphs <= 65536
  *   sigmas     host, double[n_sigmas], each finite and > 0 (1..1024 values),
@@ -78,7 +81,9 @@ qc_status qc_batch_node_offsets(qc_batch b, int64_t *offsets);
  * When the searches take more than one launch (graphs of different launch
  * shapes), the launches, largest first, run on `stream` and a stream the
  * batch owns, each on the one with the least estimated search work so far.
- * The distance histograms of the graphs one search launch
+ * The distance histograms the search leaves to a pass of their own (the
+ * rows of leaves and unconnected nodes; every row of a graph with integer
+ * weights) of the graphs one search launch
  * covers run on another stream the batch owns as soon as that launch has
  * finished, beside the following searches, and the potentials (Eq. 2 /
  * Eq. 7) and Algorithms 2-3 of the graphs of all but the last few launches
@@ -118,7 +123,7 @@ qc_status qc_batch_sweep_bf16(qc_batch b, float *psi_out, float *v_out, void *st
  *                    default 32 and 1. Each graph's plan: qc_graph_bfs_plan
  *   hist_waves_out   host, int32[3] or NULL: wavefronts per workgroup of the
  *                    histogram pass for row lengths 32, 64 and 128 (0: no
- *                    graph of that row length); each workgroup counts 32 rows
+ *                    graph of that row length); each workgroup makes 32 rows
  *   jump_global_out  host or NULL: 1 when the pointer jumping runs in global
  *                    memory, 0 when it runs in LDS
  *   overlap_out      host or NULL: 3 when the histograms and the later
@@ -127,7 +132,8 @@ qc_status qc_batch_sweep_bf16(qc_batch b, float *psi_out, float *v_out, void *st
  *                    stream order (1: the histograms only, 2: every stage
  *                    after the search beside the searches, measurement
  *                    switches)
- * The autotuner times the whole BFS stage of the batch under each planning
+ * The autotuner times the whole BFS stage of the batch's graphs with integer
+ * weights (the others' counting search has one shape per size) under each planning
  * policy (widest batch 32, 64 or 16 with the seen-in-registers shape first,
  * and 32 without it); then, after one run of the whole path, it times whole
  * steps with the histogram pass in three shapes (the default wavefront
@@ -148,7 +154,8 @@ qc_status qc_batch_recheck_count(qc_batch b, int64_t *count_out);
 /*
  * Work of the last run's multi-source searches (waits for the device), as
  * counted by the search kernel: edge_visits = sum over the batches of
- * sources of (levels pulled over the whole edge list x edge entries + the
+ * sources of (levels pulled x edge entries, those of rows a level leaves out
+ * because every source has reached them included, + the
  * sources' row entries pushed at level 1); lds_bytes = the bytes of bit
  * field those visits gathered from LDS (4 or 8 per visit, by batch width).
  * Either pointer (host) may be NULL.

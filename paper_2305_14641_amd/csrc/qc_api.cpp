@@ -251,7 +251,7 @@ qc_status ensure_hist_jobs(qc_graph g)
 // done, so batches of sources with equal eccentricity pull the fewest
 // levels; every later search of the handle (a batch, a sigma sweep, a
 // second qc_distances) takes this order, and its batches' targets with it.
-static qc_status exact_source_order(qc_graph g, hipStream_t st)
+qc_status exact_source_order(qc_graph g, hipStream_t st)
 {
     std::vector<int32_t> h((size_t)g->n * g->K);
     QC_HIP(hipMemcpyAsync(h.data(), g->d_hist, h.size() * sizeof(int32_t), hipMemcpyDeviceToHost, st));
@@ -291,12 +291,19 @@ static qc_status exact_source_order(qc_graph g, hipStream_t st)
     gfree(g, g->d_bfs_jobs);
     g->d_src = d_src;
     g->d_bfs_jobs = d_jobs;
+    QC_TRY(reorder_rows(g));
     return push_desc(g, st);
 }
 
 // BFS into g->d_dist, then histograms. The first run waits to learn dmax.
 qc_status run_distances(qc_graph g, hipStream_t st)
 {
+    if (g->dmax >= 0 && !g->plan_exact) {
+        // the counting search learnt dmax: the plan (and histogram jobs) it gives
+        QC_TRY(set_plan(g, plan_bfs(g->n_bfs, g->dmax_bfs)));
+        QC_TRY(ensure_hist_jobs(g));
+        g->plan_exact = true;
+    }
     QC_TRY(check_edges(g));
     QC_HIP(launch_fill_i32(g->d_status, 2, 0, st));
     QC_TRY(push_desc(g, st));
@@ -337,6 +344,7 @@ qc_status run_distances(qc_graph g, hipStream_t st)
         }
         gfree(g, g->d_hist);
         g->d_hist = hist;
+        g->plan_exact = true;
         QC_TRY(push_desc(g, st));
     }
     {
@@ -529,6 +537,7 @@ void destroy(qc_graph g, bool sync)
     gfree(g, g->d_bfs_jobs);
     gfree(g, g->d_node_jobs);
     gfree(g, g->d_hist_jobs);
+    free_rows(g);
     delete g;
 }
 
@@ -692,6 +701,8 @@ qc_status create_graph(int32_t n, int64_t nnz, const int32_t *row_ptr, const int
     }
     // (a bound above 126 leaves the 7-plane plan, which detects overflow)
     if (bound > kMaxDist) bound = -1;
+    g->dist_bound = bound;
+    g->directed = directed;
     std::vector<NodeJob> njobs;
     for (int i = 0; i < n; i += kNodesPerJob) njobs.push_back(NodeJob{0, i, 0});
     g->n_node_jobs = (int)njobs.size();
@@ -728,6 +739,8 @@ qc_status create_graph(int32_t n, int64_t nnz, const int32_t *row_ptr, const int
         return fail(st_);
     if ((st_ = from_hip(launch_fill_u64(g->d_recheck, 1, st))) || (st_ = push_desc(g, st)))
         return fail(st_);
+    g->row_ptr = std::move(rp);
+    g->col = std::move(col);
     *out = g;
     return QC_OK;
 }
@@ -800,7 +813,7 @@ qc_status qc_potential(qc_graph g, const double *sigmas, int32_t n_sigmas, float
     QC_TRY(validate_sigmas(sigmas, n_sigmas));
     if (precision > QC_PREC_BF16) return QC_E_INVAL;
     hipStream_t st = as_stream(stream);
-    if (!g->have_dist) QC_TRY(qc_distances(g, nullptr, nullptr, stream));
+    if (!g->have_dist) QC_TRY(can_count(g) ? run_counts(g, st) : qc_distances(g, nullptr, nullptr, stream));
 
     // until this call has succeeded the handle holds no potentials (the
     // descent refuses to run on a half-made set)

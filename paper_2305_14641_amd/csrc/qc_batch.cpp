@@ -19,6 +19,8 @@
 using namespace qc;
 
 struct BfsGroup {
+    bool count = false;        // counting search (shape `rows`), else the matrix search
+    RowsPlan rows;
     int bw = 0, nw = 0, planes = 7;
     int shape = 0;
     int bias = 0;              // the row bias its graphs' edges carry (bfs_row_bias)
@@ -33,7 +35,8 @@ struct KGroup {
     int K = 0;
     NodeJob *d_jobs = nullptr;
     int n_jobs = 0;
-    int variant = 0;   // histogram workgroup shape (launch_hist)
+    int variant = 0;   // histogram workgroup shape (hist_waves)
+    bool count = false;   // graphs of the counting search: the rows it leaves out (launch_hist_rest)
 };
 // The stages after the search for a set of the batch's graphs: histograms,
 // then (unless `rest` is false) potentials, descent and pointer jumping.
@@ -53,6 +56,7 @@ struct qc_batch_s {
     std::vector<qc_graph> graphs;
     std::vector<double> sigmas;
     std::vector<int64_t> offsets;  // [n_graphs + 1]
+    std::vector<uint8_t> counting; // per graph: histograms from the counting search, no matrix
     uint32_t tie = 0;
     uint32_t flags = 0;
     int precision = QC_PREC_FP64ACC;
@@ -220,19 +224,50 @@ constexpr int kTuneRounds = 3;
 // (half of it for the stage variants, which take their best of the rounds).
 constexpr float kTuneMargin = 0.02f;
 
-// BFS launch groups of the graphs' current plans: jobs grouped by launch
-// shape (batch width, words per thread, planes, shape), each group's jobs in
-// XCD order. Groups are appended to `out` before their tables are allocated,
-// so on failure the caller frees whatever was allocated.
-qc_status build_bfs_groups(const std::vector<qc_graph> &graphs, std::vector<BfsGroup> &out)
+// Search launch groups of the graphs' current plans: jobs grouped by launch
+// shape (the counting search's quads, threads and positions per word; the
+// matrix search's batch width, words per thread, planes and shape), each
+// group's jobs in XCD order. Groups are appended to `out` before their tables
+// are allocated, so on failure the caller frees whatever was allocated.
+qc_status build_bfs_groups(const std::vector<qc_graph> &graphs, const std::vector<uint8_t> &counting,
+                           std::vector<BfsGroup> &out, bool matrix_only = false)
 {
     std::map<std::tuple<int, int, int, int>, std::vector<int>> by_class;
+    std::map<std::tuple<int, int, int>, std::vector<int>> by_rows;
     for (size_t i = 0; i < graphs.size(); ++i) {
+        if (counting[i]) {
+            const RowsPlan &p = graphs[i]->rows.plan;
+            if (!matrix_only) by_rows[std::make_tuple(p.threads, p.nq, p.per)].push_back((int)i);
+            continue;
+        }
         QC_TRY(check_edges(graphs[i]));
         const BfsPlan &p = graphs[i]->plan;
         by_class[std::make_tuple(p.bw, p.nw, p.planes,
                                  p.shape | (graphs[i]->weighted ? kBfsWeighted : 0))]
             .push_back((int)i);
+    }
+    for (auto &kv : by_rows) {
+        std::vector<std::vector<BfsJob>> per;
+        std::vector<double> cost;
+        BfsGroup grp;
+        grp.count = true;
+        grp.rows = graphs[kv.second[0]]->rows.plan;
+        for (int gi : kv.second) {
+            qc_graph g = graphs[gi];
+            const int bw = grp.rows.batch(), n = g->rows.dev.n_search;
+            // last batch first, as in the handle's own jobs
+            std::vector<BfsJob> js;
+            for (int s0 = (n + bw - 1) / bw * bw - bw; s0 >= 0; s0 -= bw) js.push_back(BfsJob{gi, s0, 0u, 0u});
+            cost.push_back((double)js.size() * (double)(g->nnz + g->n) * (g->dmax + 2));
+            grp.rows_bytes += (double)g->n * g->n;
+            grp.cost += cost.back();
+            per.push_back(js);
+        }
+        const std::vector<BfsJob> jobs = xcd_order(per, cost);
+        grp.n_jobs = (int)jobs.size();
+        grp.graphs = kv.second;
+        out.push_back(grp);
+        QC_TRY(upload_jobs(&out.back().d_jobs, jobs));
     }
     for (auto &kv : by_class) {
         std::vector<std::vector<BfsJob>> per;
@@ -272,6 +307,13 @@ void free_bfs_groups(std::vector<BfsGroup> &gs)
     gs.clear();
 }
 
+// One search launch.
+hipError_t launch_group(const BfsGroup &g, const GraphDev *descs, hipStream_t st)
+{
+    if (g.count) return launch_count(g.rows.nq, g.rows.threads, g.rows.per, descs, g.d_jobs, g.n_jobs, st);
+    return launch_bfs(g.bw, g.nw, g.planes, g.shape, descs, g.d_jobs, g.n_jobs, st);
+}
+
 // One stage set on stream `st`.
 qc_status run_stages(qc_batch b, const Stages &c, float *psi_out, float *v_out, int32_t *labels_out,
                      hipStream_t st)
@@ -280,7 +322,10 @@ qc_status run_stages(qc_batch b, const Stages &c, float *psi_out, float *v_out, 
     const int64_t total = b->offsets.back();
     for (auto &g : c.hist) {
         StageTimer t(QC_STAGE_HIST, st);
-        QC_HIP(launch_hist(g.K, b->d_descs, g.d_jobs, g.n_jobs, st, g.variant));
+        if (g.count)
+            QC_HIP(launch_hist_rest(g.K, b->d_descs, g.d_jobs, g.n_jobs, hist_waves(g.K, g.variant), st));
+        else
+            QC_HIP(launch_hist(g.K, b->d_descs, g.d_jobs, g.n_jobs, st, g.variant));
     }
     if (!c.rest) return QC_OK;
     for (auto &g : c.pot) {
@@ -313,7 +358,7 @@ qc_status enqueue(qc_batch b, float *psi_out, float *v_out, int32_t *labels_out,
         hipStream_t bs = g.stream ? b->search_side[g.stream - 1] : st;
         {
             StageTimer t(QC_STAGE_BFS, bs);
-            QC_HIP(launch_bfs(g.bw, g.nw, g.planes, g.shape, b->d_descs, g.d_jobs, g.n_jobs, bs));
+            QC_HIP(launch_group(g, b->d_descs, bs));
         }
         if (b->overlap) QC_HIP(hipEventRecord(b->ev_bfs[i], bs));
     }
@@ -467,22 +512,33 @@ constexpr BfsPolicy kBfsPolicies[] = {{kBfsFullWidth, true}, {64, true}, {16, tr
 qc_status autotune_bfs_batch(qc_batch b, hipStream_t st, int *chosen)
 {
     *chosen = 0;
-    for (qc_graph g : b->graphs) QC_TRY(plain_edges(g));
+    // graphs of the counting search have one shape; their matrix searches
+    // (later calls on their handles) follow the planner
+    std::vector<qc_graph> matrix;
+    for (size_t i = 0; i < b->graphs.size(); ++i) {
+        qc_graph g = b->graphs[i];
+        if (b->counting[i])
+            QC_TRY(set_plan(g, plan_bfs_policy(g->n_bfs, g->dmax_bfs, kBfsFullWidth, true), false));
+        else
+            matrix.push_back(g);
+    }
+    if (matrix.empty()) return QC_OK;
+    for (qc_graph g : matrix) QC_TRY(plain_edges(g));
     float best = 1e30f;
     qc_status s = QC_OK;
     int pi = 0;
     for (const BfsPolicy &pol : kBfsPolicies) {
-        for (qc_graph g : b->graphs) {
+        for (qc_graph g : matrix) {
             if (s == QC_OK) s = set_plan(g, plan_bfs_policy(g->n_bfs, g->dmax_bfs, pol.max_bw, pol.front_first), false);
         }
         std::vector<BfsGroup> groups;
-        if (s == QC_OK) s = build_bfs_groups(b->graphs, groups);
+        if (s == QC_OK) s = build_bfs_groups(b->graphs, b->counting, groups, true);
         if (s == QC_OK) {
             const float ms = time_launches(
                 [&] {
                     hipError_t e = hipSuccess;
                     for (auto &g : groups) {
-                        e = launch_bfs(g.bw, g.nw, g.planes, g.shape, b->d_descs, g.d_jobs, g.n_jobs, st);
+                        e = launch_group(g, b->d_descs, st);
                         if (e != hipSuccess) break;
                     }
                     return e;
@@ -504,7 +560,7 @@ qc_status autotune_bfs_batch(qc_batch b, hipStream_t st, int *chosen)
     // the chosen plans, now with their edge order (even after a failure the
     // graphs keep valid plans)
     const BfsPolicy &pol = kBfsPolicies[*chosen];
-    for (qc_graph g : b->graphs) {
+    for (qc_graph g : matrix) {
         const qc_status r = set_plan(g, plan_bfs_policy(g->n_bfs, g->dmax_bfs, pol.max_bw, pol.front_first), true);
         if (s == QC_OK) s = r;
     }
@@ -542,17 +598,24 @@ qc_status qc_batch_create(const qc_graph *graphs, int32_t n_graphs, const double
     b->offsets.assign(n_graphs + 1, 0);
     for (int i = 0; i < n_graphs; ++i) {
         qc_graph g = graphs[i];
-        // the batch writes distances only into a matrix the handle owns,
-        // never into a caller's buffer an earlier qc_distances was given
-        if (!g->d_dist_owned) {
-            qc_status s = galloc(g, &g->d_dist_owned, (size_t)(g->n * owned_ld(g->n) + 16));
+        b->counting.push_back(can_count(g) ? 1 : 0);
+        if (b->counting.back()) {
+            // histograms straight from the search, no matrix
+            const qc_status s = g->dmax < 0 ? run_counts(g, st) : ensure_rows(g);
             if (s) return fail(s);
-        }
-        g->d_dist = g->d_dist_owned;
-        g->d_ld = owned_ld(g->n);
-        if (g->dmax < 0) {
-            qc_status s = run_distances(g, st);
-            if (s) return fail(s);
+        } else {
+            // the batch writes distances only into a matrix the handle owns,
+            // never into a caller's buffer an earlier qc_distances was given
+            if (!g->d_dist_owned) {
+                qc_status s = galloc(g, &g->d_dist_owned, (size_t)(g->n * owned_ld(g->n) + 16));
+                if (s) return fail(s);
+            }
+            g->d_dist = g->d_dist_owned;
+            g->d_ld = owned_ld(g->n);
+            if (g->dmax < 0 || !g->plan_exact) {
+                qc_status s = run_distances(g, st);
+                if (s) return fail(s);
+            }
         }
         // the graph's potentials are the batch's once a run has computed them
         g->have_pot = false;
@@ -579,7 +642,7 @@ qc_status qc_batch_create(const qc_graph *graphs, int32_t n_graphs, const double
     // policy that ran the batch's searches fastest)
     if ((flags & QC_BATCH_AUTOTUNE) && (s = autotune_bfs_batch(b, st, &b->bfs_policy)))
         return fail(s);
-    if ((s = build_bfs_groups(b->graphs, b->bfs))) return fail(s);
+    if ((s = build_bfs_groups(b->graphs, b->counting, b->bfs))) return fail(s);
     // When the searches take more than one launch, the histograms of each
     // launch's graphs run beside the later searches, and the potentials,
     // descent and jumping of the graphs of all but the last k launches run
@@ -658,21 +721,26 @@ qc_status qc_batch_create(const qc_graph *graphs, int32_t n_graphs, const double
         }
         for (auto &kv : by_k) {
             const int K = kv.first;
-            std::vector<NodeJob> hj, pj;
+            std::vector<NodeJob> hj[2], pj;   // matrix search, counting search
+            bool any[2] = {false, false};
             for (int gi : kv.second) {
-                const int n = graphs[gi]->n;
+                const int n = graphs[gi]->n, k = b->counting[gi];
+                any[k] = true;
                 if (with_hist)
-                    for (int r = 0; r < n; r += hist_rows_per_job(K)) hj.push_back(NodeJob{gi, r, 0});
+                    for (int r = 0; r < (k ? graphs[gi]->rows.dev.n_rest : n); r += hist_rows_per_job(K))
+                        hj[k].push_back(NodeJob{gi, r, 0});
                 if (rest)
                     for (int r = 0; r < n; r += kNodesPerJob) pj.push_back(NodeJob{gi, r, b->offsets[gi]});
             }
-            if (with_hist) {
+            for (int k = 0; k < 2; ++k) {
+                if (!with_hist || !any[k]) continue;
                 KGroup h;
                 h.K = K;
-                h.n_jobs = (int)hj.size();
+                h.n_jobs = (int)hj[k].size();
                 h.variant = 0;
+                h.count = k == 1;
                 c.hist.push_back(h);
-                QC_TRY(upload_jobs(&c.hist.back().d_jobs, hj));
+                QC_TRY(upload_jobs(&c.hist.back().d_jobs, hj[k]));
             }
             if (rest) {
                 KGroup pg;
@@ -798,7 +866,8 @@ qc_status qc_batch_run(qc_batch b, float *psi_out, float *v_out, int32_t *labels
     // a graph that is also in another batch, or searched alone since, may
     // hold its edges in the form another launch shape reads
     for (const BfsGroup &grp : b->bfs)
-        for (int gi : grp.graphs) QC_TRY(ensure_edges(b->graphs[gi], grp.bias));
+        if (!grp.count)
+            for (int gi : grp.graphs) QC_TRY(ensure_edges(b->graphs[gi], grp.bias));
     const bool use_graph = (b->flags & QC_BATCH_HIPGRAPH) && st != nullptr;
     if (!use_graph) {
         QC_TRY(enqueue(b, psi_out, v_out, labels_out, st));

@@ -10,11 +10,31 @@
 #include "qc.h"
 #include "qc_host.h"
 #include "qc_internal.h"
+#include "qc_rows.h"
 
 using qc::BfsJob;
 using qc::BfsPlan;
 using qc::GraphDev;
 using qc::NodeJob;
+
+// A handle's counting search (qc_count.h): device tables and jobs, built by
+// the first call that needs histograms but no distance matrix.
+struct RowsState {
+    bool ready = false;
+    qc::RowsPlan plan;
+    std::vector<uint8_t> kind;        // RowsKind per node
+    std::vector<uint16_t> pos;        // position of every core node
+    std::vector<uint32_t> first;      // its entries in col_pos
+    qc::RowsDev dev{};                // pointers to the buffers below
+    uint32_t *d_src = nullptr;        // [4 n_search]
+    uint16_t *d_col_pos = nullptr, *d_ent = nullptr, *d_leaf = nullptr;
+    uint32_t *d_codes = nullptr, *d_units = nullptr, *d_wave_row = nullptr, *d_wave_unit = nullptr;
+    uint32_t *d_rest = nullptr;
+    BfsJob *d_jobs = nullptr;
+    int n_jobs = 0;
+    NodeJob *d_rest_jobs = nullptr;
+    int n_rest_jobs = 0;
+};
 
 struct qc_graph_s {
     int device = 0;
@@ -25,6 +45,8 @@ struct qc_graph_s {
     int32_t n = 0;
     int64_t nnz = 0;
     int32_t n_components = 0;
+    std::vector<int32_t> row_ptr, col;   // the canonical CSR (host copy)
+    bool directed = false;
     std::vector<int32_t> comp_size;   // size of each node's component (host)
     BfsPlan plan{};
 
@@ -49,6 +71,8 @@ struct qc_graph_s {
     std::vector<uint32_t> edges_order; // that order (edges_bw > 0), rows as in edges_host
     int edges_bias = 0;               // row bias of d_edges (bfs_row_bias of the plan; -1: unknown)
 
+    RowsState rows;                   // the counting search
+
     // distances and histograms
     int8_t *d_dist_owned = nullptr;   // library-owned matrix (n rows of owned_ld(n), 16-byte padded)
     int8_t *d_dist = nullptr;         // current resident matrix (owned or caller's)
@@ -56,6 +80,8 @@ struct qc_graph_s {
     int32_t *d_hist = nullptr;
     int K = 0;
     int32_t dmax = -1;
+    int32_t dist_bound = -1;          // a bound on every distance (host sweeps; -1: none)
+    bool plan_exact = false;          // `plan` was made for the known largest distance
     int32_t dmax_bfs = -1;            // largest level of the search (>= dmax when weighted)
     bool have_dist = false;
 
@@ -119,6 +145,7 @@ struct qc_graph_s {
         d.parent = d_parent;
         d.status = d_status;
         d.recheck = d_recheck;
+        d.rows = rows.dev;
         return d;
     }
 };
@@ -246,6 +273,19 @@ qc_status check_edges(qc_graph g);
 // s0..s0+bw-1 of the source order.
 uint32_t batch_target(qc_graph g, int s0, int bw);
 qc_status run_distances(qc_graph g, hipStream_t st);
+// Whether g's histograms can come from the counting search: no integer
+// weights, and no workgroup shape of the matrix search asked for
+// (QC_BFS_SHAPE, a switch for measurements and tests).
+bool can_count(qc_graph g);
+// Build and upload the counting search's tables (a no-op when they are there).
+qc_status ensure_rows(qc_graph g);
+void free_rows(qc_graph g);
+// After a change of the source order: the counting search's source table.
+qc_status reorder_rows(qc_graph g);
+// The sources by exact eccentricity (after the first search).
+qc_status exact_source_order(qc_graph g, hipStream_t st);
+// Histograms without the matrix. The first run waits to learn dmax.
+qc_status run_counts(qc_graph g, hipStream_t st);
 qc_status ensure_sigma_buffers(qc_graph g, int S);
 // Load the weight tables of a sigma list into g (no-op if already loaded).
 qc_status load_sigmas(qc_graph g, const double *sigmas, int32_t n_sigmas, hipStream_t st);

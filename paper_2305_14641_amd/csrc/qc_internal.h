@@ -64,6 +64,36 @@ typedef const __attribute__((address_space(1))) u32x4 *global_u4;
 // GPUs: 32-bit data format, range checked against the byte count in word 2.
 constexpr int kBufferWord3 = 0x00020000;
 
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+
+// Hub rows a counting-search workgroup of NQ quads per thread and KT threads
+// keeps LDS accumulators for (the builder raises the row length from which a
+// row counts as a hub's until they fit).
+constexpr int rows_hub_cap(int nq, int kt) { return nq * kt * 4 / 10 < 256 ? 256 : nq * kt * 4 / 10 / 256 * 256; }
+
+// Device tables of the counting search (qc_count.h; built by qc_rows.cpp for
+// one launch shape).
+struct RowsDev {
+    const void *src;             // per source, in batch order: node | position << 16, first entry in
+                                 // col_pos, its degree | entries << 16, nodes of its component
+    const uint16_t *col_pos;     // positions of every node's out-neighbours that have one
+    const uint32_t *codes;       // [waves][quads] longest row of a quad
+    const uint32_t *wave_row;    // [waves] first 1,024-byte row of a wavefront's quads in `ent`
+    const uint32_t *wave_unit;   // [waves + 1] its hub units
+    const void *ent;             // entries of the quads, 64 lanes x 2 slots x 4 positions x 16 bits per row
+    const void *units;           // hub units: 64 lanes x 8 x 16 bits, then 64 targets
+    const void *leaf;            // positions of the leaves' neighbours, 16 bits each
+    uint32_t ent_bytes;
+    int32_t n_hub;
+    int32_t n_pos;               // nodes with a position
+    int32_t n_leaf;              // leaves, rounded up to a multiple of 4
+    int32_t n_search;            // sources to search
+    // Nodes that are not searched: node | neighbour << 16, the leaves first,
+    // then the ends of isolated edges, then the nodes without edges.
+    int32_t n_rest, n_rest_leaf, n_rest_pair;
+    const uint32_t *rest;
+};
+
 // Device-visible description of one graph and its resident buffers.
 // Kernels receive an array of these plus a job table, so one launch can
 // serve one graph or many.
@@ -112,6 +142,7 @@ struct GraphDev {
     // pushes from the sources), [1] bytes of the bit fields those visits
     // gathered from LDS.
     unsigned long long *visits;
+    RowsDev rows;             // the counting search's tables
 };
 
 // graph index, first source, and the number of (source, node) pairs the
@@ -177,6 +208,18 @@ hipError_t launch_bfs(int bw, int nw, int planes, int shape, const GraphDev *gra
 template <int BW>
 hipError_t launch_bfs_bw(int nw, int planes, int shape, const GraphDev *graphs, const BfsJob *jobs,
                          int n_jobs, hipStream_t stream);
+
+// Counting search (qc_count.h) over `n_jobs` (graph, first source) jobs, every
+// graph's tables built for this shape; histogram rows of the sources, the
+// largest distance into status[0].
+hipError_t launch_count(int nq, int threads, int per, const GraphDev *graphs, const BfsJob *jobs,
+                        int n_jobs, hipStream_t stream);
+hipError_t launch_count_512(int nq, const GraphDev *graphs, const BfsJob *jobs, int n_jobs,
+                            hipStream_t stream);
+// Histogram rows of the other nodes (one job = 32 of them) from the
+// searched ones, `waves` wavefronts per workgroup.
+hipError_t launch_hist_rest(int K, const GraphDev *graphs, const NodeJob *jobs, int n_jobs, int waves,
+                            hipStream_t stream);
 
 // Histograms of the resident distance rows (one job = hist_rows_per_job(K)
 // rows of one graph). `K` is the shared bin count (32, 64 or 128).

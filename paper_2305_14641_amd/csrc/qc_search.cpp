@@ -1,0 +1,175 @@
+// The counting search on a graph handle: its tables, and histograms without
+// the distance matrix.
+#include <stdlib.h>
+#include <string.h>
+
+#include <algorithm>
+
+#include "qc_handle.h"
+
+namespace qc {
+
+bool can_count(qc_graph g) { return !g->weighted && !getenv("QC_BFS_SHAPE"); }
+
+// The sources in the handle's order, with what the search needs of each.
+static std::vector<uint32_t> source_table(qc_graph g)
+{
+    const RowsState &r = g->rows;
+    std::vector<uint32_t> t;
+    t.reserve(4 * (size_t)r.dev.n_search);
+    for (int32_t v : g->src_order) {
+        if (r.kind[v] != kRowsCore) continue;
+        t.push_back((uint32_t)v | (uint32_t)r.pos[v] << 16);
+        t.push_back(r.first[v]);
+        t.push_back((uint32_t)(g->row_ptr[v + 1] - g->row_ptr[v]) | (r.first[v + 1] - r.first[v]) << 16);
+        t.push_back((uint32_t)g->comp_size[v]);
+    }
+    return t;
+}
+
+void free_rows(qc_graph g)
+{
+    RowsState &r = g->rows;
+    gfree(g, r.d_src);
+    gfree(g, r.d_col_pos);
+    gfree(g, r.d_codes);
+    gfree(g, r.d_wave_row);
+    gfree(g, r.d_wave_unit);
+    gfree(g, r.d_ent);
+    gfree(g, r.d_units);
+    gfree(g, r.d_leaf);
+    gfree(g, r.d_rest);
+    gfree(g, r.d_jobs);
+    gfree(g, r.d_rest_jobs);
+    r.dev = RowsDev{};
+    r.ready = false;
+}
+
+qc_status ensure_rows(qc_graph g)
+{
+    RowsState &r = g->rows;
+    if (r.ready) return QC_OK;
+    // With the sources in node order (QC_SOURCE_ORDER=identity, a switch for
+    // measurements and tests) every node is searched.
+    const char *so = getenv("QC_SOURCE_ORDER");
+    if (so && strcmp(so, "identity") == 0)
+        r.kind.assign(g->n, kRowsCore);
+    else
+        r.kind = rows_kinds(g->n, g->row_ptr, g->col, !g->directed);
+    const int32_t n_core = (int32_t)std::count(r.kind.begin(), r.kind.end(), (uint8_t)kRowsCore);
+    r.plan = plan_rows(n_core);
+    RowsTables t = build_rows(g->n, g->row_ptr, g->col, g->directed, g->comp_size, r.kind, r.plan);
+    r.pos = t.pos;
+    r.first = t.first;
+    r.dev = RowsDev{};
+    r.dev.n_search = r.dev.n_pos = t.n_pos;
+    r.dev.n_hub = t.n_hub;
+    r.dev.n_leaf = t.n_leaf;
+    r.dev.ent_bytes = (uint32_t)(t.ent.size() * sizeof(uint16_t));
+    const std::vector<uint32_t> rest =
+        rest_table(g->n, g->row_ptr, g->col, r.kind, r.dev.n_rest_leaf, r.dev.n_rest_pair);
+    r.dev.n_rest = (int32_t)rest.size();
+    const std::vector<uint32_t> src = source_table(g);
+    std::vector<BfsJob> jobs;
+    const int bw = r.plan.batch();
+    // last batch first: the source order puts the farthest-reaching sources
+    // (the longest searches) at the end
+    for (int s0 = (t.n_pos + bw - 1) / bw * bw - bw; s0 >= 0; s0 -= bw) jobs.push_back(BfsJob{0, s0, 0u, 0u});
+    std::vector<NodeJob> rjobs;
+    for (int i = 0; i < r.dev.n_rest; i += 32) rjobs.push_back(NodeJob{0, i, 0});
+    qc_status s = galloc(g, &r.d_src, src.size());
+    if (s == QC_OK) s = galloc(g, &r.d_col_pos, t.col_pos.size());
+    if (s == QC_OK) s = galloc(g, &r.d_codes, t.codes.size());
+    if (s == QC_OK) s = galloc(g, &r.d_wave_row, t.wave_row.size());
+    if (s == QC_OK) s = galloc(g, &r.d_wave_unit, t.wave_unit.size());
+    if (s == QC_OK) s = galloc(g, &r.d_ent, t.ent.size());
+    if (s == QC_OK) s = galloc(g, &r.d_units, t.units.size());
+    if (s == QC_OK) s = galloc(g, &r.d_leaf, t.leaf.size());
+    if (s == QC_OK) s = galloc(g, &r.d_rest, rest.size());
+    if (s == QC_OK) s = galloc(g, &r.d_jobs, jobs.size());
+    if (s == QC_OK) s = galloc(g, &r.d_rest_jobs, rjobs.size());
+    if (s == QC_OK)
+        s = upload_group(g, {span_of(r.d_src, src), span_of(r.d_col_pos, t.col_pos), span_of(r.d_codes, t.codes),
+                             span_of(r.d_wave_row, t.wave_row), span_of(r.d_wave_unit, t.wave_unit),
+                             span_of(r.d_ent, t.ent), span_of(r.d_units, t.units), span_of(r.d_leaf, t.leaf),
+                             span_of(r.d_rest, rest), span_of(r.d_jobs, jobs), span_of(r.d_rest_jobs, rjobs)});
+    if (s != QC_OK) {
+        free_rows(g);
+        return s;
+    }
+    r.dev.src = r.d_src;
+    r.dev.col_pos = r.d_col_pos;
+    r.dev.codes = r.d_codes;
+    r.dev.wave_row = r.d_wave_row;
+    r.dev.wave_unit = r.d_wave_unit;
+    r.dev.ent = r.d_ent;
+    r.dev.units = r.d_units;
+    r.dev.leaf = r.d_leaf;
+    r.dev.rest = r.d_rest;
+    r.n_jobs = (int)jobs.size();
+    r.n_rest_jobs = (int)rjobs.size();
+    r.ready = true;
+    return QC_OK;
+}
+
+// After the source order changed (exact_source_order): the sources' table.
+qc_status reorder_rows(qc_graph g)
+{
+    if (!g->rows.ready) return QC_OK;
+    return upload(g->rows.d_src, source_table(g));
+}
+
+qc_status run_counts(qc_graph g, hipStream_t st)
+{
+    QC_TRY(ensure_rows(g));
+    const bool first = g->dmax < 0;
+    int32_t *hist = nullptr;
+    if (first) {
+        // rows for the bound the host sweeps gave on every distance, or for
+        // the largest one an int8 distance can hold
+        g->K = bins_for(g->dist_bound >= 0 ? g->dist_bound : kMaxDist);
+    }
+    if (!g->d_hist || first) {
+        QC_TRY(galloc(g, &hist, (size_t)g->n * g->K));
+        gfree(g, g->d_hist);
+        g->d_hist = hist;
+    }
+    QC_HIP(launch_fill_i32(g->d_status, 2, 0, st));
+    for (;;) {
+        QC_TRY(push_desc(g, st));
+        {
+            StageTimer t(QC_STAGE_BFS, st);
+            QC_HIP(launch_count(g->rows.plan.nq, g->rows.plan.threads, g->rows.plan.per, g->d_desc, g->rows.d_jobs,
+                                g->rows.n_jobs, st));
+        }
+        {
+            StageTimer t(QC_STAGE_HIST, st);
+            QC_HIP(launch_hist_rest(g->K, g->d_desc, g->rows.d_rest_jobs, g->rows.n_rest_jobs,
+                                    hist_waves(g->K, 0), st));
+        }
+        if (g->dmax >= 0) break;
+        int32_t status[2];
+        QC_HIP(hipMemcpyAsync(status, g->d_status, sizeof status, hipMemcpyDeviceToHost, st));
+        QC_HIP(hipStreamSynchronize(st));
+        if (status[1] & 1) return QC_E_OVERFLOW;
+        const int K = bins_for(status[0]);
+        if (K != g->K) {
+            // rows of the exact length, and the search once more into them
+            int32_t *h = nullptr;
+            QC_TRY(galloc(g, &h, (size_t)g->n * K));
+            gfree(g, g->d_hist);
+            g->d_hist = h;
+            g->K = K;
+        }
+        g->dmax = g->dmax_bfs = status[0];
+        if (K == bins_for(g->dist_bound >= 0 ? g->dist_bound : kMaxDist)) {
+            QC_TRY(push_desc(g, st));
+            break;
+        }
+    }
+    if (first && g->ecc_order) QC_TRY(exact_source_order(g, st));
+    g->have_dist = true;
+    return QC_OK;
+}
+
+}  // namespace qc
