@@ -632,6 +632,7 @@ qc_status qc_batch_create(const qc_graph *graphs, int32_t n_graphs, const double
     b->d_visits = b->d_counters + 1;
     std::vector<GraphDev> descs(n_graphs);
     for (int i = 0; i < n_graphs; ++i) {
+        graphs[i]->dist_desc = false;   // the counting search's tables
         descs[i] = graphs[i]->desc();
         descs[i].recheck = b->d_recheck;
         descs[i].visits = b->d_visits;

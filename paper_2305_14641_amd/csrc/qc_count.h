@@ -39,6 +39,13 @@
 // with 88,726 entries: 119 us against 426 + 114 us (search + histogram pass);
 // 64 graphs of 1,000 to 20,000 nodes x 32 widths as one batch: 1.88 ms
 // against 4.71.
+//
+// With P > 0 the search also writes its sources' distance rows: P bit-planes
+// of the level per owned word (as in qc_bfs.h), permuted from the positions'
+// owners to the nodes' through LDS at the end and transposed to bytes there.
+// The planes fill the registers (one workgroup of 16 wavefronts per CU), and
+// the last workgroups' rows leave at HBM speed; n = 19,717, matrix, histograms
+// and all: 271 us against 521 (qc_bfs.h's search and the histogram pass).
 #pragma once
 
 #include "qc_internal.h"
@@ -130,10 +137,30 @@ __device__ __forceinline__ uint32_t carry_add(uint32_t &s, uint32_t a, uint32_t 
     return c;
 }
 
+// Transpose the 8 x 8 bit matrix in each byte lane of a[0..7]: afterwards
+// bit 8j + p of a[k] is what bit 8j + k of a[p] was.
+__device__ __forceinline__ void transpose_bytes(uint32_t (&a)[8])
+{
+    constexpr uint32_t kMask[3] = {0x0F0F0F0Fu, 0x33333333u, 0x55555555u};
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+        const int s = 4 >> r;
+#pragma unroll
+        for (int p = 0; p < 8; ++p) {
+            if (p & s) continue;
+            const uint32_t x = a[p], y = a[p + s], m = kMask[r];
+            a[p] = (x & m) | ((y << s) & ~m);
+            a[p + s] = ((x >> s) & m) | (y & ~m);
+        }
+    }
+}
+
 // NQ quads (4 positions) per lane, KT threads, PER positions per 32-bit word
-// (1: batches of 32 sources, 2: 16).
-template <int NQ, int KT, int PER>
-__global__ __launch_bounds__(KT) void k_count(const GraphDev *__restrict__ graphs,
+// (1: batches of 32 sources, 2: 16). P > 0: the distance rows of the sources
+// too, from P bit-planes of the level in registers (levels up to 2^P - 2;
+// all ones: not reached), NQN quads of consecutive nodes per lane.
+template <int NQ, int KT, int PER, int P, int NQN>
+__global__ __launch_bounds__(KT, 4) void k_count(const GraphDev *__restrict__ graphs,
                                               const BfsJob *__restrict__ jobs)
 {
     constexpr int QW = 4 / PER;             // words per quad
@@ -141,16 +168,26 @@ __global__ __launch_bounds__(KT) void k_count(const GraphDev *__restrict__ graph
     constexpr int BW = 32 / PER;
     constexpr int HUB = rows_hub_cap(NQ, KT);
     constexpr int kHubQuads = (HUB + 4 * KT - 1) / (4 * KT);   // quads per lane that may hold hubs
+    // bits of a lane's count: at most NW + 4 + 65,535 / KT
+    constexpr int CB = KT >= 1024 ? 7 : KT >= 512 ? 8 : 9;
+    constexpr int PA = P > 0 ? P : 1;
+    // `seen` in registers, or the planes' disjunction where they fill them
+    constexpr bool kSeenReg = P == 0 || NW * (P + 1) <= 64;
+    // With planes, two frontier fields: a quad's new bits go straight to the
+    // next frontier instead of waiting in registers for the barrier (the
+    // planes leave no registers, and one workgroup per CU leaves LDS).
+    constexpr bool kTwo = P > 0;
+    constexpr int kHold = kTwo ? kHubQuads * QW : NW;   // words held over the barrier
+    // registers to load a quad's third and fourth rows ahead too
+    constexpr bool kWide = P == 0 && NW <= 28;
     constexpr uint32_t kFull = PER == 1 ? ~0u : 0xFFFFu;
     constexpr uint32_t kAbsent = 0x80000000u;         // an offset past any table: loads nothing
-    // bits of a lane's count: at most NW + 4 + 65,535 / KT
-    constexpr int P = KT >= 1024 ? 7 : KT >= 512 ? 8 : 9;
     typedef const __attribute__((address_space(4))) uint32_t *const_u32;
 
-    __shared__ __attribute__((aligned(16))) uint32_t front[NW * KT];
+    __shared__ __attribute__((aligned(16))) uint32_t fields[(kTwo ? 2 : 1) * NW * KT];
     __shared__ __attribute__((aligned(16))) uint32_t hacc[HUB];
     __shared__ uint32_t hdone[HUB / 32];
-    __shared__ uint32_t cnt[3][16];
+    __shared__ uint32_t cnt[3][17];   // counts of a level; [16]: anything new at all
 
     const BfsJob job = jobs[blockIdx.x];
     const GraphDev &G = graphs[job.g];
@@ -159,9 +196,12 @@ __global__ __launch_bounds__(KT) void k_count(const GraphDev *__restrict__ graph
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n_pos = G.rows.n_pos;
     const int nb = min(BW, G.rows.n_search - job.s0);
-    const int n_hub = G.rows.n_hub;
+    // weighted edges: positions n_own .. own_end hold nothing, those from
+    // own_end on the nodes inside edges, which no histogram counts
+    const int n_own = G.rows.n_own, own_end = (n_own + 255) & ~255;
     const uint4 *__restrict__ src = (const uint4 *)G.rows.src + job.s0;
 
+    uint32_t *const front = fields;
     // own words of quad g
     auto own = [&](int g) { return (g * KT + tid) * QW; };
     auto clear_front = [&] {
@@ -177,17 +217,43 @@ __global__ __launch_bounds__(KT) void k_count(const GraphDev *__restrict__ graph
     clear_front();
     for (int i = tid; i < HUB; i += KT) hacc[i] = 0u;
     for (int i = tid; i < HUB / 32; i += KT) hdone[i] = 0u;
-    if (tid < 48) cnt[tid / 16][tid % 16] = 0u;
+    if (tid < 51) cnt[tid / 17][tid % 17] = 0u;
     __syncthreads();
     if (tid < nb) put(src[tid].x >> 16, tid);   // level 0: the sources
     __syncthreads();
-    uint32_t seen[NW], y[NW];
+    uint32_t seen_r[kSeenReg ? NW : 1], plane[NW][PA];
+    // bits of word w that are reached (or that stand for nothing)
+    auto seen_of = [&](int w) -> uint32_t {
+        if constexpr (kSeenReg) {
+            return seen_r[w];
+        } else {
+            uint32_t u = plane[w][0];
+#pragma unroll
+            for (int p = 1; p < PA; ++p) u &= plane[w][p];
+            return ~u;
+        }
+    };
+    // word w's new bits at a level
+    auto reach = [&](int w, uint32_t bits, int level) {
+        if constexpr (kSeenReg) seen_r[w] |= bits;
+        if constexpr (P > 0) {
+#pragma unroll
+            for (int p = 0; p < PA; ++p)
+                if (!((level >> p) & 1)) plane[w][p] &= ~bits;   // uniform branch
+        }
+    };
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        if constexpr (kSeenReg) seen_r[w] = 0u;
+#pragma unroll
+        for (int p = 0; p < PA; ++p) plane[w][p] = ~0u;
+    }
     const uint32_t pad_bits = (nb < BW) ? ~((1u << nb) - 1u) & kFull : 0u;
 #pragma unroll
     for (int g = 0; g < NQ; ++g)
 #pragma unroll
         for (int i = 0; i < QW; ++i)
-            seen[g * QW + i] = front[own(g) + i] | pad_bits | (PER == 1 ? 0u : pad_bits << 16);
+            reach(g * QW + i, front[own(g) + i] | pad_bits | (PER == 1 ? 0u : pad_bits << 16), 0);
     clear_front();
     __syncthreads();
     {   // level 1: their neighbours, along the sources' rows
@@ -219,50 +285,104 @@ __global__ __launch_bounds__(KT) void k_count(const GraphDev *__restrict__ graph
         uint32_t all = ~0u;
 #pragma unroll
         for (int i = 0; i < QW; ++i) {
-            uint32_t s = seen[g * QW + i] | front[own(g) + i];
-            // (a position past the last node counts as reached)
+            reach(g * QW + i, front[own(g) + i], 1);
+            // (a position that holds no node counts as reached)
+            uint32_t none = 0u;
 #pragma unroll
-            for (int h = 0; h < PER; ++h)
-                if ((g * KT + tid) * 4 + i * PER + h >= n_pos) s |= kFull << (16 * h);
-            seen[g * QW + i] = s;
-            all &= s;
+            for (int h = 0; h < PER; ++h) {
+                const int p = (g * KT + tid) * 4 + i * PER + h;
+                if (p >= n_pos || (p >= n_own && p < own_end)) none |= kFull << (16 * h);
+            }
+            reach(g * QW + i, none, 0);
+            all &= seen_of(g * QW + i);
         }
         if (__ballot(all != ~0u)) act |= 1u << g;
     }
-    const ColumnRoles roles(lane);
-    const const_u32 codes = (const_u32)G.rows.codes + wave * NQ;
-    const uint32_t row0 = ((const_u32)G.rows.wave_row)[wave] * 1024u;
-    const int u0 = (int)((const_u32)G.rows.wave_unit)[wave];
-    const int u1 = (int)((const_u32)G.rows.wave_unit)[wave + 1];
-    const int n_leaf = G.rows.n_leaf;
-    const __amdgpu_buffer_rsrc_t ent =
-        __builtin_amdgcn_make_buffer_rsrc((void *)G.rows.ent, 0, (int)G.rows.ent_bytes, kBufferWord3);
     const uint32_t voff = (uint32_t)lane * 16u;
-    auto gather = [&](uint32_t p) -> uint32_t {
-        if constexpr (PER == 1) return front[p];
-        else return ((const uint16_t *)front)[p];
+    // The graph's descriptor through an address the compiler cannot see
+    // through: what a level reads of it is loaded again (scalar loads) instead
+    // of being held in scalar registers, which have no room for all of it
+    // (instances whose scalar registers spilled by the hundred lost counts).
+    typedef const __attribute__((address_space(4))) GraphDev *const_graph;
+    auto descriptor = [&]() -> const_graph {
+        uint64_t a = (uint64_t)(uintptr_t)&G;
+        asm volatile("" : "+s"(a));
+        return (const_graph)a;
     };
-    auto row_of = [&](uint32_t row, bool on) -> u32x4 {
-        return __builtin_amdgcn_raw_buffer_load_b128(ent, (int)(voff | (on ? 0u : kAbsent)), (int)row, 0);
-    };
-
     int pulled = 0;
     bool overflow = false;
-    for (int level = 2; __ballot(left != 0u); ++level) {
+    auto ent_rsrc = [&](const_graph D) {
+        return __builtin_amdgcn_make_buffer_rsrc((void *)D->rows.ent, 0, (int)D->rows.ent_bytes, kBufferWord3);
+    };
+    auto row_of = [&](const __amdgpu_buffer_rsrc_t &ent, uint32_t r, bool on) -> u32x4 {
+        return __builtin_amdgcn_raw_buffer_load_b128(ent, (int)(voff | (on ? 0u : kAbsent)), (int)r, 0);
+    };
+    auto unit_ent = [&](const_graph D, int u) { return ((global_u4)D->rows.units)[(int64_t)u * 80 + lane]; };
+    auto unit_tgt = [&](const_graph D, int u) {
+        return ((const __attribute__((address_space(1))) uint32_t *)((global_u4)D->rows.units + (int64_t)u * 80 +
+                                                                     64))[lane];
+    };
+    // One level; true when the search ends.
+    auto run_level = [&](int level) __attribute__((always_inline)) -> bool {
+        const uint32_t *const from = fields + (kTwo ? (level & 1) * NW * KT : 0);
+        uint32_t *const to = fields + (kTwo ? (1 - (level & 1)) * NW * KT : 0);
+        auto gather = [&](uint32_t p) -> uint32_t {
+            if constexpr (PER == 1) return from[p];
+            else return ((const uint16_t *)from)[p];
+        };
         ++pulled;
+        const const_graph D = descriptor();
+        const __amdgpu_buffer_rsrc_t ent = ent_rsrc(D);
+        const int n_hub = D->rows.n_hub;
+        uint32_t any = 0u;
+        uint32_t cl[CB];   // the lane's new bits per source, bit-sliced
+#pragma unroll
+        for (int p = 0; p < CB; ++p) cl[p] = 0u;
+        auto count4 = [&](uint32_t x0, uint32_t x1, uint32_t x2, uint32_t x3) {
+            const uint32_t t0 = carry_add(cl[0], x0, x1), t1 = carry_add(cl[0], x2, x3);
+            uint32_t c = carry_add(cl[1], t0, t1);
+#pragma unroll
+            for (int p = 2; p < CB; ++p) {
+                const uint32_t d = cl[p] & c;
+                cl[p] ^= c;
+                c = d;
+            }
+        };
+        // quad g's new bits: the next frontier, `seen`, the planes
+        auto settle = [&](int g, uint32_t *y) {
+            uint32_t all = ~0u;
+#pragma unroll
+            for (int i = 0; i < QW; ++i) {
+                to[own(g) + i] = y[i];
+                reach(g * QW + i, y[i], level);
+                any |= y[i];
+                all &= seen_of(g * QW + i);
+                // (from here on only what is counted)
+                if (P > 0 && (g * KT + wave * 64) * 4 >= own_end) y[i] = 0u;
+            }
+            if (!__ballot(all != ~0u)) act &= ~(1u << g);
+            if (g < kHubQuads && (g * KT + wave * 64) * 4 < n_hub) {
+                // which hubs are done: bit (i, lane) of the quad's 256 positions
+                uint32_t v = 0u;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const uint32_t s = (seen_of(g * QW + i / PER) >> (16 * (i % PER))) & kFull;
+                    const uint64_t o = __ballot(s == kFull);
+                    if (lane == 2 * i) v = (uint32_t)o;
+                    if (lane == 2 * i + 1) v = (uint32_t)(o >> 32);
+                }
+                if (lane < 8) hdone[(g * KT + wave * 64) / 8 + lane] = v;
+            }
+        };
         // A. hub units: 8 entries per lane, the next unit's in flight
+        const int u0 = (int)((const_u32)D->rows.wave_unit)[wave], u1 = (int)((const_u32)D->rows.wave_unit)[wave + 1];
         if (u0 < u1) {
-            const global_u4 ue = (global_u4)(const void *)G.rows.units;
-            auto ent_of = [&](int u) { return ue[(int64_t)u * 80 + lane]; };
-            auto tgt_of = [&](int u) {
-                return ((const __attribute__((address_space(1))) uint32_t *)(ue + (int64_t)u * 80 + 64))[lane];
-            };
-            u32x4 e = ent_of(u0);
-            uint32_t t = tgt_of(u0);
+            u32x4 e = unit_ent(D, u0);
+            uint32_t t = unit_tgt(D, u0);
             for (int u = u0; u < u1; ++u) {
                 const int un = min(u + 1, u1 - 1);
-                const u32x4 en = ent_of(un);
-                const uint32_t tn = tgt_of(un);
+                const u32x4 en = unit_ent(D, un);
+                const uint32_t tn = unit_tgt(D, un);
                 if (!((hdone[t >> 21] >> ((t >> 16) & 31)) & 1u)) {
                     uint32_t x[8];
 #pragma unroll
@@ -280,38 +400,23 @@ __global__ __launch_bounds__(KT) void k_count(const GraphDev *__restrict__ graph
             }
         }
         // leaves: 4 per lane and step, added to the lane's count
-        uint32_t cl[P];
-#pragma unroll
-        for (int p = 0; p < P; ++p) cl[p] = 0u;
+        const int n_leaf = D->rows.n_leaf;
         for (int l = tid * 4; l < n_leaf; l += KT * 4) {
-            const uint2 e = ((const uint2 *)G.rows.leaf)[l >> 2];
+            const u32x2 e = ((const __attribute__((address_space(1))) u32x2 *)D->rows.leaf)[l >> 2];
             const uint32_t x0 = gather(e.x & 0xFFFFu), x1 = gather(e.x >> 16);
             const uint32_t x2 = gather(e.y & 0xFFFFu), x3 = gather(e.y >> 16);
-            uint32_t c;
-            if constexpr (PER == 1) {
-                const uint32_t t0 = carry_add(cl[0], x0, x1), t1 = carry_add(cl[0], x2, x3);
-                c = carry_add(cl[1], t0, t1);
-            } else {
-                const uint32_t t0 = carry_add(cl[0], x0 | x1 << 16, x2 | x3 << 16);
-                c = cl[1] & t0;
-                cl[1] ^= t0;
-            }
-#pragma unroll
-            for (int p = 2; p < P; ++p) {
-                const uint32_t d = cl[p] & c;
-                cl[p] ^= c;
-                c = d;
-            }
+            if constexpr (PER == 1) count4(x0, x1, x2, x3);
+            else count4(x0 | x1 << 16, x2 | x3 << 16, 0u, 0u);
         }
         // the quads, their first two rows of entries loaded one quad ahead
+        uint32_t hold[kHold];
         u32x4 ra[2], rb[2];
-        uint32_t wd[2], rx[2];
-        uint32_t row = row0;
+        uint32_t wd[2], rx[2], row = ((const_u32)D->rows.wave_row)[wave] * 1024u;
         auto issue = [&](int g) {
-            const uint32_t w = codes[g];
+            const uint32_t w = ((const_u32)D->rows.codes)[wave * NQ + g];
             const uint32_t on = ((act >> g) & 1u) ? w : 0u;
-            ra[g & 1] = row_of(row, on > 0u);
-            rb[g & 1] = row_of(row + 1024u, on > 2u);
+            ra[g & 1] = row_of(ent, row, on > 0u);
+            rb[g & 1] = row_of(ent, row + 1024u, on > 2u);
             wd[g & 1] = on;
             rx[g & 1] = row + 2048u;
             row += ((w + 1u) >> 1) * 1024u;
@@ -321,7 +426,11 @@ __global__ __launch_bounds__(KT) void k_count(const GraphDev *__restrict__ graph
         for (int g = 0; g < NQ; ++g) {
             const uint32_t w = wd[g & 1], xr = rx[g & 1];
             const u32x4 a = ra[g & 1], b = rb[g & 1];
-            const u32x4 c = row_of(xr, w > 4u), d = row_of(xr + 1024u, w > 6u);
+            u32x4 c, d;
+            if constexpr (kWide) {
+                c = row_of(ent, xr, w > 4u);
+                d = row_of(ent, xr + 1024u, w > 6u);
+            }
             if (g + 1 < NQ) issue(g + 1);
             uint32_t x[4] = {0u, 0u, 0u, 0u};
             // one entry of each of the 4 positions
@@ -343,13 +452,17 @@ __global__ __launch_bounds__(KT) void k_count(const GraphDev *__restrict__ graph
             if (w) {
                 uint32_t all = ~0u;
 #pragma unroll
-                for (int i = 0; i < QW; ++i) all &= seen[g * QW + i];
+                for (int i = 0; i < QW; ++i) all &= seen_of(g * QW + i);
                 if (all != ~0u) {
                     if (w >= 2u) pair(a);
                     else slot(a.x, a.y);
                     if (w >= 4u) pair(b);
                     else if (w == 3u) slot(b.x, b.y);
                     if (w > 4u) {
+                        if constexpr (!kWide) {
+                            c = row_of(ent, xr, true);
+                            d = row_of(ent, xr + 1024u, w > 6u);
+                        }
                         if (w >= 6u) pair(c);
                         else slot(c.x, c.y);
                         if (w >= 8u) pair(d);
@@ -357,10 +470,10 @@ __global__ __launch_bounds__(KT) void k_count(const GraphDev *__restrict__ graph
                         if (w > 8u) {
                             // longer rows: two entries per step, the next two in flight
                             uint32_t r = xr + 2048u;
-                            u32x4 z = row_of(r, true);
+                            u32x4 z = row_of(ent, r, true);
                             for (uint32_t k = 8u; k < w; k += 2u) {
                                 r += (k + 2u < w) ? 1024u : 0u;
-                                const u32x4 zn = row_of(r, true);
+                                const u32x4 zn = row_of(ent, r, true);
                                 if (k + 1u < w) pair(z);
                                 else slot(z.x, z.y);
                                 z = zn;
@@ -369,14 +482,21 @@ __global__ __launch_bounds__(KT) void k_count(const GraphDev *__restrict__ graph
                     }
                 }
             }
+            uint32_t y[QW];
 #pragma unroll
-            for (int i = 0; i < QW; ++i) {
-                const uint32_t v = (PER == 1) ? x[i] : (x[2 * i] | x[2 * i + 1] << 16);
-                y[g * QW + i] = v & ~seen[g * QW + i];
+            for (int i = 0; i < QW; ++i)
+                y[i] = ((PER == 1) ? x[i] : (x[2 * i] | x[2 * i + 1] << 16)) & ~seen_of(g * QW + i);
+            if (!kTwo || g < kHubQuads) {
+#pragma unroll
+                for (int i = 0; i < QW; ++i) hold[g * QW + i] = y[i];
+            } else {
+                settle(g, y);
+                if constexpr (PER == 1) count4(y[0], y[1], y[QW > 2 ? 2 : 0], y[QW > 3 ? 3 : 0]);
+                else count4(y[0], y[1], 0u, 0u);
             }
         }
         __syncthreads();
-        // B. hub rows, then the next frontier
+        // B. hub rows; the held quads' next frontier
 #pragma unroll
         for (int g = 0; g < kHubQuads; ++g) {
             if ((g * KT + wave * 64) * 4 < n_hub) {
@@ -386,52 +506,34 @@ __global__ __launch_bounds__(KT) void k_count(const GraphDev *__restrict__ graph
                 const uint32_t v[4] = {a.x, a.y, a.z, a.w};
 #pragma unroll
                 for (int i = 0; i < QW; ++i)
-                    y[g * QW + i] |= ((PER == 1) ? v[i] : (v[2 * i] | v[2 * i + 1] << 16)) & ~seen[g * QW + i];
+                    hold[g * QW + i] |=
+                        ((PER == 1) ? v[i] : (v[2 * i] | v[2 * i + 1] << 16)) & ~seen_of(g * QW + i);
             }
         }
-        uint32_t any = 0u;
 #pragma unroll
-        for (int p = 0; p < P; ++p) any |= cl[p];
-#pragma unroll
-        for (int g = 0; g < NQ; ++g) {
-            uint32_t all = ~0u;
-#pragma unroll
-            for (int i = 0; i < QW; ++i) {
-                front[own(g) + i] = y[g * QW + i];
-                seen[g * QW + i] |= y[g * QW + i];
-                any |= y[g * QW + i];
-                all &= seen[g * QW + i];
-            }
-            if (!__ballot(all != ~0u)) act &= ~(1u << g);
-            if (g < kHubQuads && (g * KT + wave * 64) * 4 < n_hub) {
-                // which hubs are done: bit (i, lane) of the quad's 256 positions
-                uint32_t v = 0u;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const uint32_t s = (PER == 1) ? seen[g * QW + i / PER] : (seen[g * QW + i / PER] >> (16 * (i % PER))) & 0xFFFFu;
-                    const uint64_t o = __ballot(s == kFull);
-                    if (lane == 2 * i) v = (uint32_t)o;
-                    if (lane == 2 * i + 1) v = (uint32_t)(o >> 32);
-                }
-                if (lane < 8) hdone[(g * KT + wave * 64) / 8 + lane] = v;
-            }
-        }
+        for (int g = 0; g < kHold / QW; ++g) settle(g, hold + g * QW);
         uint32_t *const lc = cnt[level % 3];
+#pragma unroll
+        for (int p = 0; p < CB; ++p) any |= cl[p];
         if (__ballot(any != 0u)) {
-            uint32_t plane[P];
-            add_columns<NW, 0, P>(y, plane);
-            if (n_leaf) {
+            if (P > 0 && lane == 0) lc[16] = 1u;
+            uint32_t sum[CB];
+            add_columns<kHold, 0, CB>(hold, sum);
+            if (kTwo || n_leaf) {
                 uint32_t c = 0u;
 #pragma unroll
-                for (int p = 0; p < P; ++p) c = carry_add(plane[p], cl[p], c);
+                for (int p = 0; p < CB; ++p) c = carry_add(sum[p], cl[p], c);
             }
+            int lane_now = lane;    // (recomputed per level instead of held in registers)
+            asm volatile("" : "+v"(lane_now));
+            const ColumnRoles roles(lane_now);
             uint32_t lo = 0u, hi = 0u;
 #pragma unroll
-            for (int p = P - 1; p >= 0; --p) {
+            for (int p = CB - 1; p >= 0; --p) {
                 lo <<= 1;
                 hi <<= 1;
-                if (p < 2 || __ballot(plane[p] != 0u)) {
-                    const uint32_t t = gather_columns(plane[p], roles);
+                if (p < 2 || __ballot(sum[p] != 0u)) {
+                    const uint32_t t = gather_columns(sum[p], roles);
                     lo += (uint32_t)__popc(t & 0xFFFFu);
                     hi += (uint32_t)__popc(t >> 16);
                 }
@@ -449,17 +551,158 @@ __global__ __launch_bounds__(KT) void k_count(const GraphDev *__restrict__ graph
             c = lc[lane & 15];
             if constexpr (PER == 1) c = (lane < 16) ? (c & 0xFFFFu) : (c >> 16);
         }
-        // the counters of the level after next: last read before this
-        // level's first barrier, next added to after the next level's
-        if (tid < 16) cnt[(level + 2) % 3][tid] = 0u;
-        if (!__ballot(c != 0u)) break;     // nothing new: every search ended
-        last = level;
+        const bool any_new = P > 0 ? lc[16] != 0u : __ballot(c != 0u) != 0;
+        // the counters of the level after next: last read after the previous
+        // level's last barrier, next added to after this level's successor's
+        if (tid < 17) cnt[(level + 2) % 3][tid] = 0u;
+        if (!any_new) return true;         // nothing new: every search ended
+        if (__ballot(c != 0u)) last = level;
         if (level > kMaxDist) {
             overflow = true;
-            break;
+            return true;
         }
         if (wave == 0 && lane < nb && level < K) hist[level] = (int32_t)c;
         left -= c;
+        return !__ballot(left != 0u);
+    };
+    if (__ballot(left != 0u)) {
+        for (int level = 2;; ++level)
+            if (run_level(level)) break;
+    }
+    if constexpr (P > 0) {
+        // The distance rows. The planes go from the positions' owners to the
+        // nodes' (quads of 4 consecutive nodes per lane) through the frontier's
+        // LDS, one plane at a time: a node reads its position's word, a leaf its
+        // neighbour's, to which it adds one.
+        constexpr int NN = NQN * QW;
+        typedef __attribute__((address_space(1))) int8_t gbyte;
+        typedef uint32_t __attribute__((aligned(1))) u32_any;   // rows need not be 4-byte aligned
+        typedef __attribute__((address_space(1))) u32_any gu32;
+        const int n = G.n;
+        gbyte **const rows = (gbyte **)hacc;                    // (HUB >= 256 words)
+        __syncthreads();
+        if (tid < nb) rows[tid] = (gbyte *)G.dist + (int64_t)(src[tid].x & 0xFFFFu) * G.ld;
+        const uint2 *__restrict__ node_pos = (const uint2 *)G.rows.node_pos;
+        auto gather = [&](int f, uint32_t p) -> uint32_t {
+            const uint32_t *const x = fields + f * NW * KT;
+            if constexpr (PER == 1) return x[p];
+            else return ((const uint16_t *)x)[p];
+        };
+        // plane p of the positions into field p % 2
+        auto publish = [&](int p) {
+#pragma unroll
+            for (int g = 0; g < NQ; ++g)
+#pragma unroll
+                for (int i = 0; i < QW; ++i) fields[(p & 1) * NW * KT + own(g) + i] = plane[g * QW + i][p];
+        };
+        // planes p0.. of node quad g from the fields into d[][p0..]
+        uint32_t d[NN][PA];
+        auto fetch = [&](int g, int p0, int count) {
+            const int v0 = (g * KT + tid) * 4;
+            const uint2 e = (v0 < n) ? node_pos[v0 >> 2] : make_uint2(0u, 0u);
+#pragma unroll
+            for (int q = 0; q < count; ++q) {
+                const int p = p0 + q;
+                const uint32_t x0 = gather(p & 1, e.x & 0xFFFFu), x1 = gather(p & 1, e.x >> 16);
+                const uint32_t x2 = gather(p & 1, e.y & 0xFFFFu), x3 = gather(p & 1, e.y >> 16);
+                if constexpr (PER == 1) {
+                    d[4 * g + 0][p] = x0;
+                    d[4 * g + 1][p] = x1;
+                    d[4 * g + 2][p] = x2;
+                    d[4 * g + 3][p] = x3;
+                } else {
+                    d[2 * g + 0][p] = x0 | x1 << 16;
+                    d[2 * g + 1][p] = x2 | x3 << 16;
+                }
+            }
+        };
+        // all but the last (one or two) planes into registers; the last are
+        // fetched quad by quad below, so the quads' registers die one by one
+        constexpr int kLate = 2 - (PA & 1);
+#pragma unroll
+        for (int p0 = 0; p0 + kLate < PA; p0 += 2) {
+            __syncthreads();
+            publish(p0);
+            publish(p0 + 1);
+            __syncthreads();
+#pragma unroll
+            for (int g = 0; g < NQN; ++g) fetch(g, p0, 2);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int p = PA - kLate; p < PA; ++p) publish(p);
+        __syncthreads();
+        const uint32_t *__restrict__ flags = G.rows.node_flags;
+#pragma unroll
+        for (int g = 0; g < NQN; ++g) {
+            const int v0 = (g * KT + tid) * 4;
+            if (v0 >= n) continue;
+            fetch(g, PA - kLate, kLate);
+            // per node 2 bits: 1 leaf (one more than its neighbour), 2 no edges
+            const uint32_t f = flags[v0 >> 4] >> (2 * (v0 & 15));
+            uint32_t a[QW][8];
+#pragma unroll
+            for (int i = 0; i < QW; ++i) {
+                uint32_t leaf = 0u, alone = 0u;
+#pragma unroll
+                for (int h = 0; h < PER; ++h) {
+                    const uint32_t b = f >> (2 * (i * PER + h));
+                    if (b & 1u) leaf |= kFull << (16 * h);
+                    if (b & 2u) alone |= kFull << (16 * h);
+                }
+                uint32_t u = d[g * QW + i][0];
+#pragma unroll
+                for (int p = 1; p < PA; ++p) u &= d[g * QW + i][p];
+                u |= alone;
+                uint32_t c = leaf & ~u;
+#pragma unroll
+                for (int p = 0; p < PA; ++p) {
+                    const uint32_t t = d[g * QW + i][p];
+                    a[i][p] = (t ^ c) | u;
+                    c &= t;
+                }
+#pragma unroll
+                for (int p = PA; p < 8; ++p) a[i][p] = u;
+                transpose_bytes(a[i]);
+            }
+            // byte j of a[i][k]: PER 1: node v0 + i, source 8j + k; PER 2: node
+            // v0 + 2i + j / 2, source 8 (j % 2) + k
+            auto quad = [&](int k, uint32_t (&o)[4 / PER]) {
+                if constexpr (PER == 1) {
+                    const uint32_t t0 = __builtin_amdgcn_perm(a[1][k], a[0][k], 0x05010400u);
+                    const uint32_t t1 = __builtin_amdgcn_perm(a[1][k], a[0][k], 0x07030602u);
+                    const uint32_t t2 = __builtin_amdgcn_perm(a[3][k], a[2][k], 0x05010400u);
+                    const uint32_t t3 = __builtin_amdgcn_perm(a[3][k], a[2][k], 0x07030602u);
+                    o[0] = __builtin_amdgcn_perm(t2, t0, 0x05040100u);
+                    o[1] = __builtin_amdgcn_perm(t2, t0, 0x07060302u);
+                    o[2] = __builtin_amdgcn_perm(t3, t1, 0x05040100u);
+                    o[3] = __builtin_amdgcn_perm(t3, t1, 0x07060302u);
+                } else {
+                    o[0] = __builtin_amdgcn_perm(a[1][k], a[0][k], 0x06040200u);
+                    o[1] = __builtin_amdgcn_perm(a[1][k], a[0][k], 0x07050301u);
+                }
+            };
+            if (v0 + 3 < n && nb == BW) {
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    uint32_t o[4 / PER];
+                    quad(k, o);
+#pragma unroll
+                    for (int j = 0; j < 4 / PER; ++j) *(gu32 *)(rows[8 * j + k] + v0) = o[j];
+                }
+            } else {
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    uint32_t o[4 / PER];
+                    quad(k, o);
+#pragma unroll
+                    for (int j = 0; j < 4 / PER; ++j)
+                        if (8 * j + k < nb)
+                            for (int i = 0; i < 4 && v0 + i < n; ++i)
+                                rows[8 * j + k][v0 + i] = (int8_t)((o[j] >> (8 * i)) & 0xFFu);
+                }
+            }
+        }
     }
     if (wave == 0) {
         if (lane < nb)

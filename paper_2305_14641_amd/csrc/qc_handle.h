@@ -25,11 +25,15 @@ struct RowsState {
     std::vector<uint8_t> kind;        // RowsKind per node
     std::vector<uint16_t> pos;        // position of every core node
     std::vector<uint32_t> first;      // its entries in col_pos
+    std::vector<int32_t> comp;        // own nodes of every node's component (weighted edges only)
+    int planes = 0, nqn = 0;          // distance rows (RowsDistPlan); 0: histograms only
     qc::RowsDev dev{};                // pointers to the buffers below
     uint32_t *d_src = nullptr;        // [4 n_search]
     uint16_t *d_col_pos = nullptr, *d_ent = nullptr, *d_leaf = nullptr;
     uint32_t *d_codes = nullptr, *d_units = nullptr, *d_wave_row = nullptr, *d_wave_unit = nullptr;
     uint32_t *d_rest = nullptr;
+    uint16_t *d_node_pos = nullptr;
+    uint32_t *d_node_flags = nullptr;
     BfsJob *d_jobs = nullptr;
     int n_jobs = 0;
     NodeJob *d_rest_jobs = nullptr;
@@ -46,6 +50,7 @@ struct qc_graph_s {
     int64_t nnz = 0;
     int32_t n_components = 0;
     std::vector<int32_t> row_ptr, col;   // the canonical CSR (host copy)
+    std::vector<int32_t> bfs_row_ptr, bfs_col;   // and the subdivided one (weighted edges)
     bool directed = false;
     std::vector<int32_t> comp_size;   // size of each node's component (host)
     BfsPlan plan{};
@@ -72,6 +77,7 @@ struct qc_graph_s {
     int edges_bias = 0;               // row bias of d_edges (bfs_row_bias of the plan; -1: unknown)
 
     RowsState rows;                   // the counting search
+    RowsState drows;                  // the same search writing distance rows
 
     // distances and histograms
     int8_t *d_dist_owned = nullptr;   // library-owned matrix (n rows of owned_ld(n), 16-byte padded)
@@ -110,6 +116,11 @@ struct qc_graph_s {
     int n_hist_jobs = 0;
     int hist_jobs_k = 0;
 
+    GraphDev desc_last;                       // what push_desc wrote last, and where
+    hipStream_t desc_stream = nullptr;
+    bool desc_pushed = false, desc_captured = false;
+    bool dist_desc = false;                   // the descriptor carries drows' tables, not rows'
+
     GraphDev desc() const
     {
         GraphDev d;
@@ -145,7 +156,7 @@ struct qc_graph_s {
         d.parent = d_parent;
         d.status = d_status;
         d.recheck = d_recheck;
-        d.rows = rows.dev;
+        d.rows = dist_desc ? drows.dev : rows.dev;
         return d;
     }
 };
@@ -279,7 +290,12 @@ qc_status run_distances(qc_graph g, hipStream_t st);
 bool can_count(qc_graph g);
 // Build and upload the counting search's tables (a no-op when they are there).
 qc_status ensure_rows(qc_graph g);
-void free_rows(qc_graph g);
+void free_rows(qc_graph g, RowsState &r);
+// The tables of the search that writes distance rows; r.planes stays 0 when
+// no shape holds the graph (the matrix search of qc_bfs.h takes it).
+qc_status ensure_dist_rows(qc_graph g);
+// Distances (and histograms) by it, into the handle's current matrix.
+qc_status run_dist_rows(qc_graph g, hipStream_t st);
 // After a change of the source order: the counting search's source table.
 qc_status reorder_rows(qc_graph g);
 // The sources by exact eccentricity (after the first search).

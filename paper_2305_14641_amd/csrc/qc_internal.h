@@ -81,11 +81,18 @@ struct RowsDev {
     const uint32_t *wave_row;    // [waves] first 1,024-byte row of a wavefront's quads in `ent`
     const uint32_t *wave_unit;   // [waves + 1] its hub units
     const void *ent;             // entries of the quads, 64 lanes x 2 slots x 4 positions x 16 bits per row
-    const void *units;           // hub units: 64 lanes x 8 x 16 bits, then 64 targets
+    const void *units;           // hub units: 64 lanes x 8 x 16 bits, then 64 targets (the
+                                 // hub's accumulator | its done flag's bit << 16)
     const void *leaf;            // positions of the leaves' neighbours, 16 bits each
     uint32_t ent_bytes;
-    int32_t n_hub;
-    int32_t n_pos;               // nodes with a position
+    int32_t n_hub;               // the first positions
+    int32_t n_pos;               // positions in use
+    int32_t n_own;               // positions of the graph's own nodes (weighted edges: the nodes
+                                 // inside edges come after them, from the next multiple of 256 on)
+    // For the distance rows: per node its position (a leaf's: its
+    // neighbour's), and 2 bits (1: a leaf, 2: no edges).
+    const uint16_t *node_pos;
+    const uint32_t *node_flags;
     int32_t n_leaf;              // leaves, rounded up to a multiple of 4
     int32_t n_search;            // sources to search
     // Nodes that are not searched: node | neighbour << 16, the leaves first,
@@ -216,6 +223,13 @@ hipError_t launch_count(int nq, int threads, int per, const GraphDev *graphs, co
                         int n_jobs, hipStream_t stream);
 hipError_t launch_count_512(int nq, const GraphDev *graphs, const BfsJob *jobs, int n_jobs,
                             hipStream_t stream);
+// The same search writing the distance rows of its sources too (qc_dist_*.hip;
+// plan_rows_dist lists the shapes), and the distance and histogram rows of the
+// n_rest other nodes from them (histogram rows of K bins).
+hipError_t launch_dist_4(int nq, int nqn, const GraphDev *graphs, const BfsJob *jobs, int n_jobs, hipStream_t stream);
+hipError_t launch_dist_5(int nq, int nqn, const GraphDev *graphs, const BfsJob *jobs, int n_jobs, hipStream_t stream);
+hipError_t launch_dist_7(int nq, int nqn, const GraphDev *graphs, const BfsJob *jobs, int n_jobs, hipStream_t stream);
+hipError_t launch_dist_rest(int K, const GraphDev *graph, int n_rest, hipStream_t stream);
 // Histogram rows of the other nodes (one job = 32 of them) from the
 // searched ones, `waves` wavefronts per workgroup.
 hipError_t launch_hist_rest(int K, const GraphDev *graphs, const NodeJob *jobs, int n_jobs, int waves,

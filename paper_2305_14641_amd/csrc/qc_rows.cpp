@@ -30,6 +30,32 @@ RowsPlan plan_rows(int32_t n_pos)
     return p;
 }
 
+RowsDistPlan plan_rows_dist(int32_t n, int32_t n_pos, int32_t dmax)
+{
+    RowsDistPlan d;
+    d.planes = dmax <= 14 ? 4 : dmax <= 30 ? 5 : 7;
+    d.rows.threads = 1024;
+    const int32_t need = n_pos < 65536 ? n_pos + 1 : n_pos;
+    // About 16 words x 4 planes are what the registers hold: larger shapes
+    // spill (qc_dist_*.hip have the same list). What no shape holds stays with
+    // the matrix search (qc_bfs.h), which takes 8 sources at that size.
+    struct Shape { int nq, per; };
+    static const Shape kShapes[] = {{1, 1}, {2, 1}, {3, 1}, {4, 1}, {5, 2}, {6, 2}};
+    const int most = d.planes == 4 ? 6 : d.planes == 5 ? 5 : 2;
+    for (const Shape &x : kShapes) {
+        if (x.nq > most) break;
+        if (need > x.nq * 4096) continue;
+        for (int nqn = x.nq; nqn <= x.nq + 1; ++nqn)
+            if (n <= nqn * 4096) {
+                d.rows.nq = x.nq;
+                d.rows.per = x.per;
+                d.nqn = nqn;
+                return d;
+            }
+    }
+    return d;
+}
+
 std::vector<uint8_t> rows_kinds(int32_t n, const std::vector<int32_t> &rp,
                                 const std::vector<int32_t> &col, bool leaves)
 {
@@ -53,7 +79,7 @@ std::vector<uint8_t> rows_kinds(int32_t n, const std::vector<int32_t> &rp,
     return k;
 }
 
-RowsTables build_rows(int32_t n, const std::vector<int32_t> &rp, const std::vector<int32_t> &col,
+RowsTables build_rows(int32_t n, int32_t own, const std::vector<int32_t> &rp, const std::vector<int32_t> &col,
                       bool directed, const std::vector<int32_t> &comp_size,
                       const std::vector<uint8_t> &kind, const RowsPlan &plan)
 {
@@ -75,17 +101,19 @@ RowsTables build_rows(int32_t n, const std::vector<int32_t> &rp, const std::vect
     const std::vector<int32_t> &R = directed ? irp : rp, &C = directed ? icol : col;
     // a core node's entries: its in-neighbours that are core nodes
     std::vector<int32_t> len(n, 0);
-    int32_t largest = 0, maxlen = 0, n_pos = 0;
+    int32_t largest = 0, maxlen = 0, n_core = 0, n_own = 0;
     for (int32_t v = 0; v < n; ++v) {
         if (kind[v] != kRowsCore) continue;
         int32_t d = 0;
         for (int32_t e = R[v]; e < R[v + 1]; ++e) d += kind[C[e]] == kRowsCore;
         len[v] = d;
-        ++n_pos;
+        ++n_core;
+        n_own += v < own;
         largest = std::max(largest, comp_size[v]);
         maxlen = std::max(maxlen, d);
     }
-    t.n_pos = n_pos;
+    const int32_t n_pos = t.n_pos = rows_positions(n_core, n_own);
+    t.n_own = n_own;
     std::vector<int32_t> count(maxlen + 2, 0);
     for (int32_t v = 0; v < n; ++v)
         if (kind[v] == kRowsCore) ++count[len[v]];
@@ -99,19 +127,23 @@ RowsTables build_rows(int32_t n, const std::vector<int32_t> &rp, const std::vect
             break;
         }
     }
-    // positions: by decreasing number of entries, those of the largest
-    // component first (counting sort)
-    std::vector<int32_t> by_pos(n_pos);
+    // positions: the hubs, then by decreasing number of entries, those of the
+    // largest component first (counting sort); nodes inside edges, never hubs
+    // (they have two entries at most), come last
+    std::vector<int32_t> by_pos(n_pos, -1);
     t.pos.assign(n, 0);
     {
         auto key = [&](int32_t v) {   // smaller first
+            if (v >= own) return 2 * (maxlen + 1) + maxlen - len[v];
             if (len[v] > cut) return maxlen - len[v];
             return (comp_size[v] == largest ? 0 : maxlen + 1) + maxlen - len[v];
         };
-        std::vector<int32_t> start(2 * (maxlen + 1) + 1, 0);
+        std::vector<int32_t> start(3 * (maxlen + 1) + 1, 0);
         for (int32_t v = 0; v < n; ++v)
             if (kind[v] == kRowsCore) ++start[key(v) + 1];
         std::partial_sum(start.begin(), start.end(), start.begin());
+        if (n_core > n_own)
+            for (int k = 2 * (maxlen + 1); k <= 3 * (maxlen + 1); ++k) start[k] += n_pos - n_core;
         for (int32_t v = 0; v < n; ++v)
             if (kind[v] == kRowsCore) {
                 const int32_t p = start[key(v)]++;
@@ -133,7 +165,6 @@ RowsTables build_rows(int32_t n, const std::vector<int32_t> &rp, const std::vect
     const bool spare = n_pos < plan.capacity();
     const uint16_t zero_pos = (uint16_t)(spare ? n_pos : 0);
 
-    std::vector<double> load(waves, 0.0);
     t.codes.assign((size_t)waves * nq, 0u);
     t.wave_row.assign(waves, 0u);
     size_t rows = 0;
@@ -143,10 +174,9 @@ RowsTables build_rows(int32_t n, const std::vector<int32_t> &rp, const std::vect
             const int32_t p0 = (g * plan.threads + w * 64) * 4;
             int32_t wd = 0;
             for (int32_t p = std::max(p0, t.n_hub); p < std::min(n_pos, p0 + 256); ++p)
-                wd = std::max(wd, len[by_pos[p]]);
+                if (by_pos[p] >= 0) wd = std::max(wd, len[by_pos[p]]);
             t.codes[(size_t)w * nq + g] = (uint32_t)wd;
             rows += (size_t)(wd + 1) / 2;
-            load[w] += 4.0 * wd + 8.0;
         }
     }
     t.ent.assign(rows * 512, zero_pos);
@@ -162,6 +192,7 @@ RowsTables build_rows(int32_t n, const std::vector<int32_t> &rp, const std::vect
                         base[(k / 2) * 512 + (i / 4) * 8 + (k % 2) * 4 + i % 4] = (uint16_t)(p0 + i);
             for (int32_t p = std::max(p0, t.n_hub); p < std::min(n_pos, p0 + 256); ++p) {
                 const int32_t v = by_pos[p], i = p - p0;
+                if (v < 0) continue;
                 uint16_t *const mine = base + (i / 4) * 8 + i % 4;
                 int32_t k = 0;
                 for (int32_t e = R[v]; e < R[v + 1]; ++e)
@@ -202,6 +233,9 @@ RowsTables build_rows(int32_t n, const std::vector<int32_t> &rp, const std::vect
             t.units[u * 320 + 256 + l] = ut[u * 64 + l];
         }
     }
+    std::vector<double> load(waves, 0.0);
+    for (int w = 0; w < waves; ++w)
+        for (int g = 0; g < nq; ++g) load[w] += 4.0 * t.codes[(size_t)w * nq + g] + 8.0;
     std::vector<uint32_t> share(waves, 0u);
     for (size_t u = 0; u < nu; ++u) {
         const size_t w = (size_t)(std::min_element(load.begin(), load.end()) - load.begin());
@@ -213,7 +247,7 @@ RowsTables build_rows(int32_t n, const std::vector<int32_t> &rp, const std::vect
     // leaves, in the order of their neighbours' positions
     for (int32_t p = 0; p < n_pos; ++p) {
         const int32_t v = by_pos[p];
-        if (directed || len[v] == rp[v + 1] - rp[v]) continue;
+        if (directed || v < 0 || len[v] == rp[v + 1] - rp[v]) continue;
         for (int32_t k = len[v]; k < rp[v + 1] - rp[v]; ++k) t.leaf.push_back((uint16_t)p);
     }
     while (t.leaf.size() % 4) t.leaf.push_back(zero_pos);   // (leaves leave a spare position)

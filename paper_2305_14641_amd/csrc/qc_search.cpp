@@ -1,5 +1,5 @@
-// The counting search on a graph handle: its tables, and histograms without
-// the distance matrix.
+// The counting search on a graph handle: its tables, histograms without the
+// distance matrix, and the same search writing distance rows.
 #include <stdlib.h>
 #include <string.h>
 
@@ -12,24 +12,31 @@ namespace qc {
 bool can_count(qc_graph g) { return !g->weighted && !getenv("QC_BFS_SHAPE"); }
 
 // The sources in the handle's order, with what the search needs of each.
-static std::vector<uint32_t> source_table(qc_graph g)
+static std::vector<uint32_t> source_table(qc_graph g, const RowsState &r)
 {
-    const RowsState &r = g->rows;
     std::vector<uint32_t> t;
     t.reserve(4 * (size_t)r.dev.n_search);
+    const std::vector<int32_t> &rp = g->weighted ? g->bfs_row_ptr : g->row_ptr;
+    const std::vector<int32_t> &comp = g->weighted ? r.comp : g->comp_size;
     for (int32_t v : g->src_order) {
         if (r.kind[v] != kRowsCore) continue;
+        // own nodes at distance 1: with weights, those that no node inside
+        // an edge stands before
+        uint32_t deg = (uint32_t)(rp[v + 1] - rp[v]);
+        if (g->weighted) {
+            deg = 0;
+            for (int32_t e = rp[v]; e < rp[v + 1]; ++e) deg += g->bfs_col[e] < g->n;
+        }
         t.push_back((uint32_t)v | (uint32_t)r.pos[v] << 16);
         t.push_back(r.first[v]);
-        t.push_back((uint32_t)(g->row_ptr[v + 1] - g->row_ptr[v]) | (r.first[v + 1] - r.first[v]) << 16);
-        t.push_back((uint32_t)g->comp_size[v]);
+        t.push_back(deg | (r.first[v + 1] - r.first[v]) << 16);
+        t.push_back((uint32_t)comp[v]);
     }
     return t;
 }
 
-void free_rows(qc_graph g)
+void free_rows(qc_graph g, RowsState &r)
 {
-    RowsState &r = g->rows;
     gfree(g, r.d_src);
     gfree(g, r.d_col_pos);
     gfree(g, r.d_codes);
@@ -39,42 +46,86 @@ void free_rows(qc_graph g)
     gfree(g, r.d_units);
     gfree(g, r.d_leaf);
     gfree(g, r.d_rest);
+    gfree(g, r.d_node_pos);
+    gfree(g, r.d_node_flags);
     gfree(g, r.d_jobs);
     gfree(g, r.d_rest_jobs);
     r.dev = RowsDev{};
     r.ready = false;
 }
 
-qc_status ensure_rows(qc_graph g)
+// Build and upload r's tables; with `dist`, those of the search that writes
+// distance rows (nothing is built when no shape holds the graph).
+static qc_status make_rows(qc_graph g, RowsState &r, bool dist)
 {
-    RowsState &r = g->rows;
-    if (r.ready) return QC_OK;
+    const bool w = g->weighted;
+    const std::vector<int32_t> &rp = w ? g->bfs_row_ptr : g->row_ptr, &col = w ? g->bfs_col : g->col;
     // With the sources in node order (QC_SOURCE_ORDER=identity, a switch for
     // measurements and tests) every node is searched.
     const char *so = getenv("QC_SOURCE_ORDER");
     if (so && strcmp(so, "identity") == 0)
-        r.kind.assign(g->n, kRowsCore);
+        r.kind.assign(g->n_bfs, kRowsCore);
     else
-        r.kind = rows_kinds(g->n, g->row_ptr, g->col, !g->directed);
+        r.kind = rows_kinds(g->n_bfs, rp, col, !g->directed && !w);
     const int32_t n_core = (int32_t)std::count(r.kind.begin(), r.kind.end(), (uint8_t)kRowsCore);
-    r.plan = plan_rows(n_core);
-    RowsTables t = build_rows(g->n, g->row_ptr, g->col, g->directed, g->comp_size, r.kind, r.plan);
+    const int32_t n_own = (int32_t)std::count(r.kind.begin(), r.kind.begin() + g->n, (uint8_t)kRowsCore);
+    if (dist) {
+        const RowsDistPlan p = plan_rows_dist(g->n, rows_positions(n_core, n_own), g->dmax_bfs);
+        r.planes = p.rows.nq ? p.planes : 0;
+        r.nqn = p.nqn;
+        r.plan = p.rows;
+        if (!r.planes) {
+            r.ready = true;
+            return QC_OK;
+        }
+    } else {
+        r.plan = plan_rows(n_core);
+    }
+    if (w) {
+        std::vector<int32_t> label(g->n_bfs);
+        r.comp.assign(g->n_bfs, 0);
+        // own nodes per (weak) component of the subdivided graph
+        std::vector<int32_t> all;
+        (void)count_components(g->n_bfs, rp, col, &all, &label);
+        std::vector<int32_t> own(g->n_bfs, 0);
+        for (int32_t v = 0; v < g->n; ++v) ++own[label[v]];
+        for (int32_t v = 0; v < g->n_bfs; ++v) r.comp[v] = own[label[v]];
+    }
+    const RowsTables t = build_rows(g->n_bfs, g->n, rp, col, g->directed, w ? r.comp : g->comp_size, r.kind, r.plan);
     r.pos = t.pos;
     r.first = t.first;
     r.dev = RowsDev{};
-    r.dev.n_search = r.dev.n_pos = t.n_pos;
+    r.dev.n_search = n_own;
+    r.dev.n_pos = t.n_pos;
+    r.dev.n_own = t.n_own;
     r.dev.n_hub = t.n_hub;
     r.dev.n_leaf = t.n_leaf;
     r.dev.ent_bytes = (uint32_t)(t.ent.size() * sizeof(uint16_t));
-    const std::vector<uint32_t> rest =
-        rest_table(g->n, g->row_ptr, g->col, r.kind, r.dev.n_rest_leaf, r.dev.n_rest_pair);
+    const std::vector<uint32_t> rest = rest_table(g->n, rp, col, r.kind, r.dev.n_rest_leaf, r.dev.n_rest_pair);
     r.dev.n_rest = (int32_t)rest.size();
-    const std::vector<uint32_t> src = source_table(g);
+    const std::vector<uint32_t> src = source_table(g, r);
+    std::vector<uint16_t> node_pos;
+    std::vector<uint32_t> node_flags;
+    if (dist) {
+        node_pos.assign((size_t)(g->n + 3) / 4 * 4, 0);
+        node_flags.assign((size_t)(g->n + 15) / 16, 0u);
+        for (int32_t v = 0; v < g->n; ++v) {
+            const uint32_t sh = 2u * (uint32_t)(v % 16);
+            if (r.kind[v] == kRowsCore) {
+                node_pos[v] = t.pos[v];
+            } else if (r.kind[v] == kRowsLeaf) {
+                node_pos[v] = t.pos[col[rp[v]]];
+                node_flags[v / 16] |= 1u << sh;
+            } else {
+                node_flags[v / 16] |= 2u << sh;
+            }
+        }
+    }
     std::vector<BfsJob> jobs;
     const int bw = r.plan.batch();
     // last batch first: the source order puts the farthest-reaching sources
     // (the longest searches) at the end
-    for (int s0 = (t.n_pos + bw - 1) / bw * bw - bw; s0 >= 0; s0 -= bw) jobs.push_back(BfsJob{0, s0, 0u, 0u});
+    for (int s0 = (n_own + bw - 1) / bw * bw - bw; s0 >= 0; s0 -= bw) jobs.push_back(BfsJob{0, s0, 0u, 0u});
     std::vector<NodeJob> rjobs;
     for (int i = 0; i < r.dev.n_rest; i += 32) rjobs.push_back(NodeJob{0, i, 0});
     qc_status s = galloc(g, &r.d_src, src.size());
@@ -88,13 +139,16 @@ qc_status ensure_rows(qc_graph g)
     if (s == QC_OK) s = galloc(g, &r.d_rest, rest.size());
     if (s == QC_OK) s = galloc(g, &r.d_jobs, jobs.size());
     if (s == QC_OK) s = galloc(g, &r.d_rest_jobs, rjobs.size());
+    if (s == QC_OK && dist) s = galloc(g, &r.d_node_pos, node_pos.size());
+    if (s == QC_OK && dist) s = galloc(g, &r.d_node_flags, node_flags.size());
     if (s == QC_OK)
         s = upload_group(g, {span_of(r.d_src, src), span_of(r.d_col_pos, t.col_pos), span_of(r.d_codes, t.codes),
                              span_of(r.d_wave_row, t.wave_row), span_of(r.d_wave_unit, t.wave_unit),
                              span_of(r.d_ent, t.ent), span_of(r.d_units, t.units), span_of(r.d_leaf, t.leaf),
-                             span_of(r.d_rest, rest), span_of(r.d_jobs, jobs), span_of(r.d_rest_jobs, rjobs)});
+                             span_of(r.d_rest, rest), span_of(r.d_jobs, jobs), span_of(r.d_rest_jobs, rjobs),
+                             span_of(r.d_node_pos, node_pos), span_of(r.d_node_flags, node_flags)});
     if (s != QC_OK) {
-        free_rows(g);
+        free_rows(g, r);
         return s;
     }
     r.dev.src = r.d_src;
@@ -106,37 +160,49 @@ qc_status ensure_rows(qc_graph g)
     r.dev.units = r.d_units;
     r.dev.leaf = r.d_leaf;
     r.dev.rest = r.d_rest;
+    r.dev.node_pos = r.d_node_pos;
+    r.dev.node_flags = r.d_node_flags;
     r.n_jobs = (int)jobs.size();
     r.n_rest_jobs = (int)rjobs.size();
     r.ready = true;
     return QC_OK;
 }
 
-// After the source order changed (exact_source_order): the sources' table.
+qc_status ensure_rows(qc_graph g) { return g->rows.ready ? QC_OK : make_rows(g, g->rows, false); }
+
+qc_status ensure_dist_rows(qc_graph g) { return g->drows.ready ? QC_OK : make_rows(g, g->drows, true); }
+
 qc_status reorder_rows(qc_graph g)
 {
-    if (!g->rows.ready) return QC_OK;
-    return upload(g->rows.d_src, source_table(g));
+    for (RowsState *r : {&g->rows, &g->drows})
+        if (r->ready && r->d_src) QC_TRY(upload(r->d_src, source_table(g, *r)));
+    return QC_OK;
+}
+
+// The descriptor with the tables of the search about to run.
+static qc_status push_rows(qc_graph g, bool dist, hipStream_t st)
+{
+    g->dist_desc = dist;
+    return push_desc(g, st);
 }
 
 qc_status run_counts(qc_graph g, hipStream_t st)
 {
     QC_TRY(ensure_rows(g));
     const bool first = g->dmax < 0;
-    int32_t *hist = nullptr;
-    if (first) {
-        // rows for the bound the host sweeps gave on every distance, or for
-        // the largest one an int8 distance can hold
-        g->K = bins_for(g->dist_bound >= 0 ? g->dist_bound : kMaxDist);
-    }
+    // rows for the bound the host sweeps gave on every distance, or for the
+    // largest one an int8 distance can hold
+    if (first) g->K = bins_for(g->dist_bound >= 0 ? g->dist_bound : kMaxDist);
     if (!g->d_hist || first) {
+        int32_t *hist = nullptr;
         QC_TRY(galloc(g, &hist, (size_t)g->n * g->K));
         gfree(g, g->d_hist);
         g->d_hist = hist;
     }
-    QC_HIP(launch_fill_i32(g->d_status, 2, 0, st));
+    // (later searches of the same graph find what the first one latched)
+    if (first) QC_HIP(launch_fill_i32(g->d_status, 2, 0, st));
     for (;;) {
-        QC_TRY(push_desc(g, st));
+        QC_TRY(push_rows(g, false, st));
         {
             StageTimer t(QC_STAGE_BFS, st);
             QC_HIP(launch_count(g->rows.plan.nq, g->rows.plan.threads, g->rows.plan.per, g->d_desc, g->rows.d_jobs,
@@ -153,7 +219,8 @@ qc_status run_counts(qc_graph g, hipStream_t st)
         QC_HIP(hipStreamSynchronize(st));
         if (status[1] & 1) return QC_E_OVERFLOW;
         const int K = bins_for(status[0]);
-        if (K != g->K) {
+        const bool again = K != g->K;
+        if (again) {
             // rows of the exact length, and the search once more into them
             int32_t *h = nullptr;
             QC_TRY(galloc(g, &h, (size_t)g->n * K));
@@ -162,12 +229,30 @@ qc_status run_counts(qc_graph g, hipStream_t st)
             g->K = K;
         }
         g->dmax = g->dmax_bfs = status[0];
-        if (K == bins_for(g->dist_bound >= 0 ? g->dist_bound : kMaxDist)) {
+        if (!again) {
             QC_TRY(push_desc(g, st));
             break;
         }
     }
     if (first && g->ecc_order) QC_TRY(exact_source_order(g, st));
+    g->have_dist = true;
+    return QC_OK;
+}
+
+qc_status run_dist_rows(qc_graph g, hipStream_t st)
+{
+    const RowsState &r = g->drows;
+    QC_TRY(push_rows(g, true, st));
+    {
+        StageTimer t(QC_STAGE_BFS, st);
+        if (r.n_jobs > 0)
+            QC_HIP((r.planes == 4 ? launch_dist_4 : r.planes == 5 ? launch_dist_5 : launch_dist_7)(
+                r.plan.nq, r.nqn, g->d_desc, r.d_jobs, r.n_jobs, st));
+    }
+    {
+        StageTimer t(QC_STAGE_HIST, st);
+        QC_HIP(launch_dist_rest(g->K, g->d_desc, r.dev.n_rest, st));
+    }
     g->have_dist = true;
     return QC_OK;
 }
