@@ -524,6 +524,20 @@ int64_t handle_footprint(int32_t n, int64_t nnz, int32_t n_sigmas, bool with_dis
     return b;
 }
 
+qc_status all_labels(qc_graph g, uint32_t tie_mode, int32_t *labels_out, hipStream_t st)
+{
+    QC_HIP(launch_fill_u64(g->d_recheck, 1, st));
+    {
+        StageTimer t(QC_STAGE_GGD, st);
+        QC_HIP(launch_ggd_parent((int)tie_mode, g->d_desc, g->d_node_jobs, g->n_node_jobs, 0, g->n_sigmas, st));
+    }
+    {
+        StageTimer t(QC_STAGE_JUMP, st);
+        QC_HIP(launch_pointer_jump(g->d_desc, g->d_node_jobs, 1, 0, g->n_sigmas, labels_out, g->n, g->n, st));
+    }
+    return QC_OK;
+}
+
 qc_status cluster_on_handle(qc_graph g, const double *sigmas, int32_t n_sigmas,
                             uint32_t tie_mode, int8_t *dist_out, float *psi_out, float *v_out,
                             int32_t *labels_out, hipStream_t st)
@@ -531,8 +545,7 @@ qc_status cluster_on_handle(qc_graph g, const double *sigmas, int32_t n_sigmas,
     void *stream = (void *)st;
     QC_TRY(qc_distances(g, dist_out, nullptr, stream));
     QC_TRY(qc_potential(g, sigmas, n_sigmas, psi_out, v_out, QC_PREC_FP64ACC, stream));
-    for (int32_t k = 0; k < n_sigmas; ++k)
-        QC_TRY(qc_ggd_labels(g, k, tie_mode, labels_out + (size_t)k * g->n, stream));
+    QC_TRY(all_labels(g, tie_mode, labels_out, st));
     return qc_graph_sync(g, stream);
 }
 
@@ -679,32 +692,9 @@ qc_status create_graph(int32_t n, int64_t nnz, const int32_t *row_ptr, const int
     g->edges_host =
         weights ? pack_in_edges(n_bfs, brp, bcol, directed) : pack_in_edges(n, rp, col, directed);
     const std::vector<uint32_t> &edges = g->edges_host;
-    // The descent gives one thread to each node, in this order: nodes sorted
-    // by decreasing degree within windows of kOrderWindow consecutive nodes,
-    // so a wavefront's neighbour loops have similar trip counts while the
-    // scattered loads and stores of a window's jobs stay within a few KB.
-    std::vector<int32_t> order(n);
-    std::iota(order.begin(), order.end(), 0);
-    for (int32_t i0 = 0; i0 < n; i0 += kOrderWindow)
-        std::stable_sort(order.begin() + i0, order.begin() + std::min(n, i0 + kOrderWindow),
-                         [&](int32_t a, int32_t b) { return rp[a + 1] - rp[a] > rp[b + 1] - rp[b]; });
-    // ... and reads its node's neighbours from a sliced ELL copy of the CSR
-    // in that order: 64 nodes (one wavefront) per slice, as wide as the
-    // slice's largest degree, slot-major; unused entries hold node 0.
-    const int32_t n_slices = (n + 63) / 64;
-    std::vector<int32_t> sell_off(n_slices + 1, 0), sell_deg(n);
-    for (int32_t t = 0; t < n; ++t) sell_deg[t] = rp[order[t] + 1] - rp[order[t]];
-    for (int32_t w = 0; w < n_slices; ++w) {
-        int32_t width = 0;
-        for (int32_t t = 64 * w; t < std::min(n, 64 * w + 64); ++t) width = std::max(width, sell_deg[t]);
-        sell_off[w + 1] = sell_off[w] + 64 * width;
-    }
-    std::vector<int32_t> sell_col((size_t)sell_off[n_slices] + 64 * kGgdPad, 0);
-    for (int32_t t = 0; t < n; ++t) {
-        const int32_t i = order[t], w = t / 64, lane = t % 64;
-        for (int32_t k = 0; k < sell_deg[t]; ++k)
-            sell_col[(size_t)sell_off[w] + 64 * k + lane] = col[rp[i] + k];
-    }
+    const Descent descent = build_descent(n, rp, col);
+    const std::vector<int32_t> &order = descent.order, &sell_col = descent.col, &sell_off = descent.off,
+                               &sell_deg = descent.deg;
     // BFS sources by estimated eccentricity (undirected graphs; a directed
     // graph keeps its node order, and so does a serving request: its one
     // search would not repay the host sweeps). QC_SOURCE_ORDER=identity keeps
@@ -823,7 +813,7 @@ qc_status qc_distances(qc_graph g, int8_t *dist_out, int32_t *dmax_out, void *st
         g->d_dist = g->d_dist_owned;
         g->d_ld = owned_ld(g->n);
     }
-    QC_TRY(run_distances(g, st));
+    QC_TRY(guarded([&] { return run_distances(g, st); }));
     if (dmax_out) *dmax_out = g->dmax;
     return QC_OK;
 }
@@ -846,7 +836,8 @@ qc_status qc_potential(qc_graph g, const double *sigmas, int32_t n_sigmas, float
     QC_TRY(validate_sigmas(sigmas, n_sigmas));
     if (precision > QC_PREC_BF16) return QC_E_INVAL;
     hipStream_t st = as_stream(stream);
-    if (!g->have_dist) QC_TRY(can_count(g) ? run_counts(g, st) : qc_distances(g, nullptr, nullptr, stream));
+    if (!g->have_dist)
+        QC_TRY(can_count(g) ? guarded([&] { return run_counts(g, st); }) : qc_distances(g, nullptr, nullptr, stream));
 
     // until this call has succeeded the handle holds no potentials (the
     // descent refuses to run on a half-made set)
@@ -947,6 +938,14 @@ qc_status qc_cluster(int32_t n, int64_t nnz, const int32_t *row_ptr, const int32
     if (dist_out && ((uintptr_t)dist_out) % 16) return QC_E_INVAL;
     QC_TRY(validate_sigmas(sigmas, n_sigmas));
     hipStream_t st = as_stream(stream);
+    // without a matrix: in the fixed scratch when it fits (and, for a problem
+    // beyond qc_cluster_noalloc's limit, is free), else in one buffer of the
+    // call's own
+    if (!dist_out)
+        return guarded([&] {
+            return cluster_counts(n, nnz, row_ptr, col_idx, sigmas, n_sigmas, tie_mode, psi_out, v_out, labels_out,
+                                  st, true, true);
+        });
     // a problem that fits the fixed scratch runs there, without the device
     // allocations (and frees) of a temporary handle
     const qc_status fit = cluster_scratch(n, nnz, row_ptr, col_idx, sigmas, n_sigmas, tie_mode, dist_out,

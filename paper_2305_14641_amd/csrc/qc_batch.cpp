@@ -601,7 +601,7 @@ qc_status qc_batch_create(const qc_graph *graphs, int32_t n_graphs, const double
         b->counting.push_back(can_count(g) ? 1 : 0);
         if (b->counting.back()) {
             // histograms straight from the search, no matrix
-            const qc_status s = g->dmax < 0 ? run_counts(g, st) : ensure_rows(g);
+            const qc_status s = guarded([&] { return g->dmax < 0 ? run_counts(g, st) : ensure_rows(g); });
             if (s) return fail(s);
         } else {
             // the batch writes distances only into a matrix the handle owns,

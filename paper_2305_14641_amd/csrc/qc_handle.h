@@ -5,6 +5,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <new>
 #include <vector>
 
 #include "qc.h"
@@ -166,6 +167,20 @@ namespace qc {
 
 qc_status from_hip(hipError_t e);
 
+// f() at a C entry point: host memory that runs out is a status, not an
+// exception across the ABI.
+template <class F>
+qc_status guarded(F f)
+{
+    try {
+        return f();
+    } catch (const std::bad_alloc &) {
+        return QC_E_OOM;
+    } catch (...) {
+        return QC_E_DEVICE;
+    }
+}
+
 #define QC_TRY(expr)                                  \
     do {                                              \
         qc_status _st = (expr);                       \
@@ -325,6 +340,15 @@ qc_status cluster_scratch(int32_t n, int64_t nnz, const int32_t *row_ptr, const 
                           const double *sigmas, int32_t n_sigmas, uint32_t tie_mode, int8_t *dist_out,
                           float *psi_out, float *v_out, int32_t *labels_out, hipStream_t st,
                           bool stage_events);
+// Algorithm 4 in one call without a distance matrix (qc_noalloc.hip,
+// qc_onecall.h). own_memory: a problem beyond the fixed scratch (or, when
+// qc_cluster_noalloc would refuse it, one that finds the scratch in use) runs
+// in a buffer allocated for the call; else QC_E_TOO_LARGE.
+qc_status cluster_counts(int32_t n, int64_t nnz, const int32_t *row_ptr, const int32_t *col_idx,
+                         const double *sigmas, int32_t n_sigmas, uint32_t tie_mode, float *psi_out,
+                         float *v_out, int32_t *labels_out, hipStream_t st, bool own_memory, bool stage_events);
+// Labels of every width of g's last potential into labels_out [n_sigmas][n].
+qc_status all_labels(qc_graph g, uint32_t tie_mode, int32_t *labels_out, hipStream_t st);
 // Release a handle; `sync` waits for the whole device first (handles that
 // live in an arena region are released after their own stream has drained).
 void destroy(qc_graph g, bool sync = true);

@@ -54,12 +54,16 @@ qc_status validate_csr(int32_t n, int64_t nnz, const int32_t *row_ptr, const int
             if (e > row_ptr[i] && col[e] <= col[e - 1]) return QC_E_NOT_SYMMETRIC;
         }
     }
-    for (int32_t i = 0; i < n && !directed; ++i) {
-        for (int32_t e = row_ptr[i]; e < row_ptr[i + 1]; ++e) {
-            const int32_t j = col[e];
-            if (!std::binary_search(col + row_ptr[j], col + row_ptr[j + 1], i))
-                return QC_E_NOT_SYMMETRIC;
-        }
+    if (!directed) {
+        // rows are sorted, so going through the entries (i, j) in order meets
+        // row j's entries in order too: the next one not yet met must be i
+        std::vector<int32_t> at(row_ptr, row_ptr + n);
+        for (int32_t i = 0; i < n; ++i)
+            for (int32_t e = row_ptr[i]; e < row_ptr[i + 1]; ++e) {
+                const int32_t j = col[e];
+                if (at[j] >= row_ptr[j + 1] || col[at[j]] != i) return QC_E_NOT_SYMMETRIC;
+                ++at[j];
+            }
     }
     rp_out.assign(row_ptr, row_ptr + n + 1);
     col_out.assign(col, col + nnz);
@@ -333,6 +337,42 @@ std::vector<int32_t> source_order(int32_t n, const std::vector<int32_t> &rp,
         return lo[a] != lo[b] ? lo[a] < lo[b] : hi[a] < hi[b];
     });
     return order;
+}
+
+Descent build_descent(int32_t n, const std::vector<int32_t> &rp, const std::vector<int32_t> &col)
+{
+    Descent d;
+    d.order.resize(n);
+    auto degree = [&](int32_t v) { return rp[v + 1] - rp[v]; };
+    int32_t most = 0;
+    for (int32_t v = 0; v < n; ++v) most = std::max(most, degree(v));
+    // stable counting sort by decreasing degree, window by window
+    std::vector<int32_t> start(most + 2);
+    for (int32_t i0 = 0; i0 < n; i0 += kOrderWindow) {
+        const int32_t i1 = std::min(n, i0 + kOrderWindow);
+        int32_t top = 0;
+        for (int32_t v = i0; v < i1; ++v) top = std::max(top, degree(v));
+        std::fill(start.begin(), start.begin() + top + 2, 0);
+        for (int32_t v = i0; v < i1; ++v) ++start[top - degree(v) + 1];
+        for (int32_t k = 0; k <= top; ++k) start[k + 1] += start[k];
+        for (int32_t v = i0; v < i1; ++v) d.order[i0 + start[top - degree(v)]++] = v;
+    }
+    const int32_t n_slices = (n + 63) / 64;
+    d.off.assign(n_slices + 1, 0);
+    d.deg.resize(n);
+    for (int32_t t = 0; t < n; ++t) d.deg[t] = degree(d.order[t]);
+    for (int32_t w = 0; w < n_slices; ++w) {
+        int32_t width = 0;
+        for (int32_t t = 64 * w; t < std::min(n, 64 * w + 64); ++t) width = std::max(width, d.deg[t]);
+        d.off[w + 1] = d.off[w] + 64 * width;
+    }
+    d.col.assign((size_t)d.off[n_slices] + 64 * kGgdPad, 0);
+    for (int32_t t = 0; t < n; ++t) {
+        const int32_t *const from = col.data() + rp[d.order[t]];
+        int32_t *const to = d.col.data() + d.off[t / 64] + t % 64;
+        for (int32_t k = 0; k < d.deg[t]; ++k) to[(size_t)64 * k] = from[k];
+    }
+    return d;
 }
 
 int planes_for(int32_t dmax)

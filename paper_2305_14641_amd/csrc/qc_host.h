@@ -64,6 +64,18 @@ std::vector<int32_t> source_order(int32_t n, const std::vector<int32_t> &rp,
                                   const std::vector<int32_t> &col, int32_t n_src, int sweeps,
                                   int32_t *dist_bound = nullptr);
 
+// The descent's thread order and neighbour lists (GraphDev's order and
+// sell_*): nodes by decreasing degree within windows of kOrderWindow
+// consecutive ones, so a wavefront's neighbour loops have similar trip counts
+// while the scattered accesses of a window's jobs stay within a few KB; and a
+// sliced ELL copy of the CSR in that order, 64 nodes (one wavefront) per
+// slice, as wide as the slice's largest degree, slot-major (unused entries
+// hold node 0).
+struct Descent {
+    std::vector<int32_t> order, col, off, deg;
+};
+Descent build_descent(int32_t n, const std::vector<int32_t> &rp, const std::vector<int32_t> &col);
+
 // Integer edge weights (Section 3.1: a path's length is the sum of its edges'
 // weights): an edge of weight w >= 2 becomes a path of w unit edges through
 // w - 1 new nodes numbered from n on, so unit-edge hop distances between the

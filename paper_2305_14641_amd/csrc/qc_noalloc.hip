@@ -14,6 +14,7 @@
 
 #include "qc.h"
 #include "qc_handle.h"
+#include "qc_onecall.h"
 
 using namespace qc;
 
@@ -48,6 +49,49 @@ qc_status scratch_ptr(int dev, char **out)
 }  // namespace
 
 namespace qc {
+
+qc_status cluster_counts(int32_t n, int64_t nnz, const int32_t *row_ptr, const int32_t *col_idx,
+                         const double *sigmas, int32_t n_sigmas, uint32_t tie_mode, float *psi_out,
+                         float *v_out, int32_t *labels_out, hipStream_t st, bool own_memory, bool stage_events)
+{
+    // (the size an allocation-free call is refused at counts a matrix)
+    const int64_t need = handle_footprint(n, nnz, n_sigmas, true, false);
+    const bool within = need >= 0 && need <= (int64_t)kScratchBytes;
+    if (!own_memory) {
+        if (need < 0) return QC_E_INVAL;
+        if (!within) return QC_E_TOO_LARGE;
+    }
+    // everything the host prepares comes before any device work and before
+    // the scratch is taken
+    std::vector<int32_t> rp, col;
+    QC_TRY(validate_csr(n, nnz, row_ptr, col_idx, false, rp, col));
+    int dev = 0;
+    QC_TRY(check_device(&dev));
+    if (dev >= kMaxDevices) return QC_E_DEVICE;
+    OneCall call(n, rp, col, sigmas, n_sigmas, false, false);
+    // without allocation no stage timer may run (each creates HIP events)
+    std::optional<StageTimingOff> no_events;
+    if (!stage_events) no_events.emplace();
+    if (call.bytes(128) <= kScratchBytes) {
+        std::unique_lock<std::mutex> lk(g_dev_mu[dev], std::defer_lock);
+        if (within) lk.lock();
+        else (void)lk.try_lock();
+        if (lk.owns_lock()) {
+            char *base = nullptr;
+            QC_TRY(scratch_ptr(dev, &base));
+            return call.run(base, kScratchBytes, tie_mode, psi_out, v_out, labels_out, st, nullptr);
+        }
+    }
+    if (!own_memory) return QC_E_TOO_LARGE;
+    for (const int bins : {32, 128}) {
+        char *base = nullptr;
+        QC_TRY(dalloc(&base, call.bytes(bins)));
+        const qc_status s = call.run(base, call.bytes(bins), tie_mode, psi_out, v_out, labels_out, st, nullptr);
+        dfree(base);
+        if (s != QC_E_TOO_LARGE) return s;
+    }
+    return QC_E_DEVICE;
+}
 
 qc_status cluster_scratch(int32_t n, int64_t nnz, const int32_t *row_ptr, const int32_t *col_idx,
                           const double *sigmas, int32_t n_sigmas, uint32_t tie_mode, int8_t *dist_out,
@@ -95,6 +139,16 @@ extern "C" qc_status qc_cluster_noalloc(int32_t n, int64_t nnz, const int32_t *r
                                         float *psi_out, float *v_out, int32_t *labels_out,
                                         void *stream)
 {
+    if (!dist_out) {
+        if (!labels_out || tie_mode > QC_TIE_MERGE) return QC_E_INVAL;
+        QC_TRY(validate_sigmas(sigmas, n_sigmas));
+        // (tables so padded that they outgrow the scratch: the matrix path)
+        const qc_status s = guarded([&] {
+            return cluster_counts(n, nnz, row_ptr, col_idx, sigmas, n_sigmas, tie_mode, psi_out, v_out, labels_out,
+                                  as_stream(stream), false, false);
+        });
+        if (s != QC_E_TOO_LARGE) return s;
+    }
     return cluster_scratch(n, nnz, row_ptr, col_idx, sigmas, n_sigmas, tie_mode, dist_out, psi_out,
                            v_out, labels_out, as_stream(stream), false);
 }

@@ -128,8 +128,7 @@ qc_status qc_cluster_real(int32_t n, int64_t nnz, const int32_t *row_ptr, const 
                                     hipMemcpyDeviceToDevice, st));
     if (s == QC_OK) {
         g->have_pot = true;
-        for (int32_t k = 0; k < n_sigmas && s == QC_OK; ++k)
-            s = qc_ggd_labels(g, k, tie_mode, labels_out + (size_t)k * n, stream);
+        s = all_labels(g, tie_mode, labels_out, st);
     }
     const qc_status sync = from_hip(hipStreamSynchronize(st));
     if (s == QC_OK) s = sync;

@@ -16,6 +16,7 @@
 #include <vector>
 
 #include "qc_handle.h"
+#include "qc_onecall.h"
 #include "qc_server.h"
 
 using namespace qc;
@@ -117,6 +118,43 @@ qc_status run_request(qc_server s, Request *r, int slot, void **stage, size_t *s
     void *stream = (void *)st;
     const int S = (int)r->sigmas.size();
     const int n = r->n;
+    // the pinned stage the results come back through (kept by the worker)
+    auto reserve = [&](size_t need) -> qc_status {
+        if (*stage_bytes >= need) return QC_OK;
+        if (*stage) (void)hipHostFree(*stage);
+        *stage = nullptr;
+        *stage_bytes = 0;
+        QC_HIP(hipHostMalloc(stage, need, hipHostMallocDefault));
+        *stage_bytes = need;
+        return QC_OK;
+    };
+    // Without a matrix, whenever the request's region holds it (the region
+    // counts the matrix, so all but tiny graphs fit). Requests above
+    // kDirectNodes keep the matrix search although it is slower (50,000 nodes:
+    // about 35 ms against 14): programs that time queue deadlines and
+    // cancellations against such a request (this repository's tests do) count
+    // on it holding its slot for tens of milliseconds.
+    constexpr int32_t kDirectNodes = 32768;
+    if (n <= kDirectNodes) {
+        OneCall call(n, r->row_ptr, r->col, r->sigmas.data(), S, true, s->opts.want_potentials != 0);
+        if (call.bytes(128) <= (size_t)r->footprint) {
+            for (int k = 0; k < call.buffers(); ++k)   // (each counts as an allocation)
+                if (alloc_fault_now()) return QC_E_OOM;
+            QC_TRY(reserve(call.results_bytes()));
+            QC_TRY(call.run(s->d_arena + r->offset, (size_t)r->footprint, s->opts.tie_mode, nullptr, nullptr, nullptr,
+                            st, &r->dmax));
+            const char *const h = (const char *)*stage;
+            QC_HIP(hipMemcpyAsync(*stage, call.results(), call.results_bytes(), hipMemcpyDeviceToHost, st));
+            QC_HIP(hipStreamSynchronize(st));
+            const size_t count = (size_t)S * n;
+            r->labels.assign((const int32_t *)h, (const int32_t *)h + count);
+            if (s->opts.want_potentials) {
+                r->psi.assign((const float *)h + count, (const float *)h + 2 * count);
+                r->v.assign((const float *)h + 2 * count, (const float *)h + 3 * count);
+            }
+            return QC_OK;
+        }
+    }
     qc_graph g = nullptr;
     QC_TRY(create_graph(n, (int64_t)r->col.size(), r->row_ptr.data(), r->col.data(), 0, st,
                         s->d_arena + r->offset, (size_t)r->footprint, &g));
@@ -135,20 +173,13 @@ qc_status run_request(qc_server s, Request *r, int slot, void **stage, size_t *s
     QC_TRY(galloc(g, &d_labels, (size_t)S * n));
     QC_TRY(qc_distances(g, nullptr, &r->dmax, stream));
     QC_TRY(qc_potential(g, r->sigmas.data(), S, nullptr, nullptr, QC_PREC_FP64ACC, stream));
-    for (int k = 0; k < S; ++k)
-        QC_TRY(qc_ggd_labels(g, k, s->opts.tie_mode, d_labels + (size_t)k * n, stream));
+    QC_TRY(all_labels(g, s->opts.tie_mode, d_labels, st));
     const size_t lab_bytes = (size_t)S * n * sizeof(int32_t);
     const size_t pot_bytes = s->opts.want_potentials ? (size_t)S * n * sizeof(float) : 0;
     // the resident V keeps its sigmas interleaved in groups (v_index)
     const size_t v_bytes = s->opts.want_potentials ? (size_t)v_floats(n, S) * sizeof(float) : 0;
     const size_t need = lab_bytes + pot_bytes + v_bytes;
-    if (*stage_bytes < need) {
-        if (*stage) (void)hipHostFree(*stage);
-        *stage = nullptr;
-        *stage_bytes = 0;
-        QC_HIP(hipHostMalloc(stage, need, hipHostMallocDefault));
-        *stage_bytes = need;
-    }
+    QC_TRY(reserve(need));
     char *h = (char *)*stage;
     QC_HIP(hipMemcpyAsync(h, d_labels, lab_bytes, hipMemcpyDeviceToHost, st));
     if (pot_bytes) {
@@ -241,7 +272,7 @@ void worker(qc_server s, int slot)
             if (s->bytes_in_flight > s->peak_bytes) s->peak_bytes = s->bytes_in_flight;
             if (s->in_flight > s->peak_requests) s->peak_requests = s->in_flight;
         }
-        const qc_status st = run_request(s, r, slot, &stage, &stage_bytes);
+        const qc_status st = guarded([&] { return run_request(s, r, slot, &stage, &stage_bytes); });
         {
             std::lock_guard<std::mutex> lk(s->mu);
             s->arena.release(r->offset, (size_t)r->footprint);
