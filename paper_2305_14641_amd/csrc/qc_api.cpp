@@ -526,14 +526,25 @@ int64_t handle_footprint(int32_t n, int64_t nnz, int32_t n_sigmas, bool with_dis
 
 qc_status all_labels(qc_graph g, uint32_t tie_mode, int32_t *labels_out, hipStream_t st)
 {
-    QC_HIP(launch_fill_u64(g->d_recheck, 1, st));
+    return some_labels(g, 0, g->n_sigmas, tie_mode, labels_out, st);
+}
+
+qc_status some_labels(qc_graph g, int32_t first, int32_t count, uint32_t tie_mode, int32_t *labels_out, hipStream_t st)
+{
+    // (the descent of a single pair stores the count itself)
+    if (g->n > kDescendNodes || count > 1) QC_HIP(launch_fill_u64(g->d_recheck, 1, st));
+    if (g->n <= kDescendNodes) {
+        StageTimer t(QC_STAGE_GGD, st);
+        QC_HIP(launch_descend((int)tie_mode, g->d_desc, g->d_node_jobs, 1, first, count, labels_out, g->n, g->n, st));
+        return QC_OK;
+    }
     {
         StageTimer t(QC_STAGE_GGD, st);
-        QC_HIP(launch_ggd_parent((int)tie_mode, g->d_desc, g->d_node_jobs, g->n_node_jobs, 0, g->n_sigmas, st));
+        QC_HIP(launch_ggd_parent((int)tie_mode, g->d_desc, g->d_node_jobs, g->n_node_jobs, first, count, st));
     }
     {
         StageTimer t(QC_STAGE_JUMP, st);
-        QC_HIP(launch_pointer_jump(g->d_desc, g->d_node_jobs, 1, 0, g->n_sigmas, labels_out, g->n, g->n, st));
+        QC_HIP(launch_pointer_jump(g->d_desc, g->d_node_jobs, 1, first, count, labels_out, g->n, g->n, st));
     }
     return QC_OK;
 }
@@ -693,8 +704,8 @@ qc_status create_graph(int32_t n, int64_t nnz, const int32_t *row_ptr, const int
         weights ? pack_in_edges(n_bfs, brp, bcol, directed) : pack_in_edges(n, rp, col, directed);
     const std::vector<uint32_t> &edges = g->edges_host;
     const Descent descent = build_descent(n, rp, col);
-    const std::vector<int32_t> &order = descent.order, &sell_col = descent.col, &sell_off = descent.off,
-                               &sell_deg = descent.deg;
+    const std::vector<int32_t> &order = descent.order, &sell_off = descent.off, &sell_deg = descent.deg;
+    const std::vector<uint32_t> &sell_col = descent.col;
     // BFS sources by estimated eccentricity (undirected graphs; a directed
     // graph keeps its node order, and so does a serving request: its one
     // search would not repay the host sweeps). QC_SOURCE_ORDER=identity keeps
@@ -865,18 +876,7 @@ qc_status qc_ggd_labels(qc_graph g, int32_t sigma_index, uint32_t tie_mode, int3
     if (!g->have_pot || g->pot_precision == QC_PREC_BF16) return QC_E_STATE;
     if (sigma_index < 0 || sigma_index >= g->n_sigmas) return QC_E_INVAL;
     hipStream_t st = as_stream(stream);
-    QC_HIP(launch_fill_u64(g->d_recheck, 1, st));
-    {
-        StageTimer t(QC_STAGE_GGD, st);
-        QC_HIP(launch_ggd_parent((int)tie_mode, g->d_desc, g->d_node_jobs, g->n_node_jobs,
-                                 sigma_index, 1, st));
-    }
-    {
-        StageTimer t(QC_STAGE_JUMP, st);
-        QC_HIP(launch_pointer_jump(g->d_desc, g->d_node_jobs, 1, sigma_index, 1, labels_out, 0,
-                                   g->n, st));
-    }
-    return QC_OK;
+    return some_labels(g, sigma_index, 1, tie_mode, labels_out, st);
 }
 
 qc_status qc_get_potential64(qc_graph g, double *v64_out, void *stream)

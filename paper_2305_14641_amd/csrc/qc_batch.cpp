@@ -45,11 +45,20 @@ struct Stages {
                                // -2: the last launch's, on the caller's stream, beside the side stream)
     bool rest = true;
     std::vector<KGroup> hist, pot;
-    NodeJob *d_ggd_jobs = nullptr;
-    int n_ggd_jobs = 0;
-    NodeJob *d_jump_jobs = nullptr;
-    int n_jump_jobs = 0;
     int max_n = 0;             // largest node count among the graphs
+    // Descent and pointer jumping through global memory, for every graph
+    // ([1], the jump variant that asks for it) or those that the
+    // one-workgroup descent can't hold ([0]).
+    struct Far {
+        NodeJob *d_ggd_jobs = nullptr, *d_jump_jobs = nullptr;
+        int n_ggd_jobs = 0, n_jump_jobs = 0;
+    } far[2];
+    // Jobs of the one-workgroup descent (launch_descend), by LDS size.
+    struct Descend {
+        NodeJob *d_jobs = nullptr;
+        int n_jobs = 0, max_n = 0;
+    };
+    std::vector<Descend> descend;
 };
 
 struct qc_batch_s {
@@ -116,8 +125,11 @@ void free_batch(qc_batch b)
     for (auto &c : b->stages) {
         for (auto &g : c.hist) dfree(g.d_jobs);
         for (auto &g : c.pot) dfree(g.d_jobs);
-        dfree(c.d_ggd_jobs);
-        dfree(c.d_jump_jobs);
+        for (auto &x : c.far) {
+            dfree(x.d_ggd_jobs);
+            dfree(x.d_jump_jobs);
+        }
+        for (auto &x : c.descend) dfree(x.d_jobs);
     }
     for (auto &g : b->pot_all) dfree(g.d_jobs);
     for (hipEvent_t e : b->ev_bfs) (void)hipEventDestroy(e);
@@ -333,13 +345,19 @@ qc_status run_stages(qc_batch b, const Stages &c, float *psi_out, float *v_out, 
         QC_HIP(launch_potential(b->precision, g.K, b->d_descs, g.d_jobs, g.n_jobs, psi_out, v_out,
                                 total, st));
     }
-    {
+    if (b->jump_variant == 0)
+        for (const Stages::Descend &x : c.descend) {
+            StageTimer t(QC_STAGE_GGD, st);
+            QC_HIP(launch_descend((int)b->tie, b->d_descs, x.d_jobs, x.n_jobs, 0, S, labels_out, total, x.max_n, st));
+        }
+    const Stages::Far &f = c.far[b->jump_variant];
+    if (f.n_ggd_jobs) {
         StageTimer t(QC_STAGE_GGD, st);
-        QC_HIP(launch_ggd_parent((int)b->tie, b->d_descs, c.d_ggd_jobs, c.n_ggd_jobs, 0, S, st));
+        QC_HIP(launch_ggd_parent((int)b->tie, b->d_descs, f.d_ggd_jobs, f.n_ggd_jobs, 0, S, st));
     }
-    {
+    if (f.n_jump_jobs) {
         StageTimer t(QC_STAGE_JUMP, st);
-        QC_HIP(launch_pointer_jump(b->d_descs, c.d_jump_jobs, c.n_jump_jobs, 0, S, labels_out, total,
+        QC_HIP(launch_pointer_jump(b->d_descs, f.d_jump_jobs, f.n_jump_jobs, 0, S, labels_out, total,
                                    c.max_n, st, b->jump_variant));
     }
     return QC_OK;
@@ -490,7 +508,7 @@ qc_status autotune_stages(qc_batch b, hipStream_t st)
         if (s == QC_OK) g_tiles[key] = chosen;
     };
     if (s == QC_OK) tune(0, 3, set_hist);
-    if (s == QC_OK && max_n <= 40704) tune(1, 2, [&](int v) { b->jump_variant = v; });
+    if (s == QC_OK && max_n > kDescendNodes && max_n <= 40704) tune(1, 2, [&](int v) { b->jump_variant = v; });
     (void)hipStreamSynchronize(st);
     dfree(labels);
     return s;
@@ -752,21 +770,50 @@ qc_status qc_batch_create(const qc_graph *graphs, int32_t n_graphs, const double
             }
         }
         if (!rest) return QC_OK;
-        std::vector<qc_graph> gv;
-        for (int gi : gis) gv.push_back(graphs[gi]);
-        std::vector<NodeJob> gj = xcd_pinned_node_jobs(gv), jj;
-        // pinned jobs index gv; the kernels index the batch's descriptors
-        for (auto &j : gj) j.g = gis[j.g];
-        const bool pinned = !gj.empty();
-        for (int gi : gis) {
-            if (!pinned)
-                for (int r = 0; r < graphs[gi]->n; r += kNodesPerJob) gj.push_back(NodeJob{gi, r, 0});
-            jj.push_back(NodeJob{gi, 0, b->offsets[gi]});
+        for (int k = 0; k < 2; ++k) {
+            std::vector<int> in;
+            std::vector<qc_graph> gv;
+            for (int gi : gis)
+                if (k || graphs[gi]->n > kDescendNodes) {
+                    in.push_back(gi);
+                    gv.push_back(graphs[gi]);
+                }
+            if (in.empty()) continue;
+            std::vector<NodeJob> gj = xcd_pinned_node_jobs(gv), jj;
+            // pinned jobs index gv; the kernels index the batch's descriptors
+            for (auto &j : gj) j.g = in[j.g];
+            const bool pinned = !gj.empty();
+            for (int gi : in) {
+                if (!pinned)
+                    for (int r = 0; r < graphs[gi]->n; r += kNodesPerJob) gj.push_back(NodeJob{gi, r, 0});
+                jj.push_back(NodeJob{gi, 0, b->offsets[gi]});
+            }
+            Stages::Far &f = c.far[k];
+            f.n_ggd_jobs = (int)gj.size();
+            f.n_jump_jobs = (int)jj.size();
+            QC_TRY(upload_jobs(&f.d_ggd_jobs, gj));
+            QC_TRY(upload_jobs(&f.d_jump_jobs, jj));
         }
-        c.n_ggd_jobs = (int)gj.size();
-        c.n_jump_jobs = (int)jj.size();
-        QC_TRY(upload_jobs(&c.d_ggd_jobs, gj));
-        return upload_jobs(&c.d_jump_jobs, jj);
+        // The one-workgroup descent: a launch for the graphs that fill more
+        // than half of a CU's LDS and one for the others, largest first.
+        std::vector<int> by_size = gis;
+        std::stable_sort(by_size.begin(), by_size.end(), [&](int x, int y) { return graphs[x]->n > graphs[y]->n; });
+        for (const bool large : {true, false}) {
+            std::vector<NodeJob> dj;
+            int most = 0;
+            for (int gi : by_size) {
+                const int n = graphs[gi]->n;
+                if (n > kDescendNodes || (n > kDescendHalfNodes) != large) continue;
+                dj.push_back(NodeJob{gi, 0, b->offsets[gi]});
+                most = std::max(most, n);
+            }
+            if (dj.empty()) continue;
+            c.descend.emplace_back();
+            c.descend.back().n_jobs = (int)dj.size();
+            c.descend.back().max_n = most;
+            QC_TRY(upload_jobs(&c.descend.back().d_jobs, dj));
+        }
+        return QC_OK;
     };
     std::vector<int> all(n_graphs);
     for (int i = 0; i < n_graphs; ++i) all[i] = i;

@@ -60,7 +60,7 @@ struct qc_graph_s {
     int32_t *d_row_ptr = nullptr;
     int32_t *d_col = nullptr;
     int32_t *d_order = nullptr;       // descent thread order (see create_graph)
-    int32_t *d_sell_col = nullptr;    // descent neighbour lists, sliced ELL (see GraphDev)
+    uint32_t *d_sell_col = nullptr;    // descent neighbour lists, sliced ELL (see GraphDev)
     int32_t *d_sell_off = nullptr;
     int32_t *d_sell_deg = nullptr;
     std::vector<int32_t> src_order;   // BFS sources in batch order (host copy)
@@ -349,6 +349,8 @@ qc_status cluster_counts(int32_t n, int64_t nnz, const int32_t *row_ptr, const i
                          float *v_out, int32_t *labels_out, hipStream_t st, bool own_memory, bool stage_events);
 // Labels of every width of g's last potential into labels_out [n_sigmas][n].
 qc_status all_labels(qc_graph g, uint32_t tie_mode, int32_t *labels_out, hipStream_t st);
+// ... of widths first .. first + count - 1.
+qc_status some_labels(qc_graph g, int32_t first, int32_t count, uint32_t tie_mode, int32_t *labels_out, hipStream_t st);
 // Release a handle; `sync` waits for the whole device first (handles that
 // live in an arena region are released after their own stream has drained).
 void destroy(qc_graph g, bool sync = true);

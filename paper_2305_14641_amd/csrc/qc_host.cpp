@@ -364,13 +364,16 @@ Descent build_descent(int32_t n, const std::vector<int32_t> &rp, const std::vect
     for (int32_t w = 0; w < n_slices; ++w) {
         int32_t width = 0;
         for (int32_t t = 64 * w; t < std::min(n, 64 * w + 64); ++t) width = std::max(width, d.deg[t]);
-        d.off[w + 1] = d.off[w] + 64 * width;
+        d.off[w + 1] = d.off[w] + 64 * ((width + 1) / 2);
     }
-    d.col.assign((size_t)d.off[n_slices] + 64 * kGgdPad, 0);
+    const uint32_t none = (uint32_t)std::min(n, 0xFFFF);
+    d.col.assign((size_t)d.off[n_slices] + 64 * kGgdPad, none << 16 | none);
     for (int32_t t = 0; t < n; ++t) {
         const int32_t *const from = col.data() + rp[d.order[t]];
-        int32_t *const to = d.col.data() + d.off[t / 64] + t % 64;
-        for (int32_t k = 0; k < d.deg[t]; ++k) to[(size_t)64 * k] = from[k];
+        uint32_t *const to = d.col.data() + d.off[t / 64] + t % 64;
+        const int32_t deg = d.deg[t];
+        for (int32_t k = 0; k < deg; k += 2)
+            to[(size_t)32 * k] = (uint32_t)from[k] | (k + 1 < deg ? (uint32_t)from[k + 1] : none) << 16;
     }
     return d;
 }

@@ -69,10 +69,11 @@ std::vector<int32_t> source_order(int32_t n, const std::vector<int32_t> &rp,
 // consecutive ones, so a wavefront's neighbour loops have similar trip counts
 // while the scattered accesses of a window's jobs stay within a few KB; and a
 // sliced ELL copy of the CSR in that order, 64 nodes (one wavefront) per
-// slice, as wide as the slice's largest degree, slot-major (unused entries
-// hold node 0).
+// slice, as wide as the slice's largest degree, slot-major, two neighbours a
+// word.
 struct Descent {
-    std::vector<int32_t> order, col, off, deg;
+    std::vector<int32_t> order, off, deg;
+    std::vector<uint32_t> col;
 };
 Descent build_descent(int32_t n, const std::vector<int32_t> &rp, const std::vector<int32_t> &col);
 

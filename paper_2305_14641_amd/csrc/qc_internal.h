@@ -121,11 +121,13 @@ struct GraphDev {
     const int32_t *bfs_row_ptr;   // [n_bfs+1]
     const int32_t *bfs_col;
     const int32_t *order;     // [n] nodes by decreasing degree within windows of kOrderWindow
-    // The descent's neighbour lists in sliced ELL layout: slice w holds the
-    // nodes order[64w .. 64w+63], slot-major (entry k of the slice's lane l
-    // at sell_col[sell_off[w] + 64k + l]), so the lanes of a wavefront read
-    // the k-th neighbours of their nodes from one contiguous 256-byte row.
-    const int32_t *sell_col;  // [sell_off[n_slices] + 64 * kGgdPad]
+    // The descent's neighbour lists in sliced ELL layout, two neighbours a
+    // word: slice w holds the nodes order[64w .. 64w+63], slot-major
+    // (neighbours 2k and 2k + 1 of the slice's lane l in the low and the high
+    // half of sell_col[sell_off[w] + 64k + l]), so the lanes of a wavefront
+    // read the same pair of their nodes' lists from one contiguous 256-byte
+    // row. Unused halves hold n (65535 when that is too large for one).
+    const uint32_t *sell_col;  // [sell_off[n_slices] + 64 * kGgdPad]
     const int32_t *sell_off;  // [n_slices + 1]
     const int32_t *sell_deg;  // [n] degree of node order[t]
     const int32_t *src;       // [n] BFS sources in batch order (a permutation of 0..n-1)
@@ -261,6 +263,15 @@ hipError_t launch_ggd_parent(int tie_mode, const GraphDev *graphs, const NodeJob
 hipError_t launch_pointer_jump(const GraphDev *graphs, const NodeJob *jobs, int n_jobs,
                                int sigma_base, int n_sig, int32_t *labels_base,
                                int64_t labels_ld, int max_n, hipStream_t stream, int variant = 0);
+
+// Descent and pointer jumping of (graph job, sigma) pairs in one launch, each
+// in one workgroup's LDS (qc_descend.hip): graphs of at most kDescendNodes
+// nodes (4 bytes of V and 2 of parent per node, and the near ties' queues,
+// fill the 160 KB); labels as launch_pointer_jump. Two workgroups fit a CU up
+// to kDescendHalfNodes.
+constexpr int kDescendNodes = 26560, kDescendHalfNodes = 12864;
+hipError_t launch_descend(int tie_mode, const GraphDev *graphs, const NodeJob *jobs, int n_jobs, int sigma_base,
+                          int n_sig, int32_t *labels_base, int64_t labels_ld, int max_n, hipStream_t stream);
 
 // Stage timing (qc_timing.cpp): Timer brackets one launch when enabled.
 class StageTimer {

@@ -566,6 +566,18 @@ __device__ __forceinline__ double fp64_v(const GraphDev &G, int s, int node)
                        G.inv_a[s]);
 }
 
+// Neighbours k .. k + kGgdPad - 1 (k a multiple of it) of a sliced list, as
+// valid node ids also past the list's end.
+__device__ __forceinline__ void load_ids(const uint32_t *__restrict__ sc, int k, int n, int (&j)[kGgdPad])
+{
+    uint32_t x[kGgdPad / 2];
+#pragma unroll
+    for (int u = 0; u < kGgdPad / 2; ++u) x[u] = sc[64 * (k / 2 + u)];
+#pragma unroll
+    for (int u = 0; u < kGgdPad; ++u)
+        j[u] = min((int)((u & 1) ? x[u / 2] >> 16 : x[u / 2] & 0xFFFFu), n - 1);
+}
+
 // The FP64 decision for node i (thread t of the descent's order) at sigma
 // s: among the neighbours whose FP32 V lies within the bound of the lowest
 // one (m1), the lowest canonical FP64 V, compared with the node's own. The
@@ -580,14 +592,13 @@ __device__ __noinline__ int fp64_decide(int tie_mode, const GraphDev &G, int s, 
     const float *__restrict__ V = G.v;
     const double vi64 = fp64_v(G, s, i);
     const int deg = G.sell_deg[t];
-    const int32_t *__restrict__ sc = G.sell_col + G.sell_off[t >> 6] + (t & 63);
+    const uint32_t *__restrict__ sc = G.sell_col + G.sell_off[t >> 6] + (t & 63);
     double bv = DBL_MAX;
     int best = -1;
     for (int k = 0; k < deg; k += kGgdPad) {
         int j[kGgdPad];
         float vj[kGgdPad];
-#pragma unroll
-        for (int u = 0; u < kGgdPad; ++u) j[u] = sc[64 * (k + u)];
+        load_ids(sc, k, n, j);
 #pragma unroll
         for (int u = 0; u < kGgdPad; ++u) vj[u] = V[v_index(n, s, j[u])];
         double d[kGgdPad];
@@ -662,12 +673,11 @@ __global__ __launch_bounds__(256) void k_ggd_parent(int tie_mode, const GraphDev
         // are scanned in CSR order, so the first minimum wins as in a plain
         // scan.
         const int deg = G.sell_deg[t];
-        const int32_t *__restrict__ sc = G.sell_col + G.sell_off[t >> 6] + (t & 63);
+        const uint32_t *__restrict__ sc = G.sell_col + G.sell_off[t >> 6] + (t & 63);
         for (int k = 0; k < deg; k += kGgdPad) {
             int j[kGgdPad];
             float vj[kGgdPad][KS];
-#pragma unroll
-            for (int u = 0; u < kGgdPad; ++u) j[u] = sc[64 * (k + u)];
+            load_ids(sc, k, n, j);
 #pragma unroll
             for (int u = 0; u < kGgdPad; ++u) load_v(j[u], vj[u]);
 #pragma unroll
@@ -808,9 +818,6 @@ hipError_t launch_pointer_jump(const GraphDev *graphs, const NodeJob *jobs, int 
     if (variant == 1)     // in global memory whatever the size
         hipLaunchKernelGGL(k_jump, grid, block, 0, stream, graphs, jobs, sigma_base, labels_base,
                            labels_ld);
-    else if (max_n <= 20480)   // 80 KB of LDS: two workgroups per CU
-        hipLaunchKernelGGL(k_jump_lds<20480>, grid, block, 0, stream, graphs, jobs, sigma_base,
-                           labels_base, labels_ld);
     else if (max_n <= 40704)
         hipLaunchKernelGGL(k_jump_lds<40704>, grid, block, 0, stream, graphs, jobs, sigma_base,
                            labels_base, labels_ld);

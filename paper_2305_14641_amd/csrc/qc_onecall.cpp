@@ -143,7 +143,7 @@ qc_status OneCall::run(char *base, size_t limit, uint32_t tie_mode, float *psi_o
         d.n_sigmas = S_;
         d.nnz = d.nnz_bfs = nnz_;
         d.order = (const int32_t *)at(kOrder);
-        d.sell_col = (const int32_t *)at(kSellCol);
+        d.sell_col = (const uint32_t *)at(kSellCol);
         d.sell_off = (const int32_t *)at(kSellOff);
         d.sell_deg = (const int32_t *)at(kSellDeg);
         d.hist = (int32_t *)(base + hist_);
@@ -201,10 +201,14 @@ qc_status OneCall::run(char *base, size_t limit, uint32_t tie_mode, float *psi_o
         stage(QC_STAGE_POTENTIAL, [&] {
             return launch_potential(QC_PREC_FP64ACC, bins, desc, nodes, (int)node_jobs_.size(), psi_out, v_out, n_, st);
         });
-        stage(QC_STAGE_GGD, [&] {
-            return launch_ggd_parent((int)tie_mode, desc, nodes, (int)node_jobs_.size(), 0, S_, st);
-        });
-        stage(QC_STAGE_JUMP, [&] { return launch_pointer_jump(desc, nodes, 1, 0, S_, labels, n_, n_, st); });
+        if (n_ <= kDescendNodes) {
+            stage(QC_STAGE_GGD, [&] { return launch_descend((int)tie_mode, desc, nodes, 1, 0, S_, labels, n_, n_, st); });
+        } else {
+            stage(QC_STAGE_GGD, [&] {
+                return launch_ggd_parent((int)tie_mode, desc, nodes, (int)node_jobs_.size(), 0, S_, st);
+            });
+            stage(QC_STAGE_JUMP, [&] { return launch_pointer_jump(desc, nodes, 1, 0, S_, labels, n_, n_, st); });
+        }
         int32_t status[2] = {0, 0};
         if (e == hipSuccess) e = hipMemcpyAsync(status, at(kStatus), sizeof status, hipMemcpyDeviceToHost, st);
         const hipError_t sync = hipStreamSynchronize(st);
