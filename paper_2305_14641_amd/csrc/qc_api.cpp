@@ -316,17 +316,17 @@ qc_status run_distances(qc_graph g, hipStream_t st)
 {
     // The row-owner search where it has a shape for the graph (see
     // plan_rows_dist); it needs the largest distance, which the counting
-    // search gives (a weighted graph's first search is the one below). Not
-    // for directed graphs: many of their pairs are unreachable, so no row is
-    // ever finished and left out, and their many levels each pay the fixed
-    // work (9,973 nodes, 28 levels: 271 us against 222 us; undirected, 2,708
-    // nodes: 37 against 43, 19,717: 271 against 521).
-    if (!g->bump_base && !g->directed && !getenv("QC_BFS_SHAPE")) {
-        if (g->dmax < 0 && can_count(g)) QC_TRY(run_counts(g, st));
-        if (g->dmax >= 0) {
-            QC_TRY(ensure_dist_rows(g));
-            if (g->drows.planes) return run_dist_rows(g, st);
-        }
+    // search gives. Not for directed graphs: many of their pairs are
+    // unreachable, so no row is ever finished and left out, and their many
+    // levels each pay the fixed work (9,973 nodes, 28 levels: 271 us against
+    // 222 us; undirected, 2,708 nodes: 36 against 43, 19,717: 250 against
+    // 521). Nor for weighted edges, whose searches have as many levels
+    // through nodes of two neighbours (219 nodes of weights up to 5: 72 us
+    // against 57, 2,000: 104 against 101, 4,001: 201 against 203).
+    if (!g->bump_base && !g->directed && can_count(g)) {
+        if (g->dmax < 0) QC_TRY(run_counts(g, st));
+        QC_TRY(ensure_dist_rows(g));
+        if (g->drows.planes) return run_dist_rows(g, st);
     }
     if (g->dmax >= 0 && !g->plan_exact) {
         // the counting search learnt dmax: the plan (and histogram jobs) it gives
@@ -773,8 +773,6 @@ qc_status create_graph(int32_t n, int64_t nnz, const int32_t *row_ptr, const int
         return fail(st_);
     g->row_ptr = std::move(rp);
     g->col = std::move(col);
-    g->bfs_row_ptr = std::move(brp);
-    g->bfs_col = std::move(bcol);
     *out = g;
     return QC_OK;
 }

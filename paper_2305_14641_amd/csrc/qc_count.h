@@ -187,7 +187,7 @@ __global__ __launch_bounds__(KT, 4) void k_count(const GraphDev *__restrict__ gr
     __shared__ __attribute__((aligned(16))) uint32_t fields[(kTwo ? 2 : 1) * NW * KT];
     __shared__ __attribute__((aligned(16))) uint32_t hacc[HUB];
     __shared__ uint32_t hdone[HUB / 32];
-    __shared__ uint32_t cnt[3][17];   // counts of a level; [16]: anything new at all
+    __shared__ uint32_t cnt[3][16];   // counts of a level
 
     const BfsJob job = jobs[blockIdx.x];
     const GraphDev &G = graphs[job.g];
@@ -196,9 +196,6 @@ __global__ __launch_bounds__(KT, 4) void k_count(const GraphDev *__restrict__ gr
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n_pos = G.rows.n_pos;
     const int nb = min(BW, G.rows.n_search - job.s0);
-    // weighted edges: positions n_own .. own_end hold nothing, those from
-    // own_end on the nodes inside edges, which no histogram counts
-    const int n_own = G.rows.n_own, own_end = (n_own + 255) & ~255;
     const uint4 *__restrict__ src = (const uint4 *)G.rows.src + job.s0;
 
     uint32_t *const front = fields;
@@ -217,7 +214,7 @@ __global__ __launch_bounds__(KT, 4) void k_count(const GraphDev *__restrict__ gr
     clear_front();
     for (int i = tid; i < HUB; i += KT) hacc[i] = 0u;
     for (int i = tid; i < HUB / 32; i += KT) hdone[i] = 0u;
-    if (tid < 51) cnt[tid / 17][tid % 17] = 0u;
+    if (tid < 48) cnt[tid / 16][tid % 16] = 0u;
     __syncthreads();
     if (tid < nb) put(src[tid].x >> 16, tid);   // level 0: the sources
     __syncthreads();
@@ -291,7 +288,7 @@ __global__ __launch_bounds__(KT, 4) void k_count(const GraphDev *__restrict__ gr
 #pragma unroll
             for (int h = 0; h < PER; ++h) {
                 const int p = (g * KT + tid) * 4 + i * PER + h;
-                if (p >= n_pos || (p >= n_own && p < own_end)) none |= kFull << (16 * h);
+                if (p >= n_pos) none |= kFull << (16 * h);
             }
             reach(g * QW + i, none, 0);
             all &= seen_of(g * QW + i);
@@ -357,8 +354,6 @@ __global__ __launch_bounds__(KT, 4) void k_count(const GraphDev *__restrict__ gr
                 reach(g * QW + i, y[i], level);
                 any |= y[i];
                 all &= seen_of(g * QW + i);
-                // (from here on only what is counted)
-                if (P > 0 && (g * KT + wave * 64) * 4 >= own_end) y[i] = 0u;
             }
             if (!__ballot(all != ~0u)) act &= ~(1u << g);
             if (g < kHubQuads && (g * KT + wave * 64) * 4 < n_hub) {
@@ -516,7 +511,6 @@ __global__ __launch_bounds__(KT, 4) void k_count(const GraphDev *__restrict__ gr
 #pragma unroll
         for (int p = 0; p < CB; ++p) any |= cl[p];
         if (__ballot(any != 0u)) {
-            if (P > 0 && lane == 0) lc[16] = 1u;
             uint32_t sum[CB];
             add_columns<kHold, 0, CB>(hold, sum);
             if (kTwo || n_leaf) {
@@ -551,12 +545,11 @@ __global__ __launch_bounds__(KT, 4) void k_count(const GraphDev *__restrict__ gr
             c = lc[lane & 15];
             if constexpr (PER == 1) c = (lane < 16) ? (c & 0xFFFFu) : (c >> 16);
         }
-        const bool any_new = P > 0 ? lc[16] != 0u : __ballot(c != 0u) != 0;
         // the counters of the level after next: last read after the previous
         // level's last barrier, next added to after this level's successor's
-        if (tid < 17) cnt[(level + 2) % 3][tid] = 0u;
-        if (!any_new) return true;         // nothing new: every search ended
-        if (__ballot(c != 0u)) last = level;
+        if (tid < 16) cnt[(level + 2) % 3][tid] = 0u;
+        if (!__ballot(c != 0u)) return true;   // nothing new: every search ended
+        last = level;
         if (level > kMaxDist) {
             overflow = true;
             return true;

@@ -26,7 +26,6 @@ struct RowsState {
     std::vector<uint8_t> kind;        // RowsKind per node
     std::vector<uint16_t> pos;        // position of every core node
     std::vector<uint32_t> first;      // its entries in col_pos
-    std::vector<int32_t> comp;        // own nodes of every node's component (weighted edges only)
     int planes = 0, nqn = 0;          // distance rows (RowsDistPlan); 0: histograms only
     qc::RowsDev dev{};                // pointers to the buffers below
     uint32_t *d_src = nullptr;        // [4 n_search]
@@ -51,7 +50,6 @@ struct qc_graph_s {
     int64_t nnz = 0;
     int32_t n_components = 0;
     std::vector<int32_t> row_ptr, col;   // the canonical CSR (host copy)
-    std::vector<int32_t> bfs_row_ptr, bfs_col;   // and the subdivided one (weighted edges)
     bool directed = false;
     std::vector<int32_t> comp_size;   // size of each node's component (host)
     BfsPlan plan{};

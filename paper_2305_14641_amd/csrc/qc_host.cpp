@@ -242,7 +242,7 @@ static int32_t uf_find(std::vector<int32_t> &p, int32_t x)
 }
 
 int32_t count_components(int32_t n, const std::vector<int32_t> &rp, const std::vector<int32_t> &col,
-                         std::vector<int32_t> *comp_size, std::vector<int32_t> *label)
+                         std::vector<int32_t> *comp_size)
 {
     std::vector<int32_t> p(n);
     std::iota(p.begin(), p.end(), 0);
@@ -261,8 +261,6 @@ int32_t count_components(int32_t n, const std::vector<int32_t> &rp, const std::v
         comp_size->assign(n, 0);
         for (int32_t i = 0; i < n; ++i) (*comp_size)[i] = size[uf_find(p, i)];
     }
-    if (label)
-        for (int32_t i = 0; i < n; ++i) (*label)[i] = uf_find(p, i);
     return comps;
 }
 

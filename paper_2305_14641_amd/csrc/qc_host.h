@@ -44,10 +44,9 @@ void spread_gather_banks(std::vector<uint32_t> &edges, int64_t nnz, int nodes_pe
                          int banks);
 
 // Number of connected components (union-find over the canonical CSR); if
-// comp_size is given it receives, for every node, the size of its component;
-// `label`, for every node, a node that names its component.
+// comp_size is given it receives, for every node, the size of its component.
 int32_t count_components(int32_t n, const std::vector<int32_t> &rp, const std::vector<int32_t> &col,
-                         std::vector<int32_t> *comp_size = nullptr, std::vector<int32_t> *label = nullptr);
+                         std::vector<int32_t> *comp_size = nullptr);
 
 // The order in which the BFS takes its sources (batch k holds entries
 // k*bw .. k*bw+bw-1). A batch searches until its farthest-reaching source is

@@ -87,8 +87,6 @@ struct RowsDev {
     uint32_t ent_bytes;
     int32_t n_hub;               // the first positions
     int32_t n_pos;               // positions in use
-    int32_t n_own;               // positions of the graph's own nodes (weighted edges: the nodes
-                                 // inside edges come after them, from the next multiple of 256 on)
     // For the distance rows: per node its position (a leaf's: its
     // neighbour's), and 2 bits (1: a leaf, 2: no edges).
     const uint16_t *node_pos;

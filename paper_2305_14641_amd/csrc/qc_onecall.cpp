@@ -35,7 +35,7 @@ OneCall::OneCall(int32_t n, const std::vector<int32_t> &rp, const std::vector<in
     std::vector<int32_t> comp;
     (void)count_components(n, rp, col, &comp);
     plan_ = plan_rows(n_core);
-    t_ = build_rows(n, n, rp, col, false, comp, kind, plan_);
+    t_ = build_rows(n, rp, col, false, comp, kind, plan_);
     rest_ = rest_table(n, rp, col, kind, n_rest_leaf_, n_rest_pair_);
     // The sources in the order of their positions (by decreasing number of
     // entries, which puts far-reaching sources together at the end): one
@@ -166,7 +166,7 @@ qc_status OneCall::run(char *base, size_t limit, uint32_t tie_mode, float *psi_o
         d.rows.rest = (const uint32_t *)at(kRest);
         d.rows.ent_bytes = (uint32_t)parts_[kEnt].bytes;
         d.rows.n_hub = t_.n_hub;
-        d.rows.n_pos = d.rows.n_own = d.rows.n_search = t_.n_pos;
+        d.rows.n_pos = d.rows.n_search = t_.n_pos;
         d.rows.n_leaf = t_.n_leaf;
         d.rows.n_rest = (int32_t)rest_.size();
         d.rows.n_rest_leaf = n_rest_leaf_;

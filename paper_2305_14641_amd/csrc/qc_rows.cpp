@@ -79,7 +79,7 @@ std::vector<uint8_t> rows_kinds(int32_t n, const std::vector<int32_t> &rp,
     return k;
 }
 
-RowsTables build_rows(int32_t n, int32_t own, const std::vector<int32_t> &rp, const std::vector<int32_t> &col,
+RowsTables build_rows(int32_t n, const std::vector<int32_t> &rp, const std::vector<int32_t> &col,
                       bool directed, const std::vector<int32_t> &comp_size,
                       const std::vector<uint8_t> &kind, const RowsPlan &plan)
 {
@@ -101,19 +101,17 @@ RowsTables build_rows(int32_t n, int32_t own, const std::vector<int32_t> &rp, co
     const std::vector<int32_t> &R = directed ? irp : rp, &C = directed ? icol : col;
     // a core node's entries: its in-neighbours that are core nodes
     std::vector<int32_t> len(n, 0);
-    int32_t largest = 0, maxlen = 0, n_core = 0, n_own = 0;
+    int32_t largest = 0, maxlen = 0, n_pos = 0;
     for (int32_t v = 0; v < n; ++v) {
         if (kind[v] != kRowsCore) continue;
         int32_t d = 0;
         for (int32_t e = R[v]; e < R[v + 1]; ++e) d += kind[C[e]] == kRowsCore;
         len[v] = d;
-        ++n_core;
-        n_own += v < own;
+        ++n_pos;
         largest = std::max(largest, comp_size[v]);
         maxlen = std::max(maxlen, d);
     }
-    const int32_t n_pos = t.n_pos = rows_positions(n_core, n_own);
-    t.n_own = n_own;
+    t.n_pos = n_pos;
     std::vector<int32_t> count(maxlen + 2, 0);
     for (int32_t v = 0; v < n; ++v)
         if (kind[v] == kRowsCore) ++count[len[v]];
@@ -128,22 +126,18 @@ RowsTables build_rows(int32_t n, int32_t own, const std::vector<int32_t> &rp, co
         }
     }
     // positions: the hubs, then by decreasing number of entries, those of the
-    // largest component first (counting sort); nodes inside edges, never hubs
-    // (they have two entries at most), come last
+    // largest component first (counting sort)
     std::vector<int32_t> by_pos(n_pos, -1);
     t.pos.assign(n, 0);
     {
         auto key = [&](int32_t v) {   // smaller first
-            if (v >= own) return 2 * (maxlen + 1) + maxlen - len[v];
             if (len[v] > cut) return maxlen - len[v];
             return (comp_size[v] == largest ? 0 : maxlen + 1) + maxlen - len[v];
         };
-        std::vector<int32_t> start(3 * (maxlen + 1) + 1, 0);
+        std::vector<int32_t> start(2 * (maxlen + 1) + 1, 0);
         for (int32_t v = 0; v < n; ++v)
             if (kind[v] == kRowsCore) ++start[key(v) + 1];
         std::partial_sum(start.begin(), start.end(), start.begin());
-        if (n_core > n_own)
-            for (int k = 2 * (maxlen + 1); k <= 3 * (maxlen + 1); ++k) start[k] += n_pos - n_core;
         for (int32_t v = 0; v < n; ++v)
             if (kind[v] == kRowsCore) {
                 const int32_t p = start[key(v)]++;

@@ -41,7 +41,7 @@ std::vector<uint8_t> rows_kinds(int32_t n, const std::vector<int32_t> &rp,
 
 struct RowsTables {
     RowsPlan plan;
-    int32_t n_pos = 0, n_own = 0, n_hub = 0, n_leaf = 0;
+    int32_t n_pos = 0, n_hub = 0, n_leaf = 0;
     std::vector<uint16_t> pos;         // [n] position of every core node (not uploaded)
     std::vector<uint32_t> first;       // [n + 1] its entries in col_pos (not uploaded)
     std::vector<uint16_t> col_pos;
@@ -57,17 +57,10 @@ struct RowsTables {
 // nodes: positions by decreasing number of entries (the nodes of the largest
 // component first), so that the 256 rows of a wavefront's quad have nearly
 // equal lengths and finish together; quads dealt to the wavefronts in turn,
-// hub units to the least loaded ones. Nodes from `own` on (the nodes inside
-// weighted edges) take the positions from the next multiple of 256 on.
-RowsTables build_rows(int32_t n, int32_t own, const std::vector<int32_t> &rp, const std::vector<int32_t> &col,
+// hub units to the least loaded ones.
+RowsTables build_rows(int32_t n, const std::vector<int32_t> &rp, const std::vector<int32_t> &col,
                       bool directed, const std::vector<int32_t> &comp_size,
                       const std::vector<uint8_t> &kind, const RowsPlan &plan);
-
-// Positions that n core nodes take, n_own of them the graph's own.
-inline int32_t rows_positions(int32_t n_core, int32_t n_own)
-{
-    return n_core > n_own ? (n_own + 255) / 256 * 256 + n_core - n_own : n_core;
-}
 
 // The nodes that are not searched: node | neighbour << 16 (0 for none),
 // leaves first, then the ends of isolated edges, then the nodes without

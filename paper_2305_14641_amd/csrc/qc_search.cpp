@@ -16,21 +16,13 @@ static std::vector<uint32_t> source_table(qc_graph g, const RowsState &r)
 {
     std::vector<uint32_t> t;
     t.reserve(4 * (size_t)r.dev.n_search);
-    const std::vector<int32_t> &rp = g->weighted ? g->bfs_row_ptr : g->row_ptr;
-    const std::vector<int32_t> &comp = g->weighted ? r.comp : g->comp_size;
+    const std::vector<int32_t> &rp = g->row_ptr;
     for (int32_t v : g->src_order) {
         if (r.kind[v] != kRowsCore) continue;
-        // own nodes at distance 1: with weights, those that no node inside
-        // an edge stands before
-        uint32_t deg = (uint32_t)(rp[v + 1] - rp[v]);
-        if (g->weighted) {
-            deg = 0;
-            for (int32_t e = rp[v]; e < rp[v + 1]; ++e) deg += g->bfs_col[e] < g->n;
-        }
         t.push_back((uint32_t)v | (uint32_t)r.pos[v] << 16);
         t.push_back(r.first[v]);
-        t.push_back(deg | (r.first[v + 1] - r.first[v]) << 16);
-        t.push_back((uint32_t)comp[v]);
+        t.push_back((uint32_t)(rp[v + 1] - rp[v]) | (r.first[v + 1] - r.first[v]) << 16);
+        t.push_back((uint32_t)g->comp_size[v]);
     }
     return t;
 }
@@ -58,19 +50,17 @@ void free_rows(qc_graph g, RowsState &r)
 // distance rows (nothing is built when no shape holds the graph).
 static qc_status make_rows(qc_graph g, RowsState &r, bool dist)
 {
-    const bool w = g->weighted;
-    const std::vector<int32_t> &rp = w ? g->bfs_row_ptr : g->row_ptr, &col = w ? g->bfs_col : g->col;
+    const std::vector<int32_t> &rp = g->row_ptr, &col = g->col;
     // With the sources in node order (QC_SOURCE_ORDER=identity, a switch for
     // measurements and tests) every node is searched.
     const char *so = getenv("QC_SOURCE_ORDER");
     if (so && strcmp(so, "identity") == 0)
-        r.kind.assign(g->n_bfs, kRowsCore);
+        r.kind.assign(g->n, kRowsCore);
     else
-        r.kind = rows_kinds(g->n_bfs, rp, col, !g->directed && !w);
+        r.kind = rows_kinds(g->n, rp, col, !g->directed);
     const int32_t n_core = (int32_t)std::count(r.kind.begin(), r.kind.end(), (uint8_t)kRowsCore);
-    const int32_t n_own = (int32_t)std::count(r.kind.begin(), r.kind.begin() + g->n, (uint8_t)kRowsCore);
     if (dist) {
-        const RowsDistPlan p = plan_rows_dist(g->n, rows_positions(n_core, n_own), g->dmax_bfs);
+        const RowsDistPlan p = plan_rows_dist(g->n, n_core, g->dmax);
         r.planes = p.rows.nq ? p.planes : 0;
         r.nqn = p.nqn;
         r.plan = p.rows;
@@ -81,23 +71,12 @@ static qc_status make_rows(qc_graph g, RowsState &r, bool dist)
     } else {
         r.plan = plan_rows(n_core);
     }
-    if (w) {
-        std::vector<int32_t> label(g->n_bfs);
-        r.comp.assign(g->n_bfs, 0);
-        // own nodes per (weak) component of the subdivided graph
-        std::vector<int32_t> all;
-        (void)count_components(g->n_bfs, rp, col, &all, &label);
-        std::vector<int32_t> own(g->n_bfs, 0);
-        for (int32_t v = 0; v < g->n; ++v) ++own[label[v]];
-        for (int32_t v = 0; v < g->n_bfs; ++v) r.comp[v] = own[label[v]];
-    }
-    const RowsTables t = build_rows(g->n_bfs, g->n, rp, col, g->directed, w ? r.comp : g->comp_size, r.kind, r.plan);
+    const RowsTables t = build_rows(g->n, rp, col, g->directed, g->comp_size, r.kind, r.plan);
     r.pos = t.pos;
     r.first = t.first;
     r.dev = RowsDev{};
-    r.dev.n_search = n_own;
+    r.dev.n_search = n_core;
     r.dev.n_pos = t.n_pos;
-    r.dev.n_own = t.n_own;
     r.dev.n_hub = t.n_hub;
     r.dev.n_leaf = t.n_leaf;
     r.dev.ent_bytes = (uint32_t)(t.ent.size() * sizeof(uint16_t));
@@ -125,7 +104,7 @@ static qc_status make_rows(qc_graph g, RowsState &r, bool dist)
     const int bw = r.plan.batch();
     // last batch first: the source order puts the farthest-reaching sources
     // (the longest searches) at the end
-    for (int s0 = (n_own + bw - 1) / bw * bw - bw; s0 >= 0; s0 -= bw) jobs.push_back(BfsJob{0, s0, 0u, 0u});
+    for (int s0 = (n_core + bw - 1) / bw * bw - bw; s0 >= 0; s0 -= bw) jobs.push_back(BfsJob{0, s0, 0u, 0u});
     std::vector<NodeJob> rjobs;
     for (int i = 0; i < r.dev.n_rest; i += 32) rjobs.push_back(NodeJob{0, i, 0});
     qc_status s = galloc(g, &r.d_src, src.size());
