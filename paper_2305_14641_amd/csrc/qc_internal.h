@@ -299,15 +299,31 @@ hipError_t launch_dense(const float *dist, int64_t n_rows, int64_t n_cols, int64
                         const double *sigmas, int n_sigmas, double *psi, double *v,
                         hipStream_t stream);
 
-// Shortest paths under real edge weights (qc_sssp.hip): one workgroup per
-// source s0 .. s0+count-1 over an n-node CSR (device row_ptr; col_w holds
-// each entry's column and the bits of its float weight, normal and > 0, as
-// consecutive 32-bit words, 8-byte aligned); row s of `dist` (stride
-// ld >= n) receives the least binary32 path sums from s (+inf unreached).
-// n <= kSsspMaxNodes (the row lives in LDS).
+// Shortest paths under real edge weights (qc_sssp.hip) from the sources
+// src0 .. src0+count-1: row s of `dist` (stride ld >= n) receives the least
+// binary32 path sums from s (+inf unreached). n <= kSsspMaxNodes (the rows
+// live in LDS). Nodes stand in slots, those of many in-edges first; the tables
+// are built for workgroups of sssp_waves(n) wavefronts.
 constexpr int kSsspMaxNodes = 32768;
-hipError_t launch_sssp(int n, const int32_t *row_ptr, const uint32_t *col_w, float *dist, int64_t ld,
-                       int src0, int count, hipStream_t stream);
+constexpr int kSsspBlockRows = 4;   // rows a wavefront loads together
+constexpr uint32_t kSsspEnd = 1, kSsspCut = 2;
+struct SsspDev {
+    int32_t n;
+    int32_t n_cut;              // the first slots, a multiple of 64: nodes whose in-lists are cut into parts
+    const uint16_t *slot;       // [n] of every node
+    const int32_t *row_ptr;     // [n + 1] out-edges by slot
+    const uint2 *edges;         // head's slot and the bits of the weight (normal, > 0)
+    // In-edges in rows of 64 lanes x 3 words: two tails' slots (16 bits each,
+    // n for none) and their weights. Each wavefront's rows are consecutive,
+    // in blocks of kSsspBlockRows with a 16-bit code per row: 0, or
+    // kSsspEnd << 14 | i, the last row of the nodes in slots 64i .. 64i + 63,
+    // or kSsspCut << 14, no edges but the nodes (low half) whose parts end here.
+    const uint32_t *rows;
+    const uint64_t *codes;       // [blocks + 1]
+    const int32_t *wave_block;   // [waves + 1] first block of every wavefront
+};
+int sssp_waves(int n);
+hipError_t launch_sssp(const SsspDev &t, float *dist, int64_t ld, int src0, int count, hipStream_t stream);
 // FP32 resident copy of an FP64 potential [n_sigmas][n] (v_index layout).
 hipError_t launch_v_resident(const double *v64, int n, int n_sigmas, float *v32, hipStream_t stream);
 
