@@ -10,6 +10,10 @@
 // the row. Rows are independent and read once, so the launch needs no
 // cross-workgroup locality and no XCD-aware tile order.
 #include <limits.h>
+#include <math.h>
+#include <string.h>
+
+#include <algorithm>
 
 #include "qc_internal.h"
 
@@ -25,6 +29,7 @@ constexpr int kDenseUnroll = 4;         // 16-byte loads in flight per lane
 struct DenseCoef {
     double c[kDenseMaxChunk];      // -log2(e) / a, a = (2 sigma) sigma
     double inv_a[kDenseMaxChunk];  // 1 / a
+    uint32_t plain;                // bits of the largest d whose d^2 c >= -1000 for every c
 };
 
 // 2^y for y = dd * c <= 0 in FP64: y = k + f with k = rint(y), |f| <= 1/2. 2^f comes
@@ -71,9 +76,31 @@ struct DenseAcc {
             s1[c] = fma(dd, e, s1[c]);
         }
     }
+
+    // The same for an entry with bits(d) <= k.plain: a distance whose every
+    // weight is far from underflow. With y >= -1000 the rounding to an
+    // integer is an addition that leaves it in the sum's low word, and the
+    // scaling an addition to the exponent (12,001^2 entries and 8 widths:
+    // 464 us through the general form, 388 through this one, about 53 cycles
+    // per wavefront and weight of which the exponential and the two
+    // conversions take more than half).
+    __device__ __forceinline__ void add_plain(float d, const DenseCoef &k)
+    {
+        constexpr double kRound = 6755399441055744.0;   // 1.5 * 2^52
+        const double dd = (double)d * (double)d;        // exact: 24-bit mantissas
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            const double t = fma(dd, k.c[c], kRound);
+            const float f = (float)fma(dd, k.c[c], kRound - t);
+            const double p = (double)__builtin_amdgcn_exp2f(f);
+            const double e = __hiloint2double(__double2hiint(p) + (int)((uint32_t)__double2loint(t) << 20), __double2loint(p));
+            s2[c] += e;
+            s1[c] = fma(dd, e, s1[c]);
+        }
+    }
 };
 
-template <int C, bool VEC>
+template <int C>
 __global__ __launch_bounds__(64 * kDenseWaves) void k_dense(
     const float *__restrict__ dist, int64_t n_rows, int64_t n_cols, int64_t ld, DenseCoef coef,
     int n_out, double *__restrict__ psi, double *__restrict__ v, int64_t out_ld)
@@ -84,30 +111,45 @@ __global__ __launch_bounds__(64 * kDenseWaves) void k_dense(
     const float *r = dist + row * ld;
     DenseAcc<C> acc;
     acc.zero();
-    int64_t j0 = 0;
-    if (VEC) {
-        // the row starts on a 16-byte boundary (checked by the launcher)
-        const int64_t nq = n_cols >> 2;
-        global_u4 rq = (global_u4)(const void *)r;
-        int64_t q = lane;
-        for (; q + 64 * (kDenseUnroll - 1) < nq; q += 64 * kDenseUnroll) {
-            u32x4 x[kDenseUnroll];
+    // Whole 16-byte quads from the row's first aligned entry on; the entries
+    // before and after them (at most 3 each) in one step at the end. (Rows of
+    // an odd stride read entry by entry took 554 us for 19,717^2 and one
+    // width; the copy of the same bytes at the card's rate takes about 265.)
+    const int head = (int)min(n_cols, (int64_t)((0 - ((uintptr_t)r >> 2)) & 3));
+    const int64_t nq = (n_cols - head) >> 2;
+    global_u4 rq = (global_u4)(const void *)(r + head);
+    int64_t q = lane;
+    for (; q + 64 * (kDenseUnroll - 1) < nq; q += 64 * kDenseUnroll) {
+        u32x4 x[kDenseUnroll];
 #pragma unroll
-            for (int u = 0; u < kDenseUnroll; ++u) x[u] = rq[q + 64 * u];
+        for (int u = 0; u < kDenseUnroll; ++u) x[u] = rq[q + 64 * u];
+        uint32_t most = 0u;
+#pragma unroll
+        for (int u = 0; u < kDenseUnroll; ++u) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t) most = max(most, x[u][t]);
+        }
+        if (!__ballot(most > coef.plain)) {
+#pragma unroll
+            for (int u = 0; u < kDenseUnroll; ++u) {
+#pragma unroll
+                for (int t = 0; t < 4; ++t) acc.add_plain(__uint_as_float(x[u][t]), coef);
+            }
+        } else {
 #pragma unroll
             for (int u = 0; u < kDenseUnroll; ++u) {
 #pragma unroll
                 for (int t = 0; t < 4; ++t) acc.add(__uint_as_float(x[u][t]), coef);
             }
         }
-        for (; q < nq; q += 64) {
-            const u32x4 x = rq[q];
-#pragma unroll
-            for (int t = 0; t < 4; ++t) acc.add(__uint_as_float(x[t]), coef);
-        }
-        j0 = nq << 2;
     }
-    for (int64_t j = j0 + lane; j < n_cols; j += 64) acc.add(r[j], coef);
+    for (; q < nq; q += 64) {
+        const u32x4 x = rq[q];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) acc.add(__uint_as_float(x[t]), coef);
+    }
+    const int tail = (int)(n_cols - head - 4 * nq);
+    if (lane < head + tail) acc.add(r[lane < head ? (int64_t)lane : n_cols - tail + (lane - head)], coef);
 
 #pragma unroll
     for (int c = 0; c < C; ++c) {
@@ -129,17 +171,12 @@ __global__ __launch_bounds__(64 * kDenseWaves) void k_dense(
 }
 
 template <int C>
-hipError_t launch_chunk(bool vec, const float *dist, int64_t n_rows, int64_t n_cols, int64_t ld,
+hipError_t launch_chunk(const float *dist, int64_t n_rows, int64_t n_cols, int64_t ld,
                         const DenseCoef &k, int n_out, double *psi, double *v, hipStream_t st)
 {
     const dim3 grid((unsigned)((n_rows + kDenseWaves - 1) / kDenseWaves));
     const dim3 block(64 * kDenseWaves);
-    if (vec)
-        hipLaunchKernelGGL((k_dense<C, true>), grid, block, 0, st, dist, n_rows, n_cols, ld, k,
-                           n_out, psi, v, n_rows);
-    else
-        hipLaunchKernelGGL((k_dense<C, false>), grid, block, 0, st, dist, n_rows, n_cols, ld, k,
-                           n_out, psi, v, n_rows);
+    hipLaunchKernelGGL((k_dense<C>), grid, block, 0, st, dist, n_rows, n_cols, ld, k, n_out, psi, v, n_rows);
     return hipGetLastError();
 }
 
@@ -150,26 +187,31 @@ hipError_t launch_dense(const float *dist, int64_t n_rows, int64_t n_cols, int64
                         hipStream_t st)
 {
     const double log2e = 1.4426950408889634;  // log2(e) rounded to FP64
-    const bool vec = ((uintptr_t)dist % 16 == 0) && (ld % 4 == 0);
     for (int s0 = 0; s0 < n_sigmas; s0 += kDenseMaxChunk) {
         const int cnt = n_sigmas - s0 < kDenseMaxChunk ? n_sigmas - s0 : kDenseMaxChunk;
         const int C = cnt <= 1 ? 1 : cnt <= 2 ? 2 : cnt <= 4 ? 4 : 8;
         DenseCoef k;
+        double reach = 3.4e38;
         for (int c = 0; c < kDenseMaxChunk; ++c) {
             const double sigma = sigmas[s0 + (c < cnt ? c : cnt - 1)];
             const double a = (2.0 * sigma) * sigma;
             k.c[c] = -log2e / a;
             k.inv_a[c] = 1.0 / a;
+            reach = std::min(reach, sqrt(1000.0 / -k.c[c]));
         }
+        // (rounded to float and one step down: never above)
+        const float plain = (float)reach;
+        memcpy(&k.plain, &plain, sizeof k.plain);
+        k.plain -= k.plain ? 1u : 0u;
         double *p = psi + (int64_t)s0 * n_rows;
         double *q = v + (int64_t)s0 * n_rows;
         StageTimer timer(QC_STAGE_DENSE, st);
         hipError_t e;
         switch (C) {
-        case 1: e = launch_chunk<1>(vec, dist, n_rows, n_cols, ld, k, cnt, p, q, st); break;
-        case 2: e = launch_chunk<2>(vec, dist, n_rows, n_cols, ld, k, cnt, p, q, st); break;
-        case 4: e = launch_chunk<4>(vec, dist, n_rows, n_cols, ld, k, cnt, p, q, st); break;
-        default: e = launch_chunk<8>(vec, dist, n_rows, n_cols, ld, k, cnt, p, q, st); break;
+        case 1: e = launch_chunk<1>(dist, n_rows, n_cols, ld, k, cnt, p, q, st); break;
+        case 2: e = launch_chunk<2>(dist, n_rows, n_cols, ld, k, cnt, p, q, st); break;
+        case 4: e = launch_chunk<4>(dist, n_rows, n_cols, ld, k, cnt, p, q, st); break;
+        default: e = launch_chunk<8>(dist, n_rows, n_cols, ld, k, cnt, p, q, st); break;
         }
         if (e != hipSuccess) return e;
     }
