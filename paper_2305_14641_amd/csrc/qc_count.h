@@ -36,16 +36,16 @@
 // spends 2 (an address and an OR). What bounds it: the LDS gathers (their
 // bank conflicts double them) and the fixed work per level (counts, barriers,
 // the latency of the first entries), each about 40 % of the time. n = 19,717
-// with 88,726 entries: 119 us against 426 + 114 us (search + histogram pass);
-// 64 graphs of 1,000 to 20,000 nodes x 32 widths as one batch: 1.88 ms
-// against 4.71.
+// with 88,726 entries: 104 us against 426 + 114 us (search + histogram pass);
+// a step over 64 graphs of 1,000 to 20,000 nodes x 32 widths: 4.71 -> 1.88 ms
+// with the descent of the time (1.58 with today's).
 //
 // With P > 0 the search also writes its sources' distance rows: P bit-planes
 // of the level per owned word (as in qc_bfs.h), permuted from the positions'
 // owners to the nodes' through LDS at the end and transposed to bytes there.
 // The planes fill the registers (one workgroup of 16 wavefronts per CU), and
 // the last workgroups' rows leave at HBM speed; n = 19,717, matrix, histograms
-// and all: 271 us against 521 (qc_bfs.h's search and the histogram pass).
+// and all: 250 us against 521 (qc_bfs.h's search and the histogram pass).
 #pragma once
 
 #include "qc_internal.h"
@@ -158,10 +158,13 @@ __device__ __forceinline__ void transpose_bytes(uint32_t (&a)[8])
 // NQ quads (4 positions) per lane, KT threads, PER positions per 32-bit word
 // (1: batches of 32 sources, 2: 16). P > 0: the distance rows of the sources
 // too, from P bit-planes of the level in registers (levels up to 2^P - 2;
-// all ones: not reached), NQN quads of consecutive nodes per lane.
+// all ones: not reached), NQN quads of consecutive nodes per lane. The small
+// counting shapes are held to 64 registers, so that two workgroups of 1,024
+// threads share a CU (two quads: 11 registers go to scratch; 79,000 sources of
+// 4,000 to 8,000 nodes 567 -> 471 us, the step above 1.63 -> 1.58 ms).
 template <int NQ, int KT, int PER, int P, int NQN>
-__global__ __launch_bounds__(KT, 4) void k_count(const GraphDev *__restrict__ graphs,
-                                              const BfsJob *__restrict__ jobs)
+__global__ __launch_bounds__(KT, KT == 1024 && NQ <= 2 && P == 0 ? 8 : 4) void k_count(
+    const GraphDev *__restrict__ graphs, const BfsJob *__restrict__ jobs)
 {
     constexpr int QW = 4 / PER;             // words per quad
     constexpr int NW = NQ * QW;             // words per lane
