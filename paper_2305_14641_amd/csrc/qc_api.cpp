@@ -364,7 +364,7 @@ qc_status run_distances(qc_graph g, hipStream_t st)
         int32_t *hist = nullptr;
         qc_status s = galloc(g, &hist, (size_t)g->n * g->K);
         // later runs need only enough planes for dmax: maybe a wider batch
-        if (s == QC_OK) s = set_plan(g, plan_bfs(g->n_bfs, g->dmax_bfs));
+        if (s == QC_OK) s = set_plan(g, plan_bfs_from(g->n_bfs, g->dmax_bfs, g->n));
         if (s == QC_OK) s = ensure_hist_jobs(g);
         if (s != QC_OK) {
             if (hist) gfree(g, hist);

@@ -482,6 +482,27 @@ BfsPlan plan_bfs(int32_t n, int32_t dmax)
     return plan_bfs_policy(n, dmax, kBfsFullWidth, true);
 }
 
+BfsPlan plan_bfs_from(int32_t n, int32_t dmax, int32_t n_src)
+{
+    // Batches half as wide while every one of them still gets a CU of its own:
+    // they walk the same edges, on CUs that would stand idle, with half the
+    // words (edge weights up to 4 or 5: 4,001 nodes 206 -> 178 us, 3,000:
+    // 170 -> 143, 2,000: 101 -> 92, 1,500: 121 -> 100). Not from the
+    // seen-in-registers shape, whose words cost least (2,500 nodes 110 against
+    // 113 us, 3,500: 103 against 108), nor from fewer than six words per
+    // thread, where the edges and the levels' barriers are what a batch costs
+    // (500 nodes, two words: 57 against 59).
+    constexpr int kCus = 256, kManyWords = 6;
+    BfsPlan p = plan_bfs(n, dmax);
+    if (getenv("QC_BFS_SHAPE") || p.shape == kBfsFront || p.nw < kManyWords) return p;
+    for (int bw = p.bw / 2; bw >= 8 && (n_src + bw - 1) / bw <= kCus; bw /= 2) {
+        const BfsPlan q = plan_bfs_policy(n, dmax, bw, true);
+        if (q.bw != bw) break;
+        p = q;
+    }
+    return p;
+}
+
 static void split_f32(double x, float &hi, float &lo)
 {
     hi = (float)x;
