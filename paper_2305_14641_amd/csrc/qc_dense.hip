@@ -29,7 +29,7 @@ constexpr int kDenseUnroll = 4;         // 16-byte loads in flight per lane
 struct DenseCoef {
     double c[kDenseMaxChunk];      // -log2(e) / a, a = (2 sigma) sigma
     double inv_a[kDenseMaxChunk];  // 1 / a
-    uint32_t plain;                // bits of the largest d whose d^2 c >= -1000 for every c
+    uint32_t plain[kDenseMaxChunk];   // bits of the largest d with d^2 c >= -1000
 };
 
 // 2^y for y = dd * c <= 0 in FP64: y = k + f with k = rint(y), |f| <= 1/2. 2^f comes
@@ -77,25 +77,51 @@ struct DenseAcc {
         }
     }
 
-    // The same for an entry with bits(d) <= k.plain: a distance whose every
-    // weight is far from underflow. With y >= -1000 the rounding to an
-    // integer is an addition that leaves it in the sum's low word, and the
-    // scaling an addition to the exponent (12,001^2 entries and 8 widths:
-    // 464 us through the general form, 388 through this one, about 53 cycles
-    // per wavefront and weight of which the exponential and the two
-    // conversions take more than half).
-    __device__ __forceinline__ void add_plain(float d, const DenseCoef &k)
+    // The same for a batch of entries, one width after another. Where no
+    // entry is beyond k.plain (`most` is the largest, as bits), every weight
+    // is far from underflow: with y >= -1000 the rounding to an integer is an
+    // addition that leaves it in the sum's low word, and the scaling an
+    // addition to the exponent. (12,001^2 entries and 8 widths: 464 us through
+    // the general form, 364 through this one, about 50 cycles per wavefront
+    // and weight of which the exponential and the two conversions take more
+    // than half. A matrix with no-path entries in every batch keeps the
+    // general form: 413 -> 417 us at 12,000^2 and 8 widths; a form of this one
+    // with a select per weight took 142 registers and 424.)
+    template <int N>
+    __device__ __forceinline__ void add_batch(const float (&d)[N], const DenseCoef &k)
     {
-        constexpr double kRound = 6755399441055744.0;   // 1.5 * 2^52
-        const double dd = (double)d * (double)d;        // exact: 24-bit mantissas
+        uint32_t most = 0u;
+#pragma unroll
+        for (int i = 0; i < N; ++i) most = max(most, __float_as_uint(d[i]));
+        if (__ballot(most >= 0x7F800000u)) {   // (negative, NaN or infinite entries)
+#pragma unroll
+            for (int i = 0; i < N; ++i) add(d[i], k);
+            return;
+        }
 #pragma unroll
         for (int c = 0; c < C; ++c) {
-            const double t = fma(dd, k.c[c], kRound);
-            const float f = (float)fma(dd, k.c[c], kRound - t);
-            const double p = (double)__builtin_amdgcn_exp2f(f);
-            const double e = __hiloint2double(__double2hiint(p) + (int)((uint32_t)__double2loint(t) << 20), __double2loint(p));
-            s2[c] += e;
-            s1[c] = fma(dd, e, s1[c]);
+            if (!__ballot(most > k.plain[c])) {
+#pragma unroll
+                for (int i = 0; i < N; ++i) {
+                    constexpr double kRound = 6755399441055744.0;   // 1.5 * 2^52
+                    const double dd = (double)d[i] * (double)d[i];   // exact: 24-bit mantissas
+                    const double t = fma(dd, k.c[c], kRound);
+                    const float f = (float)fma(dd, k.c[c], kRound - t);
+                    const double p = (double)__builtin_amdgcn_exp2f(f);
+                    const double e = __hiloint2double(__double2hiint(p) + (int)((uint32_t)__double2loint(t) << 20),
+                                                      __double2loint(p));
+                    s2[c] += e;
+                    s1[c] = fma(dd, e, s1[c]);
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < N; ++i) {
+                    const double dd = (double)d[i] * (double)d[i];
+                    const double e = exp2_split(dd, k.c[c], true);
+                    s2[c] += e;
+                    s1[c] = fma(dd, e, s1[c]);
+                }
+            }
         }
     }
 };
@@ -123,25 +149,13 @@ __global__ __launch_bounds__(64 * kDenseWaves) void k_dense(
         u32x4 x[kDenseUnroll];
 #pragma unroll
         for (int u = 0; u < kDenseUnroll; ++u) x[u] = rq[q + 64 * u];
-        uint32_t most = 0u;
+        float d[4 * kDenseUnroll];
 #pragma unroll
         for (int u = 0; u < kDenseUnroll; ++u) {
 #pragma unroll
-            for (int t = 0; t < 4; ++t) most = max(most, x[u][t]);
+            for (int t = 0; t < 4; ++t) d[4 * u + t] = __uint_as_float(x[u][t]);
         }
-        if (!__ballot(most > coef.plain)) {
-#pragma unroll
-            for (int u = 0; u < kDenseUnroll; ++u) {
-#pragma unroll
-                for (int t = 0; t < 4; ++t) acc.add_plain(__uint_as_float(x[u][t]), coef);
-            }
-        } else {
-#pragma unroll
-            for (int u = 0; u < kDenseUnroll; ++u) {
-#pragma unroll
-                for (int t = 0; t < 4; ++t) acc.add(__uint_as_float(x[u][t]), coef);
-            }
-        }
+        acc.add_batch(d, coef);
     }
     for (; q < nq; q += 64) {
         const u32x4 x = rq[q];
@@ -191,18 +205,16 @@ hipError_t launch_dense(const float *dist, int64_t n_rows, int64_t n_cols, int64
         const int cnt = n_sigmas - s0 < kDenseMaxChunk ? n_sigmas - s0 : kDenseMaxChunk;
         const int C = cnt <= 1 ? 1 : cnt <= 2 ? 2 : cnt <= 4 ? 4 : 8;
         DenseCoef k;
-        double reach = 3.4e38;
         for (int c = 0; c < kDenseMaxChunk; ++c) {
             const double sigma = sigmas[s0 + (c < cnt ? c : cnt - 1)];
             const double a = (2.0 * sigma) * sigma;
             k.c[c] = -log2e / a;
             k.inv_a[c] = 1.0 / a;
-            reach = std::min(reach, sqrt(1000.0 / -k.c[c]));
+            // (rounded to float and one step down: never above)
+            const float plain = (float)std::min(3.4e38, sqrt(1000.0 / -k.c[c]));
+            memcpy(&k.plain[c], &plain, sizeof plain);
+            k.plain[c] -= k.plain[c] ? 1u : 0u;
         }
-        // (rounded to float and one step down: never above)
-        const float plain = (float)reach;
-        memcpy(&k.plain, &plain, sizeof k.plain);
-        k.plain -= k.plain ? 1u : 0u;
         double *p = psi + (int64_t)s0 * n_rows;
         double *q = v + (int64_t)s0 * n_rows;
         StageTimer timer(QC_STAGE_DENSE, st);
