@@ -16,7 +16,7 @@ Also reported: graphs/s, the plain per-graph path on the same GPU, per-stage
 kernel times (from a pass with every stage in stream order), the search's edge
 visits and LDS bytes gathered, the roofline of the dominant kernel, the
 smaller workloads (one 200-node graph's latency, the 2,708- and 19,717-node
-graphs end to end, psi/V from a resident matrix), the serving form on the
+graphs end to end, psi/V once the distances are there), the serving form on the
 whole 1,024-request stream (p50/p99 latency and graphs/s at several arrival
 rates, against one request at a time), the fully connected dense workload,
 real edge weights (shortest paths and the whole path on the 2,708- and
@@ -48,39 +48,22 @@ def log(msg):
     print(f"[bench] {msg}", file=sys.stderr, flush=True)
 
 
-def bfs_bytes(g) -> float:
-    """Algorithmic bytes of one graph's distance computation: the N^2 int8
-    matrix written once plus the CSR read once (4(N+1) + 4 nnz)."""
-    return float(g.n) * g.n + 4.0 * (g.n + 1) + 4.0 * g.nnz
+PROFILE = os.path.join(ROOT, "profiles", "sweep_kernels.json")
 
 
-PROFILE = os.path.join(ROOT, "profiles", "bench_c4_kernels_and_traffic.json")
-
-
-def profiled_bfs():
-    """The k_bfs entry of the committed counter summary, or None when it is
-    missing or a kernel source changed since it was taken."""
+def profiled(entry: str, source: str):
+    """An entry of the committed counter summary (rocprofv3), or None when it
+    is missing or the kernel's source changed since it was taken."""
     import hashlib
-    if not os.path.exists(PROFILE):
+    try:
+        prof = json.load(open(PROFILE))
+        rel = f"paper_2305_14641_amd/csrc/{source}"
+        with open(os.path.join(ROOT, rel), "rb") as f:
+            if hashlib.sha256(f.read()).hexdigest() != prof["kernel_sources_sha256"][rel]:
+                return None
+        return prof["kernels"].get(entry) or prof.get(entry)
+    except (OSError, KeyError, ValueError):
         return None
-    prof = json.load(open(PROFILE))
-    for rel, digest in prof.get("kernel_sources_sha256", {}).items():
-        path = os.path.join(ROOT, rel)
-        if not os.path.exists(path) or hashlib.sha256(open(path, "rb").read()).hexdigest() != digest:
-            return None
-    return prof.get("k_bfs_tuned")
-
-
-def profiled_traffic(launches_per_step):
-    """HBM bytes per k_bfs launch measured by rocprofv3 FETCH_SIZE / WRITE_SIZE
-    (scaled by a copy-kernel calibration) for the kernel sources as they are
-    now: the profiled batched step's BFS bytes over this run's BFS launches per
-    step (the autotuner's grouping can differ between runs); None when no such
-    profile exists or a kernel source changed since."""
-    prof = profiled_bfs()
-    if not prof or not prof.get("hbm_bytes_per_step"):
-        return None
-    return prof["hbm_bytes_per_step"] / launches_per_step
 
 
 def cpu_model() -> str:
@@ -283,22 +266,18 @@ def configs_leg(args, qc, gg, torch) -> dict:
         out[key] = {"workload": f"DC-SBM N={g.n}, {len(sigmas)} sigma(s)", "end_to_end_ms": ms,
                     "pair_terms_per_s": terms / (ms * 1e-3), "graphs_per_s": 1e3 / ms}
         if key == "c3":
-            # psi/V from the resident matrix: the histogram pass over it and
-            # the potential kernel, device times from the stage events
+            # psi/V once the distances are there (the search leaves the
+            # histograms too): the potential kernel alone, from the stage events
             qc.timing_enable(True)
             reps = max(args.steps, 5)
             for _ in range(reps):
                 G.distances(dist)
                 G.potential(sigmas)
             torch.cuda.synchronize()
-            h_ms, _ = qc.timing_read(qc.STAGE_HIST)
             p_ms, _ = qc.timing_read(qc.STAGE_POTENTIAL)
             qc.timing_enable(False)
-            t = (h_ms + p_ms) / reps
-            out[key]["potential_from_resident_matrix"] = {
-                "hist_ms": h_ms / reps, "potential_ms": p_ms / reps, "ms": t,
-                "pair_terms_per_s": terms / (t * 1e-3),
-                "hbm_gbs": (float(g.n) ** 2 + 8.0 * g.n * 32 + 8.0 * g.n * len(sigmas)) / (t * 1e-3) / 1e9}
+            t = p_ms / reps
+            out[key]["potential_after_distances"] = {"ms": t, "pair_terms_per_s": terms / (t * 1e-3)}
         log(f"{key}: {ms:.3f} ms end to end, {terms / (ms * 1e-3):.3e} pair-terms/s")
         del dist
         G.close()
@@ -342,40 +321,38 @@ def quality_sweep(qc, gg, torch) -> dict:
             "rows": rows}
 
 
-DENSE_PROFILE = os.path.join(ROOT, "profiles", "k_dense_fully_connected_n20000.json")
+def search_roofline(stages, lds_gathered):
+    """The counting search's launches against the LDS rate: bytes of the bit
+    fields that its edge visits gather (counted on the device) over the
+    search's device time, against 256 CUs x 128 bytes x 2.4 GHz; HBM traffic
+    per launch from the committed counters while the source is unchanged."""
+    prof = profiled("k_count_average", "qc_count.h")
+    achieved = lds_gathered / (stages["bfs"]["ms_per_step"] * 1e-3) / 1e9
+    peak = LDS_PEAK_TBS * 1e3
+    return {"bound": "lds", "kernel": "k_count", "achieved": achieved, "peak": peak, "unit": "GB/s",
+            "frac": achieved / peak,
+            "traffic": (prof["hbm_read_bytes_per_launch"] + prof["hbm_write_bytes_per_launch"]) if prof else None,
+            "traffic_unit": "HBM bytes per launch (rocprofv3 counters, copy-calibrated)",
+            "lds_bytes_gathered_per_launch": lds_gathered / stages["bfs"]["launches_per_step"]}
 
 
-def dense_profile(kernel: str):
-    """Counter figures per launch of one dense-kernel instance from the
-    committed summary, while the kernel source is unchanged since then."""
-    import hashlib
-    try:
-        prof = json.load(open(DENSE_PROFILE))
-        src = os.path.join(ROOT, "paper_2305_14641_amd", "csrc", "qc_dense.hip")
-        if hashlib.sha256(open(src, "rb").read()).hexdigest() != prof["kernel_source_sha256"]:
-            return None
-        return prof["kernels"][kernel]
-    except (OSError, KeyError, ValueError):
+def search_alu(stages):
+    """Vector-ALU view of the counting search: VALU lane-operations per second
+    (counted wavefront instructions per launch x 64 lanes, from the committed
+    counter summary) against the issue rate of 256 CUs x 64 lanes x 2.4 GHz."""
+    prof = profiled("k_count_average", "qc_count.h")
+    if not prof:
         return None
-
-
-def bfs_alu(stages):
-    """Vector-ALU view of k_bfs: VALU lane-operations per second (counted
-    wavefront instructions x 64 lanes, from the committed counter summary)
-    against the issue rate of 256 CUs x 64 lanes x 2.4 GHz."""
-    prof = profiled_bfs()
-    if not prof or not prof.get("valu_wave_instructions_per_step"):
-        return None
-    ops = prof["valu_wave_instructions_per_step"] * 64 / (stages["bfs"]["ms_per_step"] * 1e-3) / 1e12
-    return {"bound": "alu", "kernel": "k_bfs", "achieved": ops, "peak": VALU_PEAK_TOPS,
+    per_step = prof["valu_wave_instructions_per_launch"] * stages["bfs"]["launches_per_step"]
+    ops = per_step * 64 / (stages["bfs"]["ms_per_step"] * 1e-3) / 1e12
+    return {"bound": "alu", "kernel": "k_count", "achieved": ops, "peak": VALU_PEAK_TOPS,
             "unit": "T VALU lane-ops/s", "frac": ops / VALU_PEAK_TOPS,
-            "valu_wave_instructions_per_step": prof["valu_wave_instructions_per_step"],
-            "lds_wave_instructions_per_step": prof.get("lds_wave_instructions_per_step")}
+            "valu_wave_instructions_per_launch": prof["valu_wave_instructions_per_launch"]}
 
 
 def real_leg(args, qc, torch) -> dict:
-    """Shortest paths under real edge weights (qc_distances_real: one
-    workgroup per source, binary32 path sums) and the whole real-weighted
+    """Shortest paths under real edge weights (qc_distances_real: binary32
+    path sums) and the whole real-weighted
     path (qc_cluster_real) on the 2,708- and 19,717-node graphs with seeded
     uniform weights in [0.5, 4). Kernel times from the library's stage
     events; call times include the CSR upload and the final wait."""
@@ -458,7 +435,7 @@ def dense_leg(args, qc, torch) -> dict:
         terms = float(n) * n * S
         alg = 4.0 * n * n * launches
         gbs = alg / (per * 1e-3) / 1e9
-        prof = dense_profile(f"k_dense<{min(S, 8)}, true>")
+        prof = profiled(f"k_dense<{min(S, 8)}>", "qc_dense.hip")
         traffic = (prof["hbm_read_bytes_per_launch"] + prof["hbm_write_bytes_per_launch"]) if prof else None
         hbm = {"bound": "hbm", "kernel": f"k_dense<{min(S, 8)}>", "achieved": gbs,
                "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": gbs / HBM_PEAK_GBS, "traffic": traffic,
@@ -618,13 +595,6 @@ def main():
     qc.timing_enable(False)
     dom = max(stages, key=lambda k: stages[k]["ms_per_step"])
     bfs_ms = stages["bfs"]["ms_per_step"]
-    bfs_launches = stages["bfs"]["launches_per_step"]
-    bytes_step = sum(bfs_bytes(g) for g in graphs)
-    achieved = (bytes_step / bfs_launches) / (stages["bfs"]["avg_launch_ms"] * 1e-3) / 1e9
-    hist_bytes = sum(float(g.n) * g.n + 4.0 * g.n * 32 for g in graphs)
-    # (zero when every graph's search makes its histograms itself)
-    hist_ms = stages["hist"]["ms_per_step"]
-    hist_gbs = hist_bytes / (hist_ms * 1e-3) / 1e9 if hist_ms > 0 else None
     log(f"stages: " + ", ".join(f"{k}={v_['ms_per_step']:.3f}ms" for k, v_ in stages.items()))
 
     # -- plain per-graph path (one graph at a time, synchronous); its first
@@ -740,14 +710,8 @@ def main():
                   "jump": stage_tiles["jump"],
                   "stages_beside_searches": stage_tiles["overlap"]},
         "dominant_kernel": dom,
-        "roofline": {
-            "bound": "hbm", "kernel": "k_bfs",
-            "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-            "frac": achieved / HBM_PEAK_GBS, "traffic": profiled_traffic(bfs_launches),
-            "traffic_unit": "HBM bytes per launch (rocprofv3 counters, copy-calibrated)",
-            "algorithmic_bytes_per_launch": bytes_step / bfs_launches,
-        },
-        "bfs_alu": bfs_alu(stages),
+        "roofline": search_roofline(stages, lds_gathered),
+        "bfs_alu": search_alu(stages),
         "bfs_search": {
             "edge_visits_per_step": edge_visits,
             "edge_visits_per_s": edge_visits / (bfs_ms * 1e-3),
@@ -758,7 +722,6 @@ def main():
             "note": "visits counted on the device (pulled levels x edge entries + pushed row "
                     "entries); time = the search's device time per step",
         },
-        "hist_kernel_gbs": hist_gbs,
         "plain": plain,
         "bf16_sweep": bf16,
         "dense": dense,
