@@ -187,16 +187,26 @@ SsspTables build_sssp(int32_t n, const std::vector<int32_t> &rp, const std::vect
 qc_status real_distances(int32_t n, const std::vector<int32_t> &rp, const std::vector<int32_t> &col,
                          const float *weights, bool directed, float *dist, int64_t ld, hipStream_t st)
 {
-    const SsspTables t = build_sssp(n, rp, col, weights, directed);
-    auto whole = [](size_t bytes) { return (bytes + 255) & ~(size_t)255; };
-    const size_t rows_at = whole(t.image.size()), edges_at = rows_at + whole(t.rows.size() * 4);
+    // (all host memory is taken before any device work)
+    SsspTables t;
+    std::vector<char> all;
+    size_t rows_at = 0, edges_at = 0;
+    QC_TRY(guarded([&] {
+        auto whole = [](size_t bytes) { return (bytes + 255) & ~(size_t)255; };
+        t = build_sssp(n, rp, col, weights, directed);
+        rows_at = whole(t.image.size());
+        edges_at = rows_at + whole(t.rows.size() * 4);
+        if (edges_at <= kOneUpload) {
+            all.resize(edges_at + t.edges.size() * 4);
+            memcpy(all.data(), t.image.data(), t.image.size());
+            memcpy(all.data() + rows_at, t.rows.data(), t.rows.size() * 4);
+            if (!t.edges.empty()) memcpy(all.data() + edges_at, t.edges.data(), t.edges.size() * 4);
+        }
+        return QC_OK;
+    }));
     char *base = nullptr;
     qc_status s = dalloc(&base, edges_at + t.edges.size() * 4);
-    if (s == QC_OK && edges_at <= kOneUpload) {
-        std::vector<char> all(edges_at + t.edges.size() * 4);
-        memcpy(all.data(), t.image.data(), t.image.size());
-        memcpy(all.data() + rows_at, t.rows.data(), t.rows.size() * 4);
-        if (!t.edges.empty()) memcpy(all.data() + edges_at, t.edges.data(), t.edges.size() * 4);
+    if (s == QC_OK && !all.empty()) {
         s = upload(base, all);
     } else {
         if (s == QC_OK) s = upload(base, t.image);
