@@ -246,9 +246,13 @@ int hist_waves(int K, int variant);
 
 // psi/V of every (node, sigma); one job = kNodesPerJob nodes of one graph.
 // Optional caller outputs: out[out_off + s*out_ld + (i - i0_of_graph)].
+// `derive` (FP64ACC, after a counting search whose G.rows.rest has one entry
+// per node: 0, or its kind << 16 | a leaf's neighbour): the rows of the nodes
+// that the search leaves out are derived on the way, not read.
+constexpr uint32_t kRestLeaf = 1, kRestPair = 2, kRestAlone = 3;
 hipError_t launch_potential(int precision, int K, const GraphDev *graphs, const NodeJob *jobs,
                             int n_jobs, float *psi_out, float *v_out, int64_t out_ld,
-                            hipStream_t stream);
+                            hipStream_t stream, bool derive = false);
 
 // Descent parents for sigmas sigma_base .. sigma_base+n_sig-1 of every job.
 hipError_t launch_ggd_parent(int tie_mode, const GraphDev *graphs, const NodeJob *jobs,

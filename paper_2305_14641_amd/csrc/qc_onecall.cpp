@@ -1,6 +1,6 @@
 // Algorithm 4 in one call (see qc_onecall.h): one host-to-device copy of all
-// tables, five launches (search, the rows it leaves out, potentials, descent
-// and pointer jumping of every width), one 8-byte copy back.
+// tables, three launches (search; potentials with the rows it leaves out; descent
+// and pointer jumping of every width, two above kDescendNodes), one 8-byte copy back.
 #include "qc_onecall.h"
 
 #include <math.h>
@@ -18,7 +18,7 @@ size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
 // Parts of the image, in order.
 enum {
     kDesc, kStatus, kRecheck, kOrder, kSellCol, kSellOff, kSellDeg, kSrc, kColPos, kCodes, kWaveRow, kWaveUnit,
-    kEnt, kUnits, kLeaf, kRest, kJobs, kRestJobs, kNodeJobs, kW64, kInvA, kParts
+    kEnt, kUnits, kLeaf, kRest, kJobs, kNodeJobs, kW64, kInvA, kParts
 };
 
 const int32_t kZero[2] = {0, 0};
@@ -36,7 +36,10 @@ OneCall::OneCall(int32_t n, const std::vector<int32_t> &rp, const std::vector<in
     (void)count_components(n, rp, col, &comp);
     plan_ = plan_rows(n_core);
     t_ = build_rows(n, rp, col, false, comp, kind, plan_);
-    rest_ = rest_table(n, rp, col, kind, n_rest_leaf_, n_rest_pair_);
+    rest_.assign(n, 0u);
+    for (int32_t v = 0; v < n; ++v)
+        if (kind[v] == kRowsLeaf) rest_[v] = kRestLeaf << 16 | (uint32_t)col[rp[v]];
+        else if (kind[v] != kRowsCore) rest_[v] = (kind[v] == kRowsPair ? kRestPair : kRestAlone) << 16;
     // The sources in the order of their positions (by decreasing number of
     // entries, which puts far-reaching sources together at the end): one
     // search does not repay the host sweeps that bound eccentricities.
@@ -52,7 +55,6 @@ OneCall::OneCall(int32_t n, const std::vector<int32_t> &rp, const std::vector<in
     descent_ = build_descent(n, rp, col);
     const int bw = plan_.batch();
     for (int s0 = (n_core + bw - 1) / bw * bw - bw; s0 >= 0; s0 -= bw) jobs_.push_back(BfsJob{0, s0, 0u, 0u});
-    for (int i = 0; i < (int)rest_.size(); i += 32) rest_jobs_.push_back(NodeJob{0, i, 0});
     for (int i = 0; i < n; i += kNodesPerJob) node_jobs_.push_back(NodeJob{0, i, 0});
 }
 
@@ -90,7 +92,6 @@ size_t OneCall::lay_out(int bins)
     part(kLeaf, t_.leaf);
     part(kRest, rest_);
     part(kJobs, jobs_);
-    part(kRestJobs, rest_jobs_);
     part(kNodeJobs, node_jobs_);
     part(kW64, w64_);
     part(kInvA, inv_a_);
@@ -168,9 +169,6 @@ qc_status OneCall::run(char *base, size_t limit, uint32_t tie_mode, float *psi_o
         d.rows.n_hub = t_.n_hub;
         d.rows.n_pos = d.rows.n_search = t_.n_pos;
         d.rows.n_leaf = t_.n_leaf;
-        d.rows.n_rest = (int32_t)rest_.size();
-        d.rows.n_rest_leaf = n_rest_leaf_;
-        d.rows.n_rest_pair = n_rest_pair_;
         parts_[kDesc].src = &d;
         try {
             image.resize(image_);
@@ -194,12 +192,8 @@ qc_status OneCall::run(char *base, size_t limit, uint32_t tie_mode, float *psi_o
         stage(QC_STAGE_BFS, [&] {
             return launch_count(plan_.nq, plan_.threads, plan_.per, desc, (const BfsJob *)at(kJobs), (int)jobs_.size(), st);
         });
-        stage(QC_STAGE_HIST, [&] {
-            return launch_hist_rest(bins, desc, (const NodeJob *)at(kRestJobs), (int)rest_jobs_.size(),
-                                    hist_waves(bins, 0), st);
-        });
         stage(QC_STAGE_POTENTIAL, [&] {
-            return launch_potential(QC_PREC_FP64ACC, bins, desc, nodes, (int)node_jobs_.size(), psi_out, v_out, n_, st);
+            return launch_potential(QC_PREC_FP64ACC, bins, desc, nodes, (int)node_jobs_.size(), psi_out, v_out, n_, st, true);
         });
         if (n_ <= kDescendNodes) {
             stage(QC_STAGE_GGD, [&] { return launch_descend((int)tie_mode, desc, nodes, 1, 0, S_, labels, n_, n_, st); });

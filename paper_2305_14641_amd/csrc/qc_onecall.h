@@ -53,10 +53,9 @@ class OneCall {
     RowsPlan plan_;
     RowsTables t_;
     std::vector<uint32_t> src_, rest_;
-    int32_t n_rest_leaf_ = 0, n_rest_pair_ = 0;
     Descent descent_;
     std::vector<BfsJob> jobs_;
-    std::vector<NodeJob> rest_jobs_, node_jobs_;
+    std::vector<NodeJob> node_jobs_;
     std::vector<double> w64_, inv_a_;
     std::vector<Part> parts_;
     size_t image_ = 0, total_ = 0;
