@@ -544,7 +544,7 @@ qc_status some_labels(qc_graph g, int32_t first, int32_t count, uint32_t tie_mod
     }
     {
         StageTimer t(QC_STAGE_JUMP, st);
-        QC_HIP(launch_pointer_jump(g->d_desc, g->d_node_jobs, 1, first, count, labels_out, g->n, g->n, st));
+        QC_HIP(launch_pointer_jump(g->d_desc, g->d_node_jobs, 1, first, count, labels_out, g->n, st));
     }
     return QC_OK;
 }

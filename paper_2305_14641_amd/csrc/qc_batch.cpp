@@ -45,7 +45,6 @@ struct Stages {
                                // -2: the last launch's, on the caller's stream, beside the side stream)
     bool rest = true;
     std::vector<KGroup> hist, pot;
-    int max_n = 0;             // largest node count among the graphs
     // Descent and pointer jumping through global memory, for every graph
     // ([1], the jump variant that asks for it) or those that the
     // one-workgroup descent can't hold ([0]).
@@ -357,8 +356,8 @@ qc_status run_stages(qc_batch b, const Stages &c, float *psi_out, float *v_out, 
     }
     if (f.n_jump_jobs) {
         StageTimer t(QC_STAGE_JUMP, st);
-        QC_HIP(launch_pointer_jump(b->d_descs, f.d_jump_jobs, f.n_jump_jobs, 0, S, labels_out, total,
-                                   c.max_n, st, b->jump_variant));
+        QC_HIP(launch_pointer_jump(b->d_descs, f.d_jump_jobs, f.n_jump_jobs, 0, S, labels_out, total, st,
+                                   b->jump_variant));
     }
     return QC_OK;
 }
@@ -508,7 +507,6 @@ qc_status autotune_stages(qc_batch b, hipStream_t st)
         if (s == QC_OK) g_tiles[key] = chosen;
     };
     if (s == QC_OK) tune(0, 3, set_hist);
-    if (s == QC_OK && max_n > kDescendNodes && max_n <= 40704) tune(1, 2, [&](int v) { b->jump_variant = v; });
     (void)hipStreamSynchronize(st);
     dfree(labels);
     return s;
@@ -736,7 +734,6 @@ qc_status qc_batch_create(const qc_graph *graphs, int32_t n_graphs, const double
         std::map<int, std::vector<int>> by_k;
         for (int gi : gis) {
             by_k[graphs[gi]->K].push_back(gi);
-            c.max_n = std::max(c.max_n, (int)graphs[gi]->n);
         }
         for (auto &kv : by_k) {
             const int K = kv.first;
@@ -895,7 +892,7 @@ qc_status qc_batch_stage_tiles(qc_batch b, int32_t *bfs_widest_out, int32_t *bfs
                 hist_waves_out[slot] = hist_waves(g.K, g.variant);
             }
     }
-    if (jump_global_out) *jump_global_out = (b->jump_variant == 1 || batch_max_n(b) > 40704) ? 1 : 0;
+    if (jump_global_out) *jump_global_out = b->jump_variant == 1 ? 1 : 0;
     if (overlap_out) *overlap_out = b->overlap;
     return QC_OK;
 }

@@ -259,12 +259,11 @@ hipError_t launch_ggd_parent(int tie_mode, const GraphDev *graphs, const NodeJob
                              int n_jobs, int sigma_base, int n_sig, hipStream_t stream);
 
 // Pointer jumping, one workgroup per (graph job, sigma); labels of sigma
-// sigma_base + y go to labels_base + y*labels_ld + job.out_off. max_n: the
-// largest node count among the jobs' graphs (up to 40,704 the rounds run in
-// LDS unless `variant` is 1: always in global memory).
+// sigma_base + y go to labels_base + y*labels_ld + job.out_off. The rounds run
+// in LDS, or in global memory where `variant` is 1.
 hipError_t launch_pointer_jump(const GraphDev *graphs, const NodeJob *jobs, int n_jobs,
                                int sigma_base, int n_sig, int32_t *labels_base,
-                               int64_t labels_ld, int max_n, hipStream_t stream, int variant = 0);
+                               int64_t labels_ld, hipStream_t stream, int variant = 0);
 
 // Descent and pointer jumping of (graph job, sigma) pairs in one launch, each
 // in one workgroup's LDS (qc_descend.hip): graphs of at most kDescendNodes

@@ -201,7 +201,7 @@ qc_status OneCall::run(char *base, size_t limit, uint32_t tie_mode, float *psi_o
             stage(QC_STAGE_GGD, [&] {
                 return launch_ggd_parent((int)tie_mode, desc, nodes, (int)node_jobs_.size(), 0, S_, st);
             });
-            stage(QC_STAGE_JUMP, [&] { return launch_pointer_jump(desc, nodes, 1, 0, S_, labels, n_, n_, st); });
+            stage(QC_STAGE_JUMP, [&] { return launch_pointer_jump(desc, nodes, 1, 0, S_, labels, n_, st); });
         }
         int32_t status[2] = {0, 0};
         if (e == hipSuccess) e = hipMemcpyAsync(status, at(kStatus), sizeof status, hipMemcpyDeviceToHost, st);

@@ -48,7 +48,9 @@ GRAPHS = [gg.path_graph(1), gg.path_graph(2), gg.empty_graph(65), gg.path_graph(
           gg.complete_graph(300), fans([6, 7, 8, 9, 29, 30, 31, 32, 33, 63, 64, 130]), gg.twin_leaves(60, 40),
           circulant(4095, 700), circulant(4096, 20), ring_with_chords(5000, 1), gg.dcsbm(4097, [0.6, 0.4], 6.0, seed=2),
           gg.dcsbm(12864, [0.5, 0.5], 5.0, seed=3), gg.dcsbm(12865, [0.5, 0.5], 5.0, seed=4),
-          gg.dcsbm(26560, [0.4, 0.6], 5.0, seed=5), gg.dcsbm(26561, [0.4, 0.6], 5.0, seed=6)]
+          gg.dcsbm(26560, [0.4, 0.6], 5.0, seed=5), gg.dcsbm(26561, [0.4, 0.6], 5.0, seed=6),
+          gg.dcsbm(40705, [0.4, 0.6], 5.0, seed=7), gg.dcsbm(65533, [0.4, 0.6], 4.0, seed=8),
+          gg.dcsbm(65536, [0.4, 0.6], 4.0, seed=9)]
 
 
 @pytest.mark.parametrize("g", GRAPHS, ids=lambda g: f"{g.name}-{g.n}")
