@@ -22,7 +22,7 @@ enum {
     QC_BATCH_HIPGRAPH = 1u, /* capture the launch sequence once, replay it afterwards */
     QC_BATCH_FP32C = 2u,    /* potentials in compensated FP32 instead of FP64 accumulation */
     QC_BATCH_AUTOTUNE = 4u, /* time the candidate launch shapes (BFS planning policy, histogram pass,
-                               pointer jumping, each over the whole batch), keep the fastest */
+                               each over the whole batch), keep the fastest */
     QC_BATCH_SERIAL = 8u    /* run every stage in stream order on the caller's stream (see below) */
 };
 
@@ -56,8 +56,8 @@ enum {
  *              candidate planning policy, timed with events on `stream`;
  *              the fastest policy's plans stay with the graphs, for this
  *              batch and for their own later calls; then the whole path runs
- *              once and the histogram and pointer-jumping shapes are timed,
- *              see qc_batch_stage_tiles. The outputs do not depend on it.)
+ *              once and the histogram pass's shapes are timed, see
+ *              qc_batch_stage_tiles. The outputs do not depend on it.)
  *   stream     stream for any set-up work (graphs whose largest distance is
  *              not yet known run their distances once here, synchronously)
  *   out        host, receives the batch handle
@@ -137,12 +137,11 @@ qc_status qc_batch_sweep_bf16(qc_batch b, float *psi_out, float *v_out, void *st
  * policy (widest batch 32, 64 or 16 with the seen-in-registers shape first,
  * and 32 without it); then, after one run of the whole path, it times whole
  * steps with the histogram pass in three shapes (the default wavefront
- * count, half and twice) and with the pointer jumping in LDS and in global
- * memory (in interleaved rounds, each variant's best round). Each default
+ * count, half and twice; in interleaved rounds, each variant's best round). Each default
  * (the first policy, the first variant) stays unless an alternative is
  * faster by 2 % (policies) or 1 % (variants); a later batch of the same
- * class (row length, rows, largest graph) in the process reuses the two
- * stage choices without timing. The outputs do not depend on any of these
+ * class (row length, rows, largest graph) in the process reuses the
+ * stage choice without timing. The outputs do not depend on any of these
  * choices.
  */
 qc_status qc_batch_stage_tiles(qc_batch b, int32_t *bfs_widest_out, int32_t *bfs_front_first_out,

@@ -535,7 +535,8 @@ qc_status some_labels(qc_graph g, int32_t first, int32_t count, uint32_t tie_mod
     if (g->n > kDescendNodes || count > 1) QC_HIP(launch_fill_u64(g->d_recheck, 1, st));
     if (g->n <= kDescendNodes) {
         StageTimer t(QC_STAGE_GGD, st);
-        QC_HIP(launch_descend((int)tie_mode, g->d_desc, g->d_node_jobs, 1, first, count, labels_out, g->n, g->n, st));
+        QC_HIP(launch_descend((int)tie_mode, g->d_desc, g->d_node_jobs, 1, first, count, labels_out, g->n, g->n, st,
+                              count == 1));
         return QC_OK;
     }
     {

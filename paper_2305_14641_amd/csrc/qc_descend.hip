@@ -92,7 +92,7 @@ constexpr int kChunk = 4;   // words (pairs of neighbours) in flight per thread
 template <int CAP>
 __global__ __launch_bounds__(1024, CAP <= kDescendHalfNodes ? 8 : 4) void k_descend(
     int tie_mode, const GraphDev *__restrict__ graphs, const NodeJob *__restrict__ jobs, int sigma_base,
-    int32_t *labels_base, int64_t labels_ld)
+    int32_t *labels_base, int64_t labels_ld, bool store_count)
 {
     constexpr int T = 1024, kWaves = T / 64, kGroups = T / kShare;
     constexpr uint16_t kUndecided = 0xFFFF;
@@ -348,7 +348,7 @@ __global__ __launch_bounds__(1024, CAP <= kDescendHalfNodes ? 8 : 4) void k_desc
     }
     if (tid == 0) {
         const unsigned long long ties = (unsigned long long)(n_few + n_many);
-        if (gridDim.x * gridDim.y == 1) *G.recheck = ties;
+        if (store_count) *G.recheck = ties;
         else if (ties) atomicAdd(G.recheck, ties);
     }
     __syncthreads();
@@ -387,17 +387,18 @@ __global__ __launch_bounds__(1024, CAP <= kDescendHalfNodes ? 8 : 4) void k_desc
 }  // namespace
 
 hipError_t launch_descend(int tie_mode, const GraphDev *graphs, const NodeJob *jobs, int n_jobs, int sigma_base,
-                          int n_sig, int32_t *labels_base, int64_t labels_ld, int max_n, hipStream_t stream)
+                          int n_sig, int32_t *labels_base, int64_t labels_ld, int max_n, hipStream_t stream,
+                          bool store_count)
 {
     if (n_jobs <= 0 || n_sig <= 0) return hipSuccess;
-    if (max_n > kDescendNodes) return hipErrorInvalidValue;
+    if (max_n > kDescendNodes || (store_count && (n_jobs > 1 || n_sig > 1))) return hipErrorInvalidValue;
     const dim3 grid(n_sig, n_jobs), block(1024);
     if (max_n <= kDescendHalfNodes)   // two workgroups per CU
-        hipLaunchKernelGGL(k_descend<kDescendHalfNodes>, grid, block, 0, stream, tie_mode, graphs, jobs, sigma_base, labels_base,
-                           labels_ld);
+        hipLaunchKernelGGL(k_descend<kDescendHalfNodes>, grid, block, 0, stream, tie_mode, graphs, jobs, sigma_base,
+                           labels_base, labels_ld, store_count);
     else
         hipLaunchKernelGGL(k_descend<kDescendNodes>, grid, block, 0, stream, tie_mode, graphs, jobs, sigma_base,
-                           labels_base, labels_ld);
+                           labels_base, labels_ld, store_count);
     return hipGetLastError();
 }
 

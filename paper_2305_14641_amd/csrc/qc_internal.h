@@ -269,10 +269,12 @@ hipError_t launch_pointer_jump(const GraphDev *graphs, const NodeJob *jobs, int 
 // in one workgroup's LDS (qc_descend.hip): graphs of at most kDescendNodes
 // nodes (4 bytes of V and 2 of parent per node, and the near ties' queues,
 // fill the 160 KB); labels as launch_pointer_jump. Two workgroups fit a CU up
-// to kDescendHalfNodes.
+// to kDescendHalfNodes. Near ties are added to the graph's recheck counter, or
+// stored there with `store_count` (one job and one sigma only).
 constexpr int kDescendNodes = 26560, kDescendHalfNodes = 12864;
 hipError_t launch_descend(int tie_mode, const GraphDev *graphs, const NodeJob *jobs, int n_jobs, int sigma_base,
-                          int n_sig, int32_t *labels_base, int64_t labels_ld, int max_n, hipStream_t stream);
+                          int n_sig, int32_t *labels_base, int64_t labels_ld, int max_n, hipStream_t stream,
+                          bool store_count = false);
 
 // Stage timing (qc_timing.cpp): Timer brackets one launch when enabled.
 class StageTimer {

@@ -104,3 +104,32 @@ def test_mixed_sizes_in_a_batch():
     b.close()
     for h in handles:
         h.close()
+
+
+@pytest.mark.parametrize("sigmas", [[0.3], [0.3, 1.0]])
+def test_recheck_counts_add_up(sigmas):
+    """Near ties of a batch are those of its graphs, also where each launch
+    holds one (graph, sigma) only; a graph's own count is its last call's."""
+    import torch
+    from paper_2305_14641_amd import qc
+    handles = [qc.Graph.from_graph(gg.dcsbm(n, [0.4, 0.6], 5.0, seed=n)) for n in (27000, 13000, 900)]
+    want = 0
+    for h in handles:
+        h.potential(sigmas)
+        counts = []
+        for k in range(len(sigmas)):
+            h.labels(k)
+            counts.append(h.recheck_count())
+            h.labels(k)
+            assert h.recheck_count() == counts[-1]
+        assert counts[0] > 0
+        want += sum(counts)
+    b = qc.Batch(handles, sigmas, hipgraph=False)
+    outs = b.outputs()
+    for _ in range(2):
+        b.run(*outs)
+        torch.cuda.synchronize()
+        assert b.recheck_count() == want
+    b.close()
+    for h in handles:
+        h.close()
