@@ -128,12 +128,14 @@ qc_status OneCall::run(char *base, size_t limit, uint32_t tie_mode, float *psi_o
     // hold it.
     for (int bins = 32;;) {
         if (lay_out(bins) > limit) return QC_E_TOO_LARGE;
+        // (this layout's addresses: longer rows move everything behind them)
         int32_t *labels = labels_out;
+        float *psi = psi_out, *v = v_out;
         if (with_outputs_) {
             results_ = base + out_;
             if (!labels) labels = (int32_t *)results_;
-            if (with_potentials_ && !psi_out) psi_out = (float *)(results_ + (size_t)S_ * n_ * 4);
-            if (with_potentials_ && !v_out) v_out = (float *)(results_ + (size_t)S_ * n_ * 8);
+            if (with_potentials_ && !psi) psi = (float *)(results_ + (size_t)S_ * n_ * 4);
+            if (with_potentials_ && !v) v = (float *)(results_ + (size_t)S_ * n_ * 8);
         }
         auto at = [&](int i) { return (void *)(base + parts_[i].off); };
         GraphDev d;
@@ -193,7 +195,7 @@ qc_status OneCall::run(char *base, size_t limit, uint32_t tie_mode, float *psi_o
             return launch_count(plan_.nq, plan_.threads, plan_.per, desc, (const BfsJob *)at(kJobs), (int)jobs_.size(), st);
         });
         stage(QC_STAGE_POTENTIAL, [&] {
-            return launch_potential(QC_PREC_FP64ACC, bins, desc, nodes, (int)node_jobs_.size(), psi_out, v_out, n_, st, true);
+            return launch_potential(QC_PREC_FP64ACC, bins, desc, nodes, (int)node_jobs_.size(), psi, v, n_, st, true);
         });
         if (n_ <= kDescendNodes) {
             stage(QC_STAGE_GGD, [&] { return launch_descend((int)tie_mode, desc, nodes, 1, 0, S_, labels, n_, n_, st); });
