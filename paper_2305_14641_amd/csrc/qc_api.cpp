@@ -106,16 +106,18 @@ qc_status upload_group(qc_graph g, std::vector<HostSpan> spans)
 qc_status push_desc(qc_graph g, hipStream_t st)
 {
     // What the device already holds, written earlier on the same stream, is
-    // not written again. A write recorded into a HIP graph takes place at
-    // every replay, so a handle that has one always writes.
+    // not written again. A call that is recorded into a HIP graph records its
+    // own write, whatever the device holds now: the write takes place at
+    // every replay, after calls in between may have changed the descriptor
+    // (and so a handle with a recorded write always writes).
     const GraphDev d = g->desc();
-    if (g->desc_pushed && !g->desc_captured && g->desc_stream == st && memcmp(&d, &g->desc_last, sizeof d) == 0)
-        return QC_OK;
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
         (void)hipGetLastError();
         g->desc_captured = true;
     }
+    if (g->desc_pushed && !g->desc_captured && g->desc_stream == st && memcmp(&d, &g->desc_last, sizeof d) == 0)
+        return QC_OK;
     g->desc_pushed = false;
     QC_HIP(launch_set_desc(g->d_desc, d, st));
     g->desc_last = d;
