@@ -103,6 +103,15 @@ qc_status upload_group(qc_graph g, std::vector<HostSpan> spans)
     return QC_OK;
 }
 
+// Whether st is being captured into a HIP graph (or cannot be asked now).
+static bool capturing(hipStream_t st)
+{
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone) return false;
+    (void)hipGetLastError();
+    return true;
+}
+
 qc_status push_desc(qc_graph g, hipStream_t st)
 {
     // What the device already holds, written earlier on the same stream, is
@@ -111,11 +120,7 @@ qc_status push_desc(qc_graph g, hipStream_t st)
     // every replay, after calls in between may have changed the descriptor
     // (and so a handle with a recorded write always writes).
     const GraphDev d = g->desc();
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
-        (void)hipGetLastError();
-        g->desc_captured = true;
-    }
+    if (capturing(st)) g->desc_captured = true;
     if (g->desc_pushed && !g->desc_captured && g->desc_stream == st && memcmp(&d, &g->desc_last, sizeof d) == 0)
         return QC_OK;
     g->desc_pushed = false;
@@ -325,14 +330,25 @@ qc_status run_distances(qc_graph g, hipStream_t st)
     // 521). Nor for weighted edges, whose searches have as many levels
     // through nodes of two neighbours (219 nodes of weights up to 5: 72 us
     // against 57, 2,000: 104 against 101, 4,001: 201 against 203).
-    if (!g->bump_base && !g->directed && can_count(g)) {
+    //
+    // A call that is captured into a HIP graph cannot build tables. Where an
+    // earlier potential (or a batch) learnt the largest distance without
+    // them, it takes the matrix search with the plan the handle was made with
+    // (for a bound on every distance), and the histograms that this one's
+    // pass would need job tables for from the counting search.
+    const bool captured = g->dmax >= 0 && capturing(st);
+    const bool by_rows = !g->bump_base && !g->directed && can_count(g) && (g->drows.ready || !captured);
+    if (by_rows) {
         if (g->dmax < 0) QC_TRY(run_counts(g, st));
         QC_TRY(ensure_dist_rows(g));
         if (g->drows.planes) return run_dist_rows(g, st);
     }
-    if (g->dmax >= 0 && !g->plan_exact) {
+    const bool no_tables = captured && !g->d_hist_jobs && can_count(g);
+    // (the recorded graph reads the plan's tables, so that plan stays)
+    if (no_tables) g->plan_exact = true;
+    if (g->dmax >= 0 && !no_tables) {
         // the counting search learnt dmax: the plan (and histogram jobs) it gives
-        QC_TRY(set_plan(g, plan_bfs(g->n_bfs, g->dmax_bfs)));
+        if (!g->plan_exact) QC_TRY(set_plan(g, plan_bfs(g->n_bfs, g->dmax_bfs)));
         QC_TRY(ensure_hist_jobs(g));
         g->plan_exact = true;
     }
@@ -345,6 +361,7 @@ qc_status run_distances(qc_graph g, hipStream_t st)
                           g->plan.shape | (g->weighted ? kBfsWeighted : 0), g->d_desc,
                           g->d_bfs_jobs, g->plan.n_batches, st));
     }
+    if (no_tables) return run_counts(g, st);
     const bool first = g->dmax < 0;
     if (first) {
         int32_t status[2];
@@ -821,7 +838,15 @@ qc_status qc_distances(qc_graph g, int8_t *dist_out, int32_t *dmax_out, void *st
         g->d_dist = dist_out;
         g->d_ld = g->n;
     } else {
-        if (!g->d_dist_owned) QC_TRY(galloc(g, &g->d_dist_owned, (size_t)(g->n * owned_ld(g->n) + 16)));
+        if (!g->d_dist_owned) {
+            // (a captured call may allocate: this thread's allocations are
+            // none of the capture's business)
+            hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+            QC_HIP(hipThreadExchangeStreamCaptureMode(&mode));
+            const qc_status s = galloc(g, &g->d_dist_owned, (size_t)(g->n * owned_ld(g->n) + 16));
+            QC_HIP(hipThreadExchangeStreamCaptureMode(&mode));
+            QC_TRY(s);
+        }
         g->d_dist = g->d_dist_owned;
         g->d_ld = owned_ld(g->n);
     }

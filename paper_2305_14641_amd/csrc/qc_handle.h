@@ -86,7 +86,7 @@ struct qc_graph_s {
     int K = 0;
     int32_t dmax = -1;
     int32_t dist_bound = -1;          // a bound on every distance (host sweeps; -1: none)
-    bool plan_exact = false;          // `plan` was made for the known largest distance
+    bool plan_exact = false;          // `plan` is final (made for the known largest distance, or recorded in a HIP graph)
     int32_t dmax_bfs = -1;            // largest level of the search (>= dmax when weighted)
     bool have_dist = false;
 

@@ -52,3 +52,54 @@ def test_replayed_distances_go_where_they_were_recorded(name):
     G.close()
     if name == "undirected":
         np.testing.assert_array_equal(want, oracle.distances(g.n, g.row_ptr, g.col)[0])
+
+
+FIRST = {"potential": lambda qc, G: G.potential([1.0]), "batch": lambda qc, G: qc.Batch([G], [1.0])}
+
+
+@pytest.mark.parametrize("resident", [False, True], ids=["into", "resident"])
+@pytest.mark.parametrize("first", list(FIRST))
+@pytest.mark.parametrize("name", ["undirected", "directed", "long"])
+def test_distances_recorded_before_they_ever_ran(name, first, resident):
+    """A potential (or a batch) alone has learnt the largest distance: the
+    distances can be recorded, and the recorded call outlives ordinary ones."""
+    import torch
+    from paper_2305_14641_amd import qc
+    if name == "long":      # no shape of the row-writing search holds it
+        i = np.arange(12600)
+        rp, col = gg.csr_from_edges(12600, np.concatenate([i, i]),
+                                    np.concatenate([(i + 1) % 12600, (i + 120) % 12600]))
+        G = qc.Graph(12600, rp, col)
+        n = 12600
+    else:
+        g, G = handle(name, qc)
+        n = g.n
+    print(f"[gpu] capture first {name} n={n} {first} resident={resident}", flush=True)
+    a = torch.full((n, n), 99, dtype=torch.int8, device="cuda")
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(s):
+        kept = FIRST[first](qc, G)   # noqa: F841
+        h0 = G.histograms()
+        s.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=s):
+            G.distances(None if resident else a)
+        graph.replay()
+        s.synchronize()
+        assert torch.equal(G.histograms(), h0)
+        b = torch.full_like(a, 98)
+        for k in range(2):
+            G.distances(b)           # (tables and plans of its own)
+            a.fill_(99)
+            graph.replay()
+            s.synchronize()
+            if not resident:
+                assert torch.equal(a, b)
+            assert torch.equal(G.histograms(), h0)
+        counts = torch.stack([(b[:64] == k).sum(1) for k in range(h0.shape[1])], 1).int()
+        assert torch.equal(counts, h0[:64])
+        s.synchronize()
+    if hasattr(kept, "close"):
+        kept.close()
+    G.close()
