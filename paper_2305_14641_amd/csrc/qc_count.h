@@ -703,9 +703,22 @@ __global__ __launch_bounds__(KT, KT == 1024 && NQ <= 2 && P == 0 ? 8 : 4) void k
     if (wave == 0) {
         if (lane < nb)
             for (int k = max(last, 1) + 1; k < K; ++k) hist[k] = 0;
+        // A source's leaves are not searched from and lie one further from what
+        // the source reaches last; counted here where that passes the rows' (or
+        // the library's) last distance, so that the status is final before
+        // anything reads the histograms.
+        int far = last;
+        if (last == K - 1 || last == kMaxDist) {
+            bool further = false;
+            if (lane < nb && last < K) {
+                const uint32_t z = src[lane].z;
+                further = (z & 0xFFFFu) > (z >> 16) && hist[last] != 0;
+            }
+            if (__ballot(further)) far = last + 1;
+        }
         if (lane == 0) {
-            atomicMax(&G.status[0], last);
-            if (overflow) atomicOr(&G.status[1], 1);
+            atomicMax(&G.status[0], far);
+            if (overflow || far > kMaxDist) atomicOr(&G.status[1], 1);
         }
         if (G.visits) {
             // the search's work, as the levels cover it: every entry per

@@ -152,6 +152,11 @@ struct GraphDev {
     RowsDev rows;             // the counting search's tables
 };
 
+// Whether the counting search that has just run found distances that the
+// histogram rows or an int8 can't hold (its caller then runs it again or
+// reports an error). Final once the search has ended.
+__device__ inline bool too_long(const GraphDev &G) { return G.status[0] >= G.K || (G.status[1] & 1); }
+
 // graph index, first source, and the number of (source, node) pairs the
 // batch's sources can reach (sum of their component sizes): the search stops
 // as soon as that many pairs have been found.
@@ -248,7 +253,9 @@ int hist_waves(int K, int variant);
 // Optional caller outputs: out[out_off + s*out_ld + (i - i0_of_graph)].
 // `derive` (FP64ACC, after a counting search whose G.rows.rest has one entry
 // per node: 0, or its kind << 16 | a leaf's neighbour): the rows of the nodes
-// that the search leaves out are derived on the way, not read.
+// that the search leaves out are derived on the way, not read; and nothing is
+// written when the search found distances that the rows (or the library)
+// can't hold (too_long).
 constexpr uint32_t kRestLeaf = 1, kRestPair = 2, kRestAlone = 3;
 hipError_t launch_potential(int precision, int K, const GraphDev *graphs, const NodeJob *jobs,
                             int n_jobs, float *psi_out, float *v_out, int64_t out_ld,
@@ -260,21 +267,23 @@ hipError_t launch_ggd_parent(int tie_mode, const GraphDev *graphs, const NodeJob
 
 // Pointer jumping, one workgroup per (graph job, sigma); labels of sigma
 // sigma_base + y go to labels_base + y*labels_ld + job.out_off. The rounds run
-// in LDS, or in global memory where `variant` is 1.
+// in LDS, or in global memory where `variant` is 1. `guard` (LDS): nothing is
+// written after a search whose distances were too long (too_long).
 hipError_t launch_pointer_jump(const GraphDev *graphs, const NodeJob *jobs, int n_jobs,
                                int sigma_base, int n_sig, int32_t *labels_base,
-                               int64_t labels_ld, hipStream_t stream, int variant = 0);
+                               int64_t labels_ld, hipStream_t stream, int variant = 0, bool guard = false);
 
 // Descent and pointer jumping of (graph job, sigma) pairs in one launch, each
 // in one workgroup's LDS (qc_descend.hip): graphs of at most kDescendNodes
 // nodes (4 bytes of V and 2 of parent per node, and the near ties' queues,
 // fill the 160 KB); labels as launch_pointer_jump. Two workgroups fit a CU up
 // to kDescendHalfNodes. Near ties are added to the graph's recheck counter, or
-// stored there with `store_count` (one job and one sigma only).
+// stored there with `store_count` (one job and one sigma only). `guard` as
+// launch_pointer_jump.
 constexpr int kDescendNodes = 26560, kDescendHalfNodes = 12864;
 hipError_t launch_descend(int tie_mode, const GraphDev *graphs, const NodeJob *jobs, int n_jobs, int sigma_base,
                           int n_sig, int32_t *labels_base, int64_t labels_ld, int max_n, hipStream_t stream,
-                          bool store_count = false);
+                          bool store_count = false, bool guard = false);
 
 // Stage timing (qc_timing.cpp): Timer brackets one launch when enabled.
 class StageTimer {

@@ -125,7 +125,8 @@ qc_status OneCall::run(char *base, size_t limit, uint32_t tie_mode, float *psi_o
     std::vector<char> image;
     // Rows of 32 bins hold all but unusually long graphs; the search reports
     // the largest distance, and a longer one repeats the call with rows that
-    // hold it.
+    // hold it. (The outputs are written by the run whose rows do: an error
+    // finds them as they were.)
     for (int bins = 32;;) {
         if (lay_out(bins) > limit) return QC_E_TOO_LARGE;
         // (this layout's addresses: longer rows move everything behind them)
@@ -198,12 +199,14 @@ qc_status OneCall::run(char *base, size_t limit, uint32_t tie_mode, float *psi_o
             return launch_potential(QC_PREC_FP64ACC, bins, desc, nodes, (int)node_jobs_.size(), psi, v, n_, st, true);
         });
         if (n_ <= kDescendNodes) {
-            stage(QC_STAGE_GGD, [&] { return launch_descend((int)tie_mode, desc, nodes, 1, 0, S_, labels, n_, n_, st); });
+            stage(QC_STAGE_GGD, [&] {
+                return launch_descend((int)tie_mode, desc, nodes, 1, 0, S_, labels, n_, n_, st, false, true);
+            });
         } else {
             stage(QC_STAGE_GGD, [&] {
                 return launch_ggd_parent((int)tie_mode, desc, nodes, (int)node_jobs_.size(), 0, S_, st);
             });
-            stage(QC_STAGE_JUMP, [&] { return launch_pointer_jump(desc, nodes, 1, 0, S_, labels, n_, st); });
+            stage(QC_STAGE_JUMP, [&] { return launch_pointer_jump(desc, nodes, 1, 0, S_, labels, n_, st, 0, true); });
         }
         int32_t status[2] = {0, 0};
         if (e == hipSuccess) e = hipMemcpyAsync(status, at(kStatus), sizeof status, hipMemcpyDeviceToHost, st);
