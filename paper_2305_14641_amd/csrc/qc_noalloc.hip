@@ -86,7 +86,10 @@ qc_status cluster_counts(int32_t n, int64_t nnz, const int32_t *row_ptr, const i
     for (const int bins : {32, 128}) {
         char *base = nullptr;
         QC_TRY(dalloc(&base, call.bytes(bins)));
-        const qc_status s = call.run(base, call.bytes(bins), tie_mode, psi_out, v_out, labels_out, st, nullptr);
+        // (the buffer goes back also when the host runs out of memory)
+        const qc_status s = guarded([&] {
+            return call.run(base, call.bytes(bins), tie_mode, psi_out, v_out, labels_out, st, nullptr);
+        });
         dfree(base);
         if (s != QC_E_TOO_LARGE) return s;
     }
