@@ -551,8 +551,9 @@ qc_status all_labels(qc_graph g, uint32_t tie_mode, int32_t *labels_out, hipStre
 qc_status some_labels(qc_graph g, int32_t first, int32_t count, uint32_t tie_mode, int32_t *labels_out, hipStream_t st)
 {
     // (the descent of a single pair stores the count itself)
-    if (g->n > kDescendNodes || count > 1) QC_HIP(launch_fill_u64(g->d_recheck, 1, st));
-    if (g->n <= kDescendNodes) {
+    const bool in_lds = descends_in_lds(g->n, g->nnz, g->max_degree, count);
+    if (!in_lds || count > 1) QC_HIP(launch_fill_u64(g->d_recheck, 1, st));
+    if (in_lds) {
         StageTimer t(QC_STAGE_GGD, st);
         QC_HIP(launch_descend((int)tie_mode, g->d_desc, g->d_node_jobs, 1, first, count, labels_out, g->n, g->n, st,
                               count == 1));
@@ -726,6 +727,7 @@ qc_status create_graph(int32_t n, int64_t nnz, const int32_t *row_ptr, const int
     const Descent descent = build_descent(n, rp, col);
     const std::vector<int32_t> &order = descent.order, &sell_off = descent.off, &sell_deg = descent.deg;
     const std::vector<uint32_t> &sell_col = descent.col;
+    g->max_degree = descent.max_degree;
     // BFS sources by estimated eccentricity (undirected graphs; a directed
     // graph keeps its node order, and so does a serving request: its one
     // search would not repay the host sweeps). QC_SOURCE_ORDER=identity keeps

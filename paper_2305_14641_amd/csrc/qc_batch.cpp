@@ -767,11 +767,30 @@ qc_status qc_batch_create(const qc_graph *graphs, int32_t n_graphs, const double
             }
         }
         if (!rest) return QC_OK;
+        // Which graphs descend in one workgroup per sigma: those for which
+        // that takes less than through global memory, or no longer than the
+        // pairs' turns on the chip in all.
+        std::vector<uint8_t> in_lds(n_graphs, 0);
+        {
+            double nodes = 0.0, turns = 0.0;
+            for (int gi : gis) {
+                const qc_graph g = graphs[gi];
+                if (g->n > kDescendNodes) continue;
+                nodes += (double)g->n * n_sigmas;
+                turns += descend_us(g->n, g->nnz) * n_sigmas / (g->n <= kDescendHalfNodes ? 2 * kCus : kCus);
+            }
+            for (int gi : gis) {
+                const qc_graph g = graphs[gi];
+                in_lds[gi] = g->n <= kDescendNodes &&
+                             descend_us(g->n, g->nnz) <=
+                                 std::max(turns, descend_far_us(g->n, g->max_degree, n_sigmas, nodes));
+            }
+        }
         for (int k = 0; k < 2; ++k) {
             std::vector<int> in;
             std::vector<qc_graph> gv;
             for (int gi : gis)
-                if (k || graphs[gi]->n > kDescendNodes) {
+                if (k || !in_lds[gi]) {
                     in.push_back(gi);
                     gv.push_back(graphs[gi]);
                 }
@@ -800,7 +819,7 @@ qc_status qc_batch_create(const qc_graph *graphs, int32_t n_graphs, const double
             int most = 0;
             for (int gi : by_size) {
                 const int n = graphs[gi]->n;
-                if (n > kDescendNodes || (n > kDescendHalfNodes) != large) continue;
+                if (!in_lds[gi] || (n > kDescendHalfNodes) != large) continue;
                 dj.push_back(NodeJob{gi, 0, b->offsets[gi]});
                 most = std::max(most, n);
             }

@@ -49,6 +49,7 @@ struct qc_graph_s {
     int32_t n = 0;
     int64_t nnz = 0;
     int32_t n_components = 0;
+    int32_t max_degree = 0;
     std::vector<int32_t> row_ptr, col;   // the canonical CSR (host copy)
     bool directed = false;
     std::vector<int32_t> comp_size;   // size of each node's component (host)

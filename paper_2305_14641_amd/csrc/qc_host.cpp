@@ -355,6 +355,7 @@ Descent build_descent(int32_t n, const std::vector<int32_t> &rp, const std::vect
         for (int32_t k = 0; k <= top; ++k) start[k + 1] += start[k];
         for (int32_t v = i0; v < i1; ++v) d.order[i0 + start[top - degree(v)]++] = v;
     }
+    d.max_degree = most;
     const int32_t n_slices = (n + 63) / 64;
     d.off.assign(n_slices + 1, 0);
     d.deg.resize(n);
@@ -374,6 +375,21 @@ Descent build_descent(int32_t n, const std::vector<int32_t> &rp, const std::vect
             to[(size_t)32 * k] = (uint32_t)from[k] | (k + 1 < deg ? (uint32_t)from[k + 1] : none) << 16;
     }
     return d;
+}
+
+double descend_us(int32_t n, int64_t nnz) { return 6.0 + 0.0008 * n + 0.0004 * (double)nnz; }
+
+double descend_far_us(int32_t n, int32_t max_degree, int n_sig, double pair_nodes)
+{
+    return 11.5 + 0.0007 * n + (n_sig < kGgdSigmas ? 0.18 : 0.5) * max_degree + 2e-5 * pair_nodes;
+}
+
+bool descends_in_lds(int32_t n, int64_t nnz, int32_t max_degree, int n_sig)
+{
+    // (more pairs than CUs take turns)
+    const double one = descend_us(n, nnz);
+    const double turns = std::max(1.0, n_sig / (double)(n <= kDescendHalfNodes ? 2 * kCus : kCus));
+    return n <= kDescendNodes && one * turns <= descend_far_us(n, max_degree, n_sig, (double)n * n_sig);
 }
 
 int planes_for(int32_t dmax)
@@ -492,7 +508,7 @@ BfsPlan plan_bfs_from(int32_t n, int32_t dmax, int32_t n_src)
     // 113 us, 3,500: 103 against 108), nor from fewer than six words per
     // thread, where the edges and the levels' barriers are what a batch costs
     // (500 nodes, two words: 57 against 59).
-    constexpr int kCus = 256, kManyWords = 6;
+    constexpr int kManyWords = 6;
     BfsPlan p = plan_bfs(n, dmax);
     if (getenv("QC_BFS_SHAPE") || p.shape == kBfsFront || p.nw < kManyWords) return p;
     for (int bw = p.bw / 2; bw >= 8 && (n_src + bw - 1) / bw <= kCus; bw /= 2) {

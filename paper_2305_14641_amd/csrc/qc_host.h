@@ -73,8 +73,26 @@ std::vector<int32_t> source_order(int32_t n, const std::vector<int32_t> &rp,
 struct Descent {
     std::vector<int32_t> order, off, deg;
     std::vector<uint32_t> col;
+    int32_t max_degree = 0;
 };
 Descent build_descent(int32_t n, const std::vector<int32_t> &rp, const std::vector<int32_t> &col);
+
+// Estimated microseconds of one (graph, sigma) pair's descent in one
+// workgroup (launch_descend), and of `n_sig` sigmas' through global memory
+// (launch_ggd_parent and launch_pointer_jump) beside `pair_nodes` nodes of
+// pairs in all. One workgroup is one CU's LDS, so it pays for every entry;
+// the other form spreads the lists over the chip, one thread each, waits for
+// the longest of them (four sigmas at a time from n_sig = 4 on) and pays for
+// its launches. Fitted between widths that tie many nodes and widths that tie
+// none (one sigma, tied: 2,000 nodes of 5 neighbours 14 against 18 us, 8,000:
+// 29 against 22, 20,000: 60 against 30; of 60 neighbours 500: 23 against 33,
+// 5,000: 141 against 41; 20,000 with a hub of 422: 104 against 119; a complete
+// graph of 256: 58 against 77, of 1,000: 757 against 294; 8 such graphs of
+// 8,000 nodes x 32 sigmas 33 against 62).
+double descend_us(int32_t n, int64_t nnz);
+double descend_far_us(int32_t n, int32_t max_degree, int n_sig, double pair_nodes);
+// Whether `n_sig` sigmas of one graph descend in one workgroup each.
+bool descends_in_lds(int32_t n, int64_t nnz, int32_t max_degree, int n_sig);
 
 // Integer edge weights (Section 3.1: a path's length is the sum of its edges'
 // weights): an edge of weight w >= 2 becomes a path of w unit edges through

@@ -16,6 +16,8 @@ constexpr int kMaxNodes = 65536;
 // the packed edge list the BFS streams then spans less than 2 GB, within the
 // 32-bit byte offsets of its buffer loads.
 constexpr int64_t kMaxEdges = (int64_t)1 << 29;
+// Compute units of the chip.
+constexpr int kCus = 256;
 // Threads per workgroup of the multi-source BFS: the three-field shape (and
 // the 1024-thread two-field one) and the 512-thread two-field ("wide") shape.
 constexpr int kBfsThreads = 1024;

@@ -1,6 +1,7 @@
 // Algorithm 4 in one call (see qc_onecall.h): one host-to-device copy of all
 // tables, three launches (search; potentials with the rows it leaves out; descent
-// and pointer jumping of every width, two above kDescendNodes), one 8-byte copy back.
+// and pointer jumping of every width, two where descends_in_lds says so), one
+// 8-byte copy back.
 #include "qc_onecall.h"
 
 #include <math.h>
@@ -198,7 +199,7 @@ qc_status OneCall::run(char *base, size_t limit, uint32_t tie_mode, float *psi_o
         stage(QC_STAGE_POTENTIAL, [&] {
             return launch_potential(QC_PREC_FP64ACC, bins, desc, nodes, (int)node_jobs_.size(), psi, v, n_, st, true);
         });
-        if (n_ <= kDescendNodes) {
+        if (descends_in_lds(n_, nnz_, descent_.max_degree, S_)) {
             stage(QC_STAGE_GGD, [&] {
                 return launch_descend((int)tie_mode, desc, nodes, 1, 0, S_, labels, n_, n_, st, false, true);
             });
