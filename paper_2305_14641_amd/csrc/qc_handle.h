@@ -27,13 +27,9 @@ struct RowsState {
     std::vector<uint16_t> pos;        // position of every core node
     std::vector<uint32_t> first;      // its entries in col_pos
     int planes = 0, nqn = 0;          // distance rows (RowsDistPlan); 0: histograms only
-    qc::RowsDev dev{};                // pointers to the buffers below
+    char *d_base = nullptr;           // every table below, in one buffer
+    qc::RowsDev dev{};                // pointers into it
     uint32_t *d_src = nullptr;        // [4 n_search]
-    uint16_t *d_col_pos = nullptr, *d_ent = nullptr, *d_leaf = nullptr;
-    uint32_t *d_codes = nullptr, *d_units = nullptr, *d_wave_row = nullptr, *d_wave_unit = nullptr;
-    uint32_t *d_rest = nullptr;
-    uint16_t *d_node_pos = nullptr;
-    uint32_t *d_node_flags = nullptr;
     BfsJob *d_jobs = nullptr;
     int n_jobs = 0;
     NodeJob *d_rest_jobs = nullptr;
@@ -271,12 +267,12 @@ HostSpan span_of(T *dst, const std::vector<T> &src)
 {
     return HostSpan{(void *)dst, (const void *)src.data(), src.size() * sizeof(T)};
 }
-// Upload several host arrays (set-up only). In a handle's arena region,
-// small arrays whose buffers follow one another (separated only by the
-// region's 256-byte alignment padding, which no buffer uses) go as one copy
-// from a staging buffer; large arrays, and every array outside a region,
-// are copies of their own.
-qc_status upload_group(qc_graph g, std::vector<HostSpan> spans);
+// Upload several host arrays (set-up only). In a handle's arena region, or
+// where all lie in `one_buffer`, small arrays whose buffers follow one another
+// (separated only by 256-byte alignment padding, which nothing uses) go as one
+// copy from a staging buffer; large arrays, and every array elsewhere, are
+// copies of their own.
+qc_status upload_group(qc_graph g, std::vector<HostSpan> spans, bool one_buffer = false);
 
 inline hipStream_t as_stream(void *s) { return (hipStream_t)s; }
 

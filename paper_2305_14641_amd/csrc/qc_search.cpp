@@ -29,19 +29,10 @@ static std::vector<uint32_t> source_table(qc_graph g, const RowsState &r)
 
 void free_rows(qc_graph g, RowsState &r)
 {
-    gfree(g, r.d_src);
-    gfree(g, r.d_col_pos);
-    gfree(g, r.d_codes);
-    gfree(g, r.d_wave_row);
-    gfree(g, r.d_wave_unit);
-    gfree(g, r.d_ent);
-    gfree(g, r.d_units);
-    gfree(g, r.d_leaf);
-    gfree(g, r.d_rest);
-    gfree(g, r.d_node_pos);
-    gfree(g, r.d_node_flags);
-    gfree(g, r.d_jobs);
-    gfree(g, r.d_rest_jobs);
+    gfree(g, r.d_base);
+    r.d_src = nullptr;
+    r.d_jobs = nullptr;
+    r.d_rest_jobs = nullptr;
     r.dev = RowsDev{};
     r.ready = false;
 }
@@ -107,40 +98,43 @@ static qc_status make_rows(qc_graph g, RowsState &r, bool dist)
     for (int s0 = (n_core + bw - 1) / bw * bw - bw; s0 >= 0; s0 -= bw) jobs.push_back(BfsJob{0, s0, 0u, 0u});
     std::vector<NodeJob> rjobs;
     for (int i = 0; i < r.dev.n_rest; i += 32) rjobs.push_back(NodeJob{0, i, 0});
-    qc_status s = galloc(g, &r.d_src, src.size());
-    if (s == QC_OK) s = galloc(g, &r.d_col_pos, t.col_pos.size());
-    if (s == QC_OK) s = galloc(g, &r.d_codes, t.codes.size());
-    if (s == QC_OK) s = galloc(g, &r.d_wave_row, t.wave_row.size());
-    if (s == QC_OK) s = galloc(g, &r.d_wave_unit, t.wave_unit.size());
-    if (s == QC_OK) s = galloc(g, &r.d_ent, t.ent.size());
-    if (s == QC_OK) s = galloc(g, &r.d_units, t.units.size());
-    if (s == QC_OK) s = galloc(g, &r.d_leaf, t.leaf.size());
-    if (s == QC_OK) s = galloc(g, &r.d_rest, rest.size());
-    if (s == QC_OK) s = galloc(g, &r.d_jobs, jobs.size());
-    if (s == QC_OK) s = galloc(g, &r.d_rest_jobs, rjobs.size());
-    if (s == QC_OK && dist) s = galloc(g, &r.d_node_pos, node_pos.size());
-    if (s == QC_OK && dist) s = galloc(g, &r.d_node_flags, node_flags.size());
-    if (s == QC_OK)
-        s = upload_group(g, {span_of(r.d_src, src), span_of(r.d_col_pos, t.col_pos), span_of(r.d_codes, t.codes),
-                             span_of(r.d_wave_row, t.wave_row), span_of(r.d_wave_unit, t.wave_unit),
-                             span_of(r.d_ent, t.ent), span_of(r.d_units, t.units), span_of(r.d_leaf, t.leaf),
-                             span_of(r.d_rest, rest), span_of(r.d_jobs, jobs), span_of(r.d_rest_jobs, rjobs),
-                             span_of(r.d_node_pos, node_pos), span_of(r.d_node_flags, node_flags)});
+    // one buffer and few copies: on a small graph each allocation and each
+    // copy cost as much as the search (a 10-node graph's first distances
+    // 593 us with 26 of both)
+    size_t bytes = 0;
+    std::vector<HostSpan> spans;
+    auto place = [&](const auto &v) {
+        const size_t at = bytes, size = v.size() * sizeof(v[0]);
+        spans.push_back(HostSpan{(void *)at, (const void *)v.data(), size});
+        bytes += (std::max<size_t>(size, 1) + 255) & ~(size_t)255;
+        return at;
+    };
+    const size_t at_src = place(src), at_col_pos = place(t.col_pos), at_codes = place(t.codes),
+                 at_wave_row = place(t.wave_row), at_wave_unit = place(t.wave_unit), at_leaf = place(t.leaf),
+                 at_rest = place(rest), at_jobs = place(jobs), at_rest_jobs = place(rjobs),
+                 at_node_pos = place(node_pos), at_node_flags = place(node_flags), at_units = place(t.units),
+                 at_ent = place(t.ent);
+    QC_TRY(galloc(g, &r.d_base, bytes));
+    for (HostSpan &x : spans) x.dst = r.d_base + (size_t)x.dst;
+    const qc_status s = upload_group(g, spans, true);
     if (s != QC_OK) {
         free_rows(g, r);
         return s;
     }
+    r.d_src = (uint32_t *)(r.d_base + at_src);
+    r.d_jobs = (BfsJob *)(r.d_base + at_jobs);
+    r.d_rest_jobs = (NodeJob *)(r.d_base + at_rest_jobs);
     r.dev.src = r.d_src;
-    r.dev.col_pos = r.d_col_pos;
-    r.dev.codes = r.d_codes;
-    r.dev.wave_row = r.d_wave_row;
-    r.dev.wave_unit = r.d_wave_unit;
-    r.dev.ent = r.d_ent;
-    r.dev.units = r.d_units;
-    r.dev.leaf = r.d_leaf;
-    r.dev.rest = r.d_rest;
-    r.dev.node_pos = r.d_node_pos;
-    r.dev.node_flags = r.d_node_flags;
+    r.dev.col_pos = (const uint16_t *)(r.d_base + at_col_pos);
+    r.dev.codes = (const uint32_t *)(r.d_base + at_codes);
+    r.dev.wave_row = (const uint32_t *)(r.d_base + at_wave_row);
+    r.dev.wave_unit = (const uint32_t *)(r.d_base + at_wave_unit);
+    r.dev.ent = r.d_base + at_ent;
+    r.dev.units = r.d_base + at_units;
+    r.dev.leaf = r.d_base + at_leaf;
+    r.dev.rest = (const uint32_t *)(r.d_base + at_rest);
+    r.dev.node_pos = (const uint16_t *)(r.d_base + at_node_pos);
+    r.dev.node_flags = (const uint32_t *)(r.d_base + at_node_flags);
     r.n_jobs = (int)jobs.size();
     r.n_rest_jobs = (int)rjobs.size();
     r.ready = true;
