@@ -332,7 +332,11 @@ qc_status run_distances(qc_graph g, hipStream_t st)
     // 222 us; undirected, 2,708 nodes: 36 against 43, 19,717: 250 against
     // 521). Nor for weighted edges, whose searches have as many levels
     // through nodes of two neighbours (219 nodes of weights up to 5: 72 us
-    // against 57, 2,000: 104 against 101, 4,001: 201 against 203).
+    // against 57, 2,000: 104 against 101, 4,001: 201 against 203). Nor for
+    // small graphs of many levels, which are all fixed work (a path of 60: 88
+    // us against 68, of 120: 169 against 134; grids of 2 x 60 80 against 69, of
+    // 4 x 100 133 against 122; at 20 x 20 nodes and 38 levels both take 54, and
+    // with fewer levels the rows win, 10 x 10 nodes 26 against 31).
     //
     // A call that is captured into a HIP graph cannot build tables. Where an
     // earlier potential (or a batch) learnt the largest distance without
@@ -340,7 +344,9 @@ qc_status run_distances(qc_graph g, hipStream_t st)
     // (for a bound on every distance), and the histograms that this one's
     // pass would need job tables for from the counting search.
     const bool captured = g->dmax >= 0 && capturing(st);
-    const bool by_rows = !g->bump_base && !g->directed && can_count(g) && (g->drows.ready || !captured);
+    const int levels = g->dmax >= 0 ? g->dmax : g->dist_bound >= 0 ? g->dist_bound : kMaxDist;   // (at most)
+    const bool by_rows = !g->bump_base && !g->directed && can_count(g) && (g->drows.ready || !captured) &&
+                         (g->n > 512 || levels <= std::max(24, g->n / 6));
     if (by_rows) {
         if (g->dmax < 0) QC_TRY(run_counts(g, st));
         QC_TRY(ensure_dist_rows(g));
