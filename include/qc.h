@@ -188,7 +188,7 @@ qc_status qc_get_histograms(qc_graph g, int32_t *hist_out, int32_t *k_out, void 
  *   precision  QC_PREC_* (see above)
  * Searches the distances first if neither qc_distances nor this call has
  * run: their histograms only, without a matrix (with a library-owned one for
- * a graph with integer weights).
+ * a graph with integer weights, or a small one of many levels).
  * The values are kept resident for qc_ggd_labels; `sigma_index` there indexes
  * this list. Relative error of psi and V vs an FP64 evaluation: <= 1e-6 for
  * FP64ACC and FP32C.

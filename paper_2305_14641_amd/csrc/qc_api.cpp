@@ -344,9 +344,8 @@ qc_status run_distances(qc_graph g, hipStream_t st)
     // (for a bound on every distance), and the histograms that this one's
     // pass would need job tables for from the counting search.
     const bool captured = g->dmax >= 0 && capturing(st);
-    const int levels = g->dmax >= 0 ? g->dmax : g->dist_bound >= 0 ? g->dist_bound : kMaxDist;   // (at most)
-    const bool by_rows = !g->bump_base && !g->directed && can_count(g) && (g->drows.ready || !captured) &&
-                         (g->n > 512 || levels <= std::max(24, g->n / 6));
+    const bool by_rows =
+        !g->bump_base && !g->directed && can_count(g) && !small_deep(g) && (g->drows.ready || !captured);
     if (by_rows) {
         if (g->dmax < 0) QC_TRY(run_counts(g, st));
         QC_TRY(ensure_dist_rows(g));
@@ -884,8 +883,11 @@ qc_status qc_potential(qc_graph g, const double *sigmas, int32_t n_sigmas, float
     QC_TRY(validate_sigmas(sigmas, n_sigmas));
     if (precision > QC_PREC_BF16) return QC_E_INVAL;
     hipStream_t st = as_stream(stream);
+    // (a path of 60 nodes: 498 us by the counting search, which learns here that
+    // its rows are too long for it, 400 by the distances)
+    const bool counts = can_count(g) && (g->directed || !small_deep(g));
     if (!g->have_dist)
-        QC_TRY(can_count(g) ? guarded([&] { return run_counts(g, st); }) : qc_distances(g, nullptr, nullptr, stream));
+        QC_TRY(counts ? guarded([&] { return run_counts(g, st); }) : qc_distances(g, nullptr, nullptr, stream));
 
     // until this call has succeeded the handle holds no potentials (the
     // descent refuses to run on a half-made set)

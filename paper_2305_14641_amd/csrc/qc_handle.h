@@ -298,6 +298,9 @@ qc_status run_distances(qc_graph g, hipStream_t st);
 // weights, and no workgroup shape of the matrix search asked for
 // (QC_BFS_SHAPE, a switch for measurements and tests).
 bool can_count(qc_graph g);
+// Whether g is small and has so many levels (as far as is known) that only
+// the fixed work of a level counts, which the matrix search has less of.
+bool small_deep(qc_graph g);
 // Build and upload the counting search's tables (a no-op when they are there).
 qc_status ensure_rows(qc_graph g);
 void free_rows(qc_graph g, RowsState &r);

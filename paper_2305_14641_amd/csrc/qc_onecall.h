@@ -60,7 +60,7 @@ class OneCall {
     std::vector<Part> parts_;
     size_t image_ = 0, total_ = 0;
     size_t hist_ = 0, psi_ = 0, v_ = 0, v64_ = 0, parent_ = 0, out_ = 0;
-    int bins_ = 0;
+    int bins_ = 0, first_bins_ = 32;
     char *results_ = nullptr;
 };
 

@@ -11,6 +11,12 @@ namespace qc {
 
 bool can_count(qc_graph g) { return !g->weighted && !getenv("QC_BFS_SHAPE"); }
 
+bool small_deep(qc_graph g)
+{
+    const int levels = g->dmax >= 0 ? g->dmax : g->dist_bound >= 0 ? g->dist_bound : kMaxDist;   // (at most)
+    return g->n <= 512 && levels > std::max(24, g->n / 6);
+}
+
 // The sources in the handle's order, with what the search needs of each.
 static std::vector<uint32_t> source_table(qc_graph g, const RowsState &r)
 {

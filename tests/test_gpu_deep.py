@@ -46,3 +46,38 @@ def test_distances_of_deep_graphs(g, first):
     p2, v2 = G.potential([0.8, 2.0])
     assert torch.equal(p2, psi) and torch.equal(v2, v)
     G.close()
+
+
+@pytest.mark.parametrize("mixed", [False, True], ids=["deep", "mixed"])
+def test_a_batch_of_deep_graphs(mixed):
+    """Nothing but small deep graphs (the matrix search), and beside others."""
+    import torch
+    from paper_2305_14641_amd import qc
+    graphs = [gg.path_graph(127), gg.path_graph(40), grid(2, 60), gg.path_graph(128 - 1)]
+    if mixed:
+        graphs += [gg.path_graph(9), gg.dcsbm(700, [0.5, 0.5], 4.0, seed=3)]
+    sigmas = [0.6, 1.9]
+    print(f"[gpu] deep batch mixed={mixed}", flush=True)
+    handles = [qc.Graph.from_graph(g) for g in graphs]
+    handles[1].potential([1.0])      # (one has searched before)
+    b = qc.Batch(handles, sigmas)
+    outs = b.outputs()
+    for _ in range(2):
+        b.run(*outs)
+    torch.cuda.synchronize()
+    for i, (g, h) in enumerate(zip(graphs, handles)):
+        dist, dmax = oracle.distances(g.n, g.row_ptr, g.col)
+        hist = oracle.hist_rows(dist, dmax + 1)
+        at = slice(int(b.offsets[i]), int(b.offsets[i + 1]))
+        for k, s in enumerate(sigmas):
+            psi, v = oracle.potential_canonical(hist, s)
+            np.testing.assert_allclose(outs[0][k, at].cpu().numpy(), psi, rtol=1e-6, atol=0)
+            np.testing.assert_allclose(outs[1][k, at].cpu().numpy(), v, rtol=1e-6, atol=0)
+            want = oracle.find_centers(oracle.ggd_parent(g.n, g.row_ptr, g.col, v, 0))
+            np.testing.assert_array_equal(outs[2][k, at].cpu().numpy(), want)
+        d = torch.full((g.n, g.n), 99, dtype=torch.int8, device="cuda")
+        assert h.distances(d) == dmax
+        np.testing.assert_array_equal(d.cpu().numpy(), dist)
+    b.close()
+    for h in handles:
+        h.close()
