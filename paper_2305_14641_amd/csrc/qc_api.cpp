@@ -883,9 +883,10 @@ qc_status qc_potential(qc_graph g, const double *sigmas, int32_t n_sigmas, float
     QC_TRY(validate_sigmas(sigmas, n_sigmas));
     if (precision > QC_PREC_BF16) return QC_E_INVAL;
     hipStream_t st = as_stream(stream);
-    // (a path of 60 nodes: 498 us by the counting search, which learns here that
-    // its rows are too long for it, 400 by the distances)
-    const bool counts = can_count(g) && (g->directed || !small_deep(g));
+    // (a path of 60 nodes: 498 us by the counting search, which finds its rows
+    // too long here, 400 by the distances; a 4 x 100 grid 600 against 912, the
+    // order of its edges for the matrix search among them)
+    const bool counts = can_count(g) && (g->directed || g->n > 256 || !small_deep(g));
     if (!g->have_dist)
         QC_TRY(counts ? guarded([&] { return run_counts(g, st); }) : qc_distances(g, nullptr, nullptr, stream));
 

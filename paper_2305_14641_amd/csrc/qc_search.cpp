@@ -50,11 +50,18 @@ static qc_status make_rows(qc_graph g, RowsState &r, bool dist)
     const std::vector<int32_t> &rp = g->row_ptr, &col = g->col;
     // With the sources in node order (QC_SOURCE_ORDER=identity, a switch for
     // measurements and tests) every node is searched.
+    // So is it for the distance rows of a graph whose batches all find a CU
+    // several times over: a launch for the left-out nodes' rows would wait for
+    // the search (a binary tree of 1,000 nodes 36 -> 28 us, 1,000 nodes with
+    // 117 leaves 25 -> 20, 2,000 with 476 29 -> 26; from 3,000 nodes on it is
+    // the other way round as often). Not where most nodes are left out (a star
+    // of 4,000 leaves 20 -> 24).
     const char *so = getenv("QC_SOURCE_ORDER");
-    if (so && strcmp(so, "identity") == 0)
+    r.kind = rows_kinds(g->n, rp, col, !g->directed);
+    const bool all = dist && g->n <= 2048 &&
+                     2 * std::count(r.kind.begin(), r.kind.end(), (uint8_t)kRowsCore) >= g->n;
+    if (all || (so && strcmp(so, "identity") == 0))
         r.kind.assign(g->n, kRowsCore);
-    else
-        r.kind = rows_kinds(g->n, rp, col, !g->directed);
     const int32_t n_core = (int32_t)std::count(r.kind.begin(), r.kind.end(), (uint8_t)kRowsCore);
     if (dist) {
         const RowsDistPlan p = plan_rows_dist(g->n, n_core, g->dmax);

@@ -18,9 +18,12 @@ def grid(w, h):
 
 
 GRAPHS = [gg.path_graph(n) for n in (1, 2, 24, 25, 26, 27, 33, 64, 65, 127)] + \
-         [grid(2, 60), grid(8, 64), grid(9, 57), grid(6, 80), grid(10, 10), grid(13, 13), grid(20, 20), gg.twin_leaves(12, 30),
+         [grid(2, 60), grid(8, 64), grid(9, 57), grid(6, 80), grid(4, 64), grid(10, 10), grid(13, 13), grid(20, 20), gg.twin_leaves(12, 30),
           gg.disjoint_union(gg.path_graph(40), gg.star_graph(9), gg.empty_graph(2), gg.path_graph(2)),
-          gg.dcsbm(512, [0.5, 0.5], 3.0, seed=1), gg.dcsbm(513, [0.5, 0.5], 3.0, seed=2)]
+          gg.dcsbm(512, [0.5, 0.5], 3.0, seed=1), gg.dcsbm(513, [0.5, 0.5], 3.0, seed=2),
+          # leaves' rows searched like the others' (up to 2,048 nodes, most of them no leaves), or derived
+          gg.dcsbm(2048, [0.5, 0.5], 3.0, seed=3), gg.dcsbm(2049, [0.5, 0.5], 3.0, seed=4), gg.star_graph(60),
+          gg.disjoint_union(gg.complete_graph(9), gg.empty_graph(3), gg.path_graph(2), gg.star_graph(4))]
 
 
 @pytest.mark.parametrize("first", ["distances", "potential"])
