@@ -35,15 +35,22 @@ RowsDistPlan plan_rows_dist(int32_t n, int32_t n_pos, int32_t dmax)
     RowsDistPlan d;
     d.planes = dmax <= 14 ? 4 : dmax <= 30 ? 5 : 7;
     d.rows.threads = 1024;
-    const int32_t need = n_pos < 65536 ? n_pos + 1 : n_pos;
+    // (a graph whose nodes all have positions can fill its shape: build_rows
+    // then lets unused entries gather the row's own bits)
+    const int32_t need = n_pos < n ? n_pos + 1 : n_pos;
     // About 16 words x 4 planes are what the registers hold: larger shapes
-    // spill (qc_dist_*.hip have the same list). What no shape holds stays with
-    // the matrix search (qc_bfs.h), which takes 8 sources at that size.
+    // spill more than they gain (qc_dist_*.hip have the same list). What no
+    // shape holds stays with the matrix search (qc_bfs.h). So do 5 planes above
+    // 16,384 nodes while it takes 32 sources at a time and the row owners only
+    // 16 (nodes of 3 neighbours, 5 planes, 17,000 nodes: 489 against 524 us; but
+    // with 4 planes, 5 neighbours, 345 against 327; at 18,400 nodes 514 against 508,
+    // and above 18,432, both at 16, 951 against 538).
     struct Shape { int nq, per; };
     static const Shape kShapes[] = {{1, 1}, {2, 1}, {3, 1}, {4, 1}, {5, 2}, {6, 2}};
     const int most = d.planes == 4 ? 6 : d.planes == 5 ? 5 : 2;
     for (const Shape &x : kShapes) {
         if (x.nq > most) break;
+        if (d.planes == 5 && x.per > 1 && n <= 18200) break;
         if (need > x.nq * 4096) continue;
         for (int nqn = x.nq; nqn <= x.nq + 1; ++nqn)
             if (n <= nqn * 4096) {
