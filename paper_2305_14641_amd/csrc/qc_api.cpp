@@ -344,8 +344,8 @@ qc_status run_distances(qc_graph g, hipStream_t st)
     // (for a bound on every distance), and the histograms that this one's
     // pass would need job tables for from the counting search.
     const bool captured = g->dmax >= 0 && capturing(st);
-    const bool by_rows =
-        !g->bump_base && !g->directed && can_count(g) && !small_deep(g) && (g->drows.ready || !captured);
+    const bool by_rows = !g->bump_base && !g->directed && can_count(g) && !small_deep(g) &&
+                         (g->drows.ready || !captured) && (g->dmax >= 0 || may_have_rows(g));
     if (by_rows) {
         if (g->dmax < 0) QC_TRY(run_counts(g, st));
         QC_TRY(ensure_dist_rows(g));

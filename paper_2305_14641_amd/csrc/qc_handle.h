@@ -304,6 +304,11 @@ bool small_deep(qc_graph g);
 // Build and upload the counting search's tables (a no-op when they are there).
 qc_status ensure_rows(qc_graph g);
 void free_rows(qc_graph g, RowsState &r);
+// Whether, before the largest distance is known, some shape of the search
+// that writes distance rows may hold g (else the counting search that would
+// learn that distance, and its tables, are spared: 12,000 nodes of 110 levels
+// 12.0 -> 11.1 ms of first distances).
+bool may_have_rows(qc_graph g);
 // The tables of the search that writes distance rows; r.planes stays 0 when
 // no shape holds the graph (the matrix search of qc_bfs.h takes it).
 qc_status ensure_dist_rows(qc_graph g);

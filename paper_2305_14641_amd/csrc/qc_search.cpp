@@ -17,6 +17,17 @@ bool small_deep(qc_graph g)
     return g->n <= 512 && levels > std::max(24, g->n / 6);
 }
 
+bool may_have_rows(qc_graph g)
+{
+    // the sweeps' bound is at most twice the largest distance (and above 126
+    // where it is none); nodes of one neighbour at most may need no position
+    if (!g->ecc_order) return true;
+    const int least = (g->dist_bound >= 0 ? g->dist_bound + 1 : kMaxDist + 2) / 2;
+    int32_t n_core = 0;
+    for (int32_t v = 0; v < g->n; ++v) n_core += g->row_ptr[v + 1] - g->row_ptr[v] > 1;
+    return plan_rows_dist(g->n, n_core, least).rows.nq > 0;
+}
+
 // The sources in the handle's order, with what the search needs of each.
 static std::vector<uint32_t> source_table(qc_graph g, const RowsState &r)
 {
