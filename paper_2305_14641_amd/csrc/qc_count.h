@@ -160,7 +160,7 @@ __device__ __forceinline__ void transpose_bytes(uint32_t (&a)[8])
 // too, from P bit-planes of the level in registers (levels up to 2^P - 2;
 // all ones: not reached), NQN quads of consecutive nodes per lane. The small
 // counting shapes are held to 64 registers, so that two workgroups of 1,024
-// threads share a CU (two quads: 11 registers go to scratch; 79,000 sources of
+// threads share a CU (two quads: 6 registers go to scratch; 79,000 sources of
 // 4,000 to 8,000 nodes 567 -> 471 us, the step above 1.63 -> 1.58 ms).
 template <int NQ, int KT, int PER, int P, int NQN>
 __global__ __launch_bounds__(KT, KT == 1024 && NQ <= 2 && P == 0 ? 8 : 4) void k_count(
@@ -191,6 +191,7 @@ __global__ __launch_bounds__(KT, KT == 1024 && NQ <= 2 && P == 0 ? 8 : 4) void k
     __shared__ __attribute__((aligned(16))) uint32_t hacc[HUB];
     __shared__ uint32_t hdone[HUB / 32];
     __shared__ uint32_t cnt[3][16];   // counts of a level
+    __shared__ int batch[2];          // sources, and the first one's place
 
     const BfsJob job = jobs[blockIdx.x];
     const GraphDev &G = graphs[job.g];
@@ -218,6 +219,10 @@ __global__ __launch_bounds__(KT, KT == 1024 && NQ <= 2 && P == 0 ? 8 : 4) void k
     for (int i = tid; i < HUB; i += KT) hacc[i] = 0u;
     for (int i = tid; i < HUB / 32; i += KT) hdone[i] = 0u;
     if (tid < 48) cnt[tid / 16][tid % 16] = 0u;
+    if (tid == 0) {
+        batch[0] = nb;
+        batch[1] = job.s0;
+    }
     __syncthreads();
     if (tid < nb) put(src[tid].x >> 16, tid);   // level 0: the sources
     __syncthreads();
@@ -301,8 +306,14 @@ __global__ __launch_bounds__(KT, KT == 1024 && NQ <= 2 && P == 0 ? 8 : 4) void k
     const uint32_t voff = (uint32_t)lane * 16u;
     // The graph's descriptor through an address the compiler cannot see
     // through: what a level reads of it is loaded again (scalar loads) instead
-    // of being held in scalar registers, which have no room for all of it
-    // (instances whose scalar registers spilled by the hundred lost counts).
+    // of being held in scalar registers, which have no room for all of it. An
+    // instance of 16 quads with 101 scalar registers spilled (to lanes of two
+    // vector registers) and 37 vector ones lost counts; nothing in the source
+    // explains it (every value a level branches on is the wavefront's or the
+    // workgroup's own, from ballots, scalar loads and LDS after a barrier), and
+    // no spill in its listing is stored under a narrower mask than it is
+    // loaded. Whatever the cause, the build refuses an instance that spills a
+    // scalar register (build.py).
     typedef const __attribute__((address_space(4))) GraphDev *const_graph;
     auto descriptor = [&]() -> const_graph {
         uint64_t a = (uint64_t)(uintptr_t)&G;
@@ -700,38 +711,43 @@ __global__ __launch_bounds__(KT, KT == 1024 && NQ <= 2 && P == 0 ? 8 : 4) void k
             }
         }
     }
-    if (wave == 0) {
-        if (lane < nb)
-            for (int k = max(last, 1) + 1; k < K; ++k) hist[k] = 0;
+    // (everything anew from the descriptor and LDS: held over the levels, it
+    // took scalar registers that the smaller shapes do not have)
+    int tid_now = (int)threadIdx.x;
+    asm volatile("" : "+v"(tid_now));
+    if (__builtin_amdgcn_readfirstlane(tid_now >> 6) == 0) {
+        const const_graph D = descriptor();
+        const int l = tid_now & 63, rows = D->K, mine = batch[0], s0 = batch[1];
+        const uint4 s = (l < mine) ? ((const uint4 *)D->rows.src)[s0 + l] : make_uint4(0u, 0u, 0u, 1u);
+        int32_t *const h = D->hist + (int64_t)(s.x & 0xFFFFu) * rows;
+        if (l < mine)
+            for (int k = max(last, 1) + 1; k < rows; ++k) h[k] = 0;
         // A source's leaves are not searched from and lie one further from what
         // the source reaches last; counted here where that passes the rows' (or
         // the library's) last distance, so that the status is final before
         // anything reads the histograms.
         int far = last;
-        if (last == K - 1 || last == kMaxDist) {
-            bool further = false;
-            if (lane < nb && last < K) {
-                const uint32_t z = src[lane].z;
-                further = (z & 0xFFFFu) > (z >> 16) && hist[last] != 0;
-            }
+        if (last == rows - 1 || last == kMaxDist) {
+            const bool further = l < mine && last < rows && (s.z & 0xFFFFu) > (s.z >> 16) && h[last] != 0;
             if (__ballot(further)) far = last + 1;
         }
-        if (lane == 0) {
-            atomicMax(&G.status[0], far);
-            if (overflow || far > kMaxDist) atomicOr(&G.status[1], 1);
+        if (l == 0) {
+            atomicMax(&D->status[0], far);
+            if (overflow || far > kMaxDist) atomicOr(&D->status[1], 1);
         }
-        if (G.visits) {
+        unsigned long long *const visits = D->visits;
+        if (visits) {
             // the search's work, as the levels cover it: every entry per
             // pulled level (what the skipped rows leave out included), and the
             // sources' own entries
-            uint32_t deg = my_deg;
+            uint32_t deg = s.z & 0xFFFFu;
 #pragma unroll
             for (int off = 32; off > 0; off >>= 1) deg += (uint32_t)__shfl_xor((int)deg, off);
-            if (lane == 0) {
+            if (l == 0) {
                 const unsigned long long v =
-                    (unsigned long long)pulled * (unsigned long long)G.nnz_bfs + deg;
-                atomicAdd(&G.visits[0], v);
-                atomicAdd(&G.visits[1], v * 4ull);
+                    (unsigned long long)pulled * (unsigned long long)D->nnz_bfs + deg;
+                atomicAdd(&visits[0], v);
+                atomicAdd(&visits[1], v * 4ull);
             }
         }
     }
