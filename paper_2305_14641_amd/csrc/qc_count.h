@@ -191,7 +191,7 @@ __global__ __launch_bounds__(KT, KT == 1024 && NQ <= 2 && P == 0 ? 8 : 4) void k
     __shared__ __attribute__((aligned(16))) uint32_t hacc[HUB];
     __shared__ uint32_t hdone[HUB / 32];
     __shared__ uint32_t cnt[3][16];   // counts of a level
-    __shared__ int batch[2];          // sources, and the first one's place
+    __shared__ uint32_t batch[2][BW + 1];   // the sources' first and third words; how many
 
     const BfsJob job = jobs[blockIdx.x];
     const GraphDev &G = graphs[job.g];
@@ -219,12 +219,14 @@ __global__ __launch_bounds__(KT, KT == 1024 && NQ <= 2 && P == 0 ? 8 : 4) void k
     for (int i = tid; i < HUB; i += KT) hacc[i] = 0u;
     for (int i = tid; i < HUB / 32; i += KT) hdone[i] = 0u;
     if (tid < 48) cnt[tid / 16][tid % 16] = 0u;
-    if (tid == 0) {
-        batch[0] = nb;
-        batch[1] = job.s0;
-    }
+    if (tid == 0) batch[0][BW] = (uint32_t)nb;
     __syncthreads();
-    if (tid < nb) put(src[tid].x >> 16, tid);   // level 0: the sources
+    if (tid < nb) {   // level 0: the sources
+        const uint4 s = src[tid];
+        put(s.x >> 16, tid);
+        batch[0][tid] = s.x;
+        batch[1][tid] = s.z;
+    }
     __syncthreads();
     uint32_t seen_r[kSeenReg ? NW : 1], plane[NW][PA];
     // bits of word w that are reached (or that stand for nothing)
@@ -717,9 +719,9 @@ __global__ __launch_bounds__(KT, KT == 1024 && NQ <= 2 && P == 0 ? 8 : 4) void k
     asm volatile("" : "+v"(tid_now));
     if (__builtin_amdgcn_readfirstlane(tid_now >> 6) == 0) {
         const const_graph D = descriptor();
-        const int l = tid_now & 63, rows = D->K, mine = batch[0], s0 = batch[1];
-        const uint4 s = (l < mine) ? ((const uint4 *)D->rows.src)[s0 + l] : make_uint4(0u, 0u, 0u, 1u);
-        int32_t *const h = D->hist + (int64_t)(s.x & 0xFFFFu) * rows;
+        const int l = tid_now & 63, rows = D->K, mine = (int)batch[0][BW];
+        const uint32_t node = (l < mine) ? batch[0][l] & 0xFFFFu : 0u, z = (l < mine) ? batch[1][l] : 0u;
+        int32_t *const h = D->hist + (int64_t)node * rows;
         if (l < mine)
             for (int k = max(last, 1) + 1; k < rows; ++k) h[k] = 0;
         // A source's leaves are not searched from and lie one further from what
@@ -728,7 +730,7 @@ __global__ __launch_bounds__(KT, KT == 1024 && NQ <= 2 && P == 0 ? 8 : 4) void k
         // anything reads the histograms.
         int far = last;
         if (last == rows - 1 || last == kMaxDist) {
-            const bool further = l < mine && last < rows && (s.z & 0xFFFFu) > (s.z >> 16) && h[last] != 0;
+            const bool further = l < mine && last < rows && (z & 0xFFFFu) > (z >> 16) && h[last] != 0;
             if (__ballot(further)) far = last + 1;
         }
         if (l == 0) {
@@ -740,7 +742,7 @@ __global__ __launch_bounds__(KT, KT == 1024 && NQ <= 2 && P == 0 ? 8 : 4) void k
             // the search's work, as the levels cover it: every entry per
             // pulled level (what the skipped rows leave out included), and the
             // sources' own entries
-            uint32_t deg = s.z & 0xFFFFu;
+            uint32_t deg = z & 0xFFFFu;
 #pragma unroll
             for (int off = 32; off > 0; off >>= 1) deg += (uint32_t)__shfl_xor((int)deg, off);
             if (l == 0) {

@@ -92,7 +92,7 @@ constexpr int kChunk = 4;   // words (pairs of neighbours) in flight per thread
 template <int CAP>
 __global__ __launch_bounds__(1024, CAP <= kDescendHalfNodes ? 8 : 4) void k_descend(
     int tie_mode, const GraphDev *__restrict__ graphs, const NodeJob *__restrict__ jobs, int sigma_base,
-    int32_t *labels_base, int64_t labels_ld, bool store_count, bool guard)
+    int32_t *labels_base, int64_t labels_ld, bool store_count)
 {
     constexpr int T = 1024, kWaves = T / 64, kGroups = T / kShare;
     constexpr uint16_t kUndecided = 0xFFFF;
@@ -106,7 +106,7 @@ __global__ __launch_bounds__(1024, CAP <= kDescendHalfNodes ? 8 : 4) void k_desc
     const GraphDev &G = graphs[job.g];
     const int n = G.n, tid = (int)threadIdx.x;
     const int s = sigma_base + (int)blockIdx.x;
-    if (s >= G.n_sigmas || n > CAP || (guard && too_long(G))) return;
+    if (s >= G.n_labels || n > CAP) return;
     const int32_t *__restrict__ order = G.order, *__restrict__ sdeg = G.sell_deg, *__restrict__ soff = G.sell_off;
     const uint32_t *__restrict__ scol = G.sell_col;
     int32_t *const spill = G.parent + (int64_t)s * n;
@@ -388,17 +388,17 @@ __global__ __launch_bounds__(1024, CAP <= kDescendHalfNodes ? 8 : 4) void k_desc
 
 hipError_t launch_descend(int tie_mode, const GraphDev *graphs, const NodeJob *jobs, int n_jobs, int sigma_base,
                           int n_sig, int32_t *labels_base, int64_t labels_ld, int max_n, hipStream_t stream,
-                          bool store_count, bool guard)
+                          bool store_count)
 {
     if (n_jobs <= 0 || n_sig <= 0) return hipSuccess;
     if (max_n > kDescendNodes || (store_count && (n_jobs > 1 || n_sig > 1))) return hipErrorInvalidValue;
     const dim3 grid(n_sig, n_jobs), block(1024);
     if (max_n <= kDescendHalfNodes)   // two workgroups per CU
         hipLaunchKernelGGL(k_descend<kDescendHalfNodes>, grid, block, 0, stream, tie_mode, graphs, jobs, sigma_base,
-                           labels_base, labels_ld, store_count, guard);
+                           labels_base, labels_ld, store_count);
     else
         hipLaunchKernelGGL(k_descend<kDescendNodes>, grid, block, 0, stream, tie_mode, graphs, jobs, sigma_base,
-                           labels_base, labels_ld, store_count, guard);
+                           labels_base, labels_ld, store_count);
     return hipGetLastError();
 }
 

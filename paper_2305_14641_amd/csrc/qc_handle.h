@@ -124,7 +124,7 @@ struct qc_graph_s {
         d.n = n;
         d.K = K;
         d.dmax = dmax;
-        d.n_sigmas = n_sigmas;
+        d.n_sigmas = d.n_labels = n_sigmas;
         d.nnz = nnz;
         d.row_ptr = d_row_ptr;
         d.col = d_col;

@@ -116,7 +116,8 @@ struct GraphDev {
     // graph with every edge of weight w subdivided into w unit edges; its
     // first n nodes are the graph's nodes.
     int32_t n_bfs;
-    int32_t pad_bfs;
+    int32_t n_labels;             // sigmas that labels are stored for: n_sigmas, or 0 after a search
+                                  // that found too long distances (launch_potential with `derive`)
     int64_t nnz_bfs;              // its edges (= nnz without weights)
     const int32_t *bfs_row_ptr;   // [n_bfs+1]
     const int32_t *bfs_col;
@@ -255,9 +256,9 @@ int hist_waves(int K, int variant);
 // Optional caller outputs: out[out_off + s*out_ld + (i - i0_of_graph)].
 // `derive` (FP64ACC, after a counting search whose G.rows.rest has one entry
 // per node: 0, or its kind << 16 | a leaf's neighbour): the rows of the nodes
-// that the search leaves out are derived on the way, not read; and nothing is
-// written when the search found distances that the rows (or the library)
-// can't hold (too_long).
+// that the search leaves out are derived on the way, not read; and when the
+// search found distances that the rows (or the library) can't hold (too_long),
+// the caller's outputs stay as they are and no labels follow (n_labels).
 constexpr uint32_t kRestLeaf = 1, kRestPair = 2, kRestAlone = 3;
 hipError_t launch_potential(int precision, int K, const GraphDev *graphs, const NodeJob *jobs,
                             int n_jobs, float *psi_out, float *v_out, int64_t out_ld,
@@ -269,23 +270,21 @@ hipError_t launch_ggd_parent(int tie_mode, const GraphDev *graphs, const NodeJob
 
 // Pointer jumping, one workgroup per (graph job, sigma); labels of sigma
 // sigma_base + y go to labels_base + y*labels_ld + job.out_off. The rounds run
-// in LDS, or in global memory where `variant` is 1. `guard` (LDS): nothing is
-// written after a search whose distances were too long (too_long).
+// in LDS, or in global memory where `variant` is 1.
 hipError_t launch_pointer_jump(const GraphDev *graphs, const NodeJob *jobs, int n_jobs,
                                int sigma_base, int n_sig, int32_t *labels_base,
-                               int64_t labels_ld, hipStream_t stream, int variant = 0, bool guard = false);
+                               int64_t labels_ld, hipStream_t stream, int variant = 0);
 
 // Descent and pointer jumping of (graph job, sigma) pairs in one launch, each
 // in one workgroup's LDS (qc_descend.hip): graphs of at most kDescendNodes
 // nodes (4 bytes of V and 2 of parent per node, and the near ties' queues,
 // fill the 160 KB); labels as launch_pointer_jump. Two workgroups fit a CU up
 // to kDescendHalfNodes. Near ties are added to the graph's recheck counter, or
-// stored there with `store_count` (one job and one sigma only). `guard` as
-// launch_pointer_jump.
+// stored there with `store_count` (one job and one sigma only).
 constexpr int kDescendNodes = 26560, kDescendHalfNodes = 12864;
 hipError_t launch_descend(int tie_mode, const GraphDev *graphs, const NodeJob *jobs, int n_jobs, int sigma_base,
                           int n_sig, int32_t *labels_base, int64_t labels_ld, int max_n, hipStream_t stream,
-                          bool store_count = false, bool guard = false);
+                          bool store_count = false);
 
 // Stage timing (qc_timing.cpp): Timer brackets one launch when enabled.
 class StageTimer {

@@ -304,7 +304,7 @@ __global__ __launch_bounds__(256) void k_potential(const GraphDev *__restrict__ 
     const NodeJob job = jobs[blockIdx.x];
     const GraphDev &G = graphs[job.g];
     const int n = G.n;
-    if (REST && too_long(G)) return;
+    const bool bad = REST && too_long(G);   // (asked for beside the row)
     const int i = REST ? min(job.i0 + (int)threadIdx.x, n - 1) : job.i0 + (int)threadIdx.x;
     if (i >= n) return;
     const int kmax = min(G.dmax + 1, K);
@@ -346,6 +346,11 @@ __global__ __launch_bounds__(256) void k_potential(const GraphDev *__restrict__ 
             if (far > kMaxDist) atomicOr(&G.status[1], 1);
         }
         if (job.i0 + (int)threadIdx.x >= n) return;
+        // (then the resident copies take what no caller may see)
+        if (bad) {
+            psi_out = v_out = nullptr;
+            if (threadIdx.x == 0) const_cast<GraphDev &>(G).n_labels = 0;
+        }
     }
 
     // one (node, sigma) result: FP32 psi and V for the caller (or resident
@@ -819,7 +824,7 @@ __global__ __launch_bounds__(1024) void k_jump(const GraphDev *__restrict__ grap
 // call 130 us with the rounds in global memory, 74 with these).
 __global__ __launch_bounds__(1024) void k_jump_lds(const GraphDev *__restrict__ graphs,
                                                    const NodeJob *__restrict__ jobs, int sigma_base,
-                                                   int32_t *labels_base, int64_t labels_ld, bool guard)
+                                                   int32_t *labels_base, int64_t labels_ld)
 {
     constexpr int T = 1024;
     __shared__ uint64_t lab4[kMaxNodes / 4];
@@ -829,7 +834,7 @@ __global__ __launch_bounds__(1024) void k_jump_lds(const GraphDev *__restrict__ 
     const GraphDev &G = graphs[job.g];
     const int n = G.n, tid = (int)threadIdx.x;
     const int s = sigma_base + (int)blockIdx.y;
-    if (s >= G.n_sigmas || n > kMaxNodes || (guard && too_long(G))) return;
+    if (s >= G.n_labels || n > kMaxNodes) return;
     // parents are stored in the descent's thread order: node order[t]'s at t
     const int32_t *__restrict__ par = G.parent + (int64_t)s * n;
     for (int t = tid; t < n; t += T) lab[G.order[t]] = (uint16_t)par[t];
@@ -865,17 +870,16 @@ __global__ __launch_bounds__(1024) void k_jump_lds(const GraphDev *__restrict__ 
 
 hipError_t launch_pointer_jump(const GraphDev *graphs, const NodeJob *jobs, int n_jobs,
                                int sigma_base, int n_sig, int32_t *labels_base,
-                               int64_t labels_ld, hipStream_t stream, int variant, bool guard)
+                               int64_t labels_ld, hipStream_t stream, int variant)
 {
     if (n_jobs <= 0 || n_sig <= 0) return hipSuccess;
-    if (variant == 1 && guard) return hipErrorInvalidValue;
     const dim3 grid(n_jobs, n_sig), block(1024);
     if (variant == 1)     // in global memory whatever the size
         hipLaunchKernelGGL(k_jump, grid, block, 0, stream, graphs, jobs, sigma_base, labels_base,
                            labels_ld);
     else
         hipLaunchKernelGGL(k_jump_lds, grid, block, 0, stream, graphs, jobs, sigma_base, labels_base,
-                           labels_ld, guard);
+                           labels_ld);
     return hipGetLastError();
 }
 

@@ -8,6 +8,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <memory>
 #include <new>
 
 namespace qc {
@@ -84,19 +85,13 @@ OneCall::OneCall(int32_t n, const std::vector<int32_t> &rp, const std::vector<in
 
 size_t OneCall::results_bytes() const { return (size_t)S_ * n_ * (with_potentials_ ? 12 : 4); }
 
-// Offsets of everything for `bins` histogram bins; the weight tables with
-// them (exp(-k^2 / a) by the host C library, as weight_tables).
+// Offsets of everything for `bins` histogram bins.
 size_t OneCall::lay_out(int bins)
 {
     if (bins_ == bins) return total_;
     bins_ = bins;
-    w64_.assign((size_t)S_ * bins, 0.0);
-    inv_a_.assign(S_, 0.0);
-    for (int s = 0; s < S_; ++s) {
-        const double a = (2.0 * sigmas_[s]) * sigmas_[s];
-        inv_a_[s] = 1.0 / a;
-        for (int k = 0; k < bins; ++k) w64_[(size_t)s * bins + k] = exp(-(double)(k * k) / a);
-    }
+    w64_.resize((size_t)S_ * bins);
+    inv_a_.resize(S_);
     parts_.assign(kParts, Part{nullptr, 0, 0});
     auto part = [&](int i, const auto &v) { parts_[i] = Part{v.data(), v.size() * sizeof(v[0]), 0}; };
     parts_[kDesc] = Part{nullptr, sizeof(GraphDev), 0};   // (its contents follow from the address)
@@ -141,12 +136,23 @@ size_t OneCall::lay_out(int bins)
     return total_;
 }
 
+// The weight tables of the current layout: exp(-k^2 / a) by the host C
+// library, as weight_tables.
+void OneCall::set_weights()
+{
+    for (int s = 0; s < S_; ++s) {
+        const double a = (2.0 * sigmas_[s]) * sigmas_[s];
+        inv_a_[s] = 1.0 / a;
+        for (int k = 0; k < bins_; ++k) w64_[(size_t)s * bins_ + k] = exp(-(double)(k * k) / a);
+    }
+}
+
 size_t OneCall::bytes(int bins) { return lay_out(bins); }
 
 qc_status OneCall::run(char *base, size_t limit, uint32_t tie_mode, float *psi_out, float *v_out,
                        int32_t *labels_out, hipStream_t st, int32_t *dmax_out)
 {
-    std::vector<char> image;
+    std::unique_ptr<char[]> image;
     // Rows of 32 bins hold all but unusually long graphs, most of which
     // first_bins_ knows where they are small; the search reports
     // the largest distance, and a longer one repeats the call with rows that
@@ -154,6 +160,7 @@ qc_status OneCall::run(char *base, size_t limit, uint32_t tie_mode, float *psi_o
     // finds them as they were.)
     for (int bins = first_bins_;;) {
         if (lay_out(bins) > limit) return QC_E_TOO_LARGE;
+        set_weights();
         // (this layout's addresses: longer rows move everything behind them)
         int32_t *labels = labels_out;
         float *psi = psi_out, *v = v_out;
@@ -169,7 +176,7 @@ qc_status OneCall::run(char *base, size_t limit, uint32_t tie_mode, float *psi_o
         d.n = d.n_bfs = n_;
         d.K = bins;
         d.dmax = bins - 1;   // (bins past the largest distance are zero)
-        d.n_sigmas = S_;
+        d.n_sigmas = d.n_labels = S_;
         d.nnz = d.nnz_bfs = nnz_;
         d.order = (const int32_t *)at(kOrder);
         d.sell_col = (const uint32_t *)at(kSellCol);
@@ -198,15 +205,13 @@ qc_status OneCall::run(char *base, size_t limit, uint32_t tie_mode, float *psi_o
         d.rows.n_pos = d.rows.n_search = t_.n_pos;
         d.rows.n_leaf = t_.n_leaf;
         parts_[kDesc].src = &d;
-        try {
-            image.resize(image_);
-        } catch (const std::bad_alloc &) {
-            return QC_E_OOM;   // (the caller has a buffer to give back)
-        }
+        // (unset between the parts, which nothing reads)
+        image.reset(new (std::nothrow) char[image_]);
+        if (!image) return QC_E_OOM;   // (the caller has a buffer to give back)
         for (const Part &p : parts_)
-            if (p.bytes) memcpy(image.data() + p.off, p.src, p.bytes);
+            if (p.bytes) memcpy(image.get() + p.off, p.src, p.bytes);
         parts_[kDesc].src = nullptr;
-        QC_HIP(hipMemcpyAsync(base, image.data(), image_, hipMemcpyHostToDevice, st));
+        QC_HIP(hipMemcpyAsync(base, image.get(), image_, hipMemcpyHostToDevice, st));
         const GraphDev *const desc = (const GraphDev *)at(kDesc);
         const NodeJob *const nodes = (const NodeJob *)at(kNodeJobs);
         // (whatever fails from here on, `image` and the caller's memory are
@@ -224,14 +229,12 @@ qc_status OneCall::run(char *base, size_t limit, uint32_t tie_mode, float *psi_o
             return launch_potential(QC_PREC_FP64ACC, bins, desc, nodes, (int)node_jobs_.size(), psi, v, n_, st, true);
         });
         if (descends_in_lds(n_, nnz_, descent_.max_degree, S_)) {
-            stage(QC_STAGE_GGD, [&] {
-                return launch_descend((int)tie_mode, desc, nodes, 1, 0, S_, labels, n_, n_, st, false, true);
-            });
+            stage(QC_STAGE_GGD, [&] { return launch_descend((int)tie_mode, desc, nodes, 1, 0, S_, labels, n_, n_, st); });
         } else {
             stage(QC_STAGE_GGD, [&] {
                 return launch_ggd_parent((int)tie_mode, desc, nodes, (int)node_jobs_.size(), 0, S_, st);
             });
-            stage(QC_STAGE_JUMP, [&] { return launch_pointer_jump(desc, nodes, 1, 0, S_, labels, n_, st, 0, true); });
+            stage(QC_STAGE_JUMP, [&] { return launch_pointer_jump(desc, nodes, 1, 0, S_, labels, n_, st); });
         }
         int32_t status[2] = {0, 0};
         if (e == hipSuccess) e = hipMemcpyAsync(status, at(kStatus), sizeof status, hipMemcpyDeviceToHost, st);

@@ -45,6 +45,7 @@ class OneCall {
         size_t bytes, off;
     };
     size_t lay_out(int bins);
+    void set_weights();
 
     int32_t n_, S_;
     int64_t nnz_;
