@@ -5,7 +5,6 @@
 #include <string.h>
 
 #include <algorithm>
-#include <functional>
 #include <map>
 #include <mutex>
 #include <set>
@@ -45,13 +44,12 @@ struct Stages {
                                // -2: the last launch's, on the caller's stream, beside the side stream)
     bool rest = true;
     std::vector<KGroup> hist, pot;
-    // Descent and pointer jumping through global memory, for every graph
-    // ([1], the jump variant that asks for it) or those that the
-    // one-workgroup descent can't hold ([0]).
+    // Descent and pointer jumping through global memory: the graphs that do
+    // not descend in one workgroup each (every graph with jump variant 1).
     struct Far {
         NodeJob *d_ggd_jobs = nullptr, *d_jump_jobs = nullptr;
         int n_ggd_jobs = 0, n_jump_jobs = 0;
-    } far[2];
+    } far;
     // Jobs of the one-workgroup descent (launch_descend), by LDS size.
     struct Descend {
         NodeJob *d_jobs = nullptr;
@@ -124,10 +122,8 @@ void free_batch(qc_batch b)
     for (auto &c : b->stages) {
         for (auto &g : c.hist) dfree(g.d_jobs);
         for (auto &g : c.pot) dfree(g.d_jobs);
-        for (auto &x : c.far) {
-            dfree(x.d_ggd_jobs);
-            dfree(x.d_jump_jobs);
-        }
+        dfree(c.far.d_ggd_jobs);
+        dfree(c.far.d_jump_jobs);
         for (auto &x : c.descend) dfree(x.d_jobs);
     }
     for (auto &g : b->pot_all) dfree(g.d_jobs);
@@ -344,12 +340,11 @@ qc_status run_stages(qc_batch b, const Stages &c, float *psi_out, float *v_out, 
         QC_HIP(launch_potential(b->precision, g.K, b->d_descs, g.d_jobs, g.n_jobs, psi_out, v_out,
                                 total, st));
     }
-    if (b->jump_variant == 0)
-        for (const Stages::Descend &x : c.descend) {
-            StageTimer t(QC_STAGE_GGD, st);
-            QC_HIP(launch_descend((int)b->tie, b->d_descs, x.d_jobs, x.n_jobs, 0, S, labels_out, total, x.max_n, st));
-        }
-    const Stages::Far &f = c.far[b->jump_variant];
+    for (const Stages::Descend &x : c.descend) {
+        StageTimer t(QC_STAGE_GGD, st);
+        QC_HIP(launch_descend((int)b->tie, b->d_descs, x.d_jobs, x.n_jobs, 0, S, labels_out, total, x.max_n, st));
+    }
+    const Stages::Far &f = c.far;
     if (f.n_ggd_jobs) {
         StageTimer t(QC_STAGE_GGD, st);
         QC_HIP(launch_ggd_parent((int)b->tie, b->d_descs, f.d_ggd_jobs, f.n_ggd_jobs, 0, S, st));
@@ -450,20 +445,19 @@ float time_launches(F launch, hipStream_t st)
     return ms;
 }
 
-// The stage tiles the autotuner chose, process-wide, by workload class:
-// (stage, overlapped form, log2 of the batch's nodes, log2 of the largest
-// graph); a batch of the same class reuses the choice.
+// The histogram shape the autotuner chose, process-wide, by workload class:
+// (overlapped form, log2 of the batch's nodes, log2 of the largest graph); a
+// batch of the same class reuses the choice.
 std::mutex g_tiles_mu;
-std::map<std::tuple<int, int, int, int>, int> g_tiles;
+std::map<std::tuple<int, int, int>, int> g_tiles;
 
 // The autotuner's second part: after one eager run of the whole path (so the
 // matrices, histograms and parents are the batch's own and re-running a
 // stage rewrites identical values), time whole steps with the histogram pass
-// in each of its three workgroup shapes, then with pointer jumping in LDS and
-// in global memory (interleaved rounds, each variant's best round); keep the
-// fastest, and remember it for the class. Whole
-// steps, because in the overlapped forms a stage's best shape is the one
-// that shares the GPU best with the searches beside it.
+// in each of its three workgroup shapes (interleaved rounds, each variant's
+// best round); keep the fastest, and remember it for the class. Whole steps,
+// because in the overlapped forms a stage's best shape is the one that shares
+// the GPU best with the searches beside it.
 qc_status autotune_stages(qc_batch b, hipStream_t st)
 {
     StageTimingOff quiet;
@@ -481,32 +475,31 @@ qc_status autotune_stages(qc_batch b, hipStream_t st)
         for (auto &c : b->stages)
             for (auto &g : c.hist) g.variant = v;
     };
-    auto tune = [&](int stage, int n_variants, const std::function<void(int)> &apply) {
-        const auto key = std::make_tuple(stage, b->overlap, log2_bucket((double)total), log2_bucket(max_n));
-        {
-            std::lock_guard<std::mutex> lk(g_tiles_mu);
-            auto it = g_tiles.find(key);
-            if (it != g_tiles.end()) {
-                apply(it->second);
-                return;
-            }
-        }
-        std::vector<float> best((size_t)n_variants, 1e30f);
+    const auto key = std::make_tuple(b->overlap, log2_bucket((double)total), log2_bucket(max_n));
+    bool known = false;
+    {
+        std::lock_guard<std::mutex> lk(g_tiles_mu);
+        auto it = g_tiles.find(key);
+        known = it != g_tiles.end();
+        if (known) set_hist(it->second);
+    }
+    if (!known) {
+        constexpr int kVariants = 3;
+        float best[kVariants] = {1e30f, 1e30f, 1e30f};
         for (int r = 0; r < kTuneRounds && s == QC_OK; ++r)
-            for (int v = 0; v < n_variants && s == QC_OK; ++v) {
-                apply(v);
+            for (int v = 0; v < kVariants && s == QC_OK; ++v) {
+                set_hist(v);
                 const float ms = time_launches(step, st);
                 if (ms < 0.0f) s = QC_E_DEVICE;
-                else best[(size_t)v] = std::min(best[(size_t)v], ms);
+                else best[v] = std::min(best[v], ms);
             }
         // the default (variant 0) stays unless another is clearly faster
-        int chosen = (int)(std::min_element(best.begin(), best.end()) - best.begin());
-        if (chosen != 0 && best[(size_t)chosen] > best[0] * (1.0f - kTuneMargin / 2)) chosen = 0;
-        apply(chosen);
+        int chosen = (int)(std::min_element(best, best + kVariants) - best);
+        if (chosen != 0 && best[chosen] > best[0] * (1.0f - kTuneMargin / 2)) chosen = 0;
+        set_hist(chosen);
         std::lock_guard<std::mutex> lk(g_tiles_mu);
         if (s == QC_OK) g_tiles[key] = chosen;
-    };
-    if (s == QC_OK) tune(0, 3, set_hist);
+    }
     (void)hipStreamSynchronize(st);
     dfree(labels);
     return s;
@@ -727,6 +720,12 @@ qc_status qc_batch_create(const qc_graph *graphs, int32_t n_graphs, const double
             load[(size_t)g.stream] += g.cost;
         }
     }
+    // QC_JUMP_VARIANT=1 (a switch for measurements and tests): every graph
+    // descends and jumps in global memory
+    if (!(flags & QC_BATCH_AUTOTUNE)) {
+        const char *jv = getenv("QC_JUMP_VARIANT");
+        b->jump_variant = (jv && atoi(jv) == 1) ? 1 : 0;
+    }
     // One stage set over graphs `gis`: histogram and potential jobs grouped
     // by bin count, descent jobs (pinned to XCDs when the graphs allow it),
     // one jumping job per graph. Appended before its tables are allocated,
@@ -786,20 +785,19 @@ qc_status qc_batch_create(const qc_graph *graphs, int32_t n_graphs, const double
             }
             for (int gi : gis) {
                 const qc_graph g = graphs[gi];
-                in_lds[gi] = g->n <= kDescendNodes &&
+                in_lds[gi] = b->jump_variant == 0 && g->n <= kDescendNodes &&
                              descend_us(g->n, g->nnz) <=
                                  std::max(turns, descend_far_us(g->n, g->max_degree, n_sigmas, nodes));
             }
         }
-        for (int k = 0; k < 2; ++k) {
+        {
             std::vector<int> in;
             std::vector<qc_graph> gv;
             for (int gi : gis)
-                if (k || !in_lds[gi]) {
+                if (!in_lds[gi]) {
                     in.push_back(gi);
                     gv.push_back(graphs[gi]);
                 }
-            if (in.empty()) continue;
             std::vector<NodeJob> gj = xcd_pinned_node_jobs(gv), jj;
             // pinned jobs index gv; the kernels index the batch's descriptors
             for (auto &j : gj) j.g = in[j.g];
@@ -809,11 +807,12 @@ qc_status qc_batch_create(const qc_graph *graphs, int32_t n_graphs, const double
                     for (int r = 0; r < graphs[gi]->n; r += kNodesPerJob) gj.push_back(NodeJob{gi, r, 0});
                 jj.push_back(NodeJob{gi, 0, b->offsets[gi]});
             }
-            Stages::Far &f = c.far[k];
-            f.n_ggd_jobs = (int)gj.size();
-            f.n_jump_jobs = (int)jj.size();
-            QC_TRY(upload_jobs(&f.d_ggd_jobs, gj));
-            QC_TRY(upload_jobs(&f.d_jump_jobs, jj));
+            c.far.n_ggd_jobs = (int)gj.size();
+            c.far.n_jump_jobs = (int)jj.size();
+            if (!in.empty()) {
+                QC_TRY(upload_jobs(&c.far.d_ggd_jobs, gj));
+                QC_TRY(upload_jobs(&c.far.d_jump_jobs, jj));
+            }
         }
         // The one-workgroup descent: a launch for the graphs that fill more
         // than half of a CU's LDS and one for the others, largest first.
@@ -890,13 +889,12 @@ qc_status qc_batch_create(const qc_graph *graphs, int32_t n_graphs, const double
     if (flags & QC_BATCH_AUTOTUNE) {
         if ((s = autotune_stages(b, st))) return fail(s);
     } else {
-        // QC_HIST_VARIANT / QC_JUMP_VARIANT (switches for measurements and
-        // tests): a fixed histogram shape (0-2) and jumping variant (0-1)
-        const char *hv = getenv("QC_HIST_VARIANT"), *jv = getenv("QC_JUMP_VARIANT");
+        // QC_HIST_VARIANT (a switch for measurements and tests): a fixed
+        // histogram shape (0-2)
+        const char *hv = getenv("QC_HIST_VARIANT");
         if (hv && atoi(hv) >= 0 && atoi(hv) <= 2)
             for (auto &c : b->stages)
                 for (auto &g : c.hist) g.variant = atoi(hv);
-        if (jv && (atoi(jv) == 0 || atoi(jv) == 1)) b->jump_variant = atoi(jv);
     }
     *out = b;
     return QC_OK;
