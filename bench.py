@@ -475,7 +475,7 @@ def main():
     ap.add_argument("--cpu-budget-s", type=float, default=15.0)
     ap.add_argument("--no-plain", action="store_true")
     ap.add_argument("--no-autotune", action="store_true",
-                    help="keep the planner's BFS launch shapes (no timing at set-up)")
+                    help="keep the default launch shapes (no timing at set-up)")
     ap.add_argument("--no-dense", action="store_true",
                     help="skip the fully connected (dense float distance) leg")
     ap.add_argument("--dense-n", type=int, default=20000)
@@ -534,17 +534,11 @@ def main():
 
     handles = [qc.Graph.from_graph(g) for g in graphs]
     for G in handles:
-        G.distances()       # learns dmax: the planner's final choice
-    planned = [G.bfs_plan() for G in handles]
+        G.distances()       # learns the largest distance
     t0 = time.perf_counter()
     batch = qc.Batch(handles, sigmas, tie_mode=qc.TIE_STRICT, hipgraph=True,
                      autotune=not args.no_autotune)
-    tuned = [G.bfs_plan() for G in handles]
-    log(f"batch set-up {time.perf_counter() - t0:.2f}s; autotuner changed the BFS plan of "
-        f"{sum(a != b for a, b in zip(planned, tuned))} of {len(handles)} graphs")
-    from collections import Counter
-    log("BFS plans (batch width, words, planes, shape): "
-        + ", ".join(f"{k}x{c}" for k, c in sorted(Counter(tuned).items())))
+    log(f"batch set-up {time.perf_counter() - t0:.2f}s")
     stage_tiles = batch.stage_tiles()
     log(f"stage tiles: {stage_tiles}")
     psi, v, lab = batch.outputs()
@@ -701,12 +695,7 @@ def main():
         "graphs_per_s": len(graphs) / dt,
         "fp64_rechecks_per_step": rechecks,
         "stages": stages,
-        "tiles": {"bfs_plans": {f"{bw}x{nw}x{p}x{sh}": c for (bw, nw, p, sh), c
-                                in sorted(Counter(tuned).items())},
-                  "bfs_plan_key": "sources per batch x words per thread x planes x shape",
-                  "bfs_policy": {"widest_batch": stage_tiles["bfs_widest"],
-                                 "seen_in_registers_first": stage_tiles["bfs_front_first"]},
-                  "hist_waves": {str(k): w for k, w in stage_tiles["hist_waves"].items() if w},
+        "tiles": {"hist_waves": {str(k): w for k, w in stage_tiles["hist_waves"].items() if w},
                   "jump": stage_tiles["jump"],
                   "stages_beside_searches": stage_tiles["overlap"]},
         "dominant_kernel": dom,
