@@ -578,6 +578,52 @@ __global__ __launch_bounds__(KT, KT == 1024 && NQ <= 2 && P == 0 ? 8 : 4) void k
         for (int level = 2;; ++level)
             if (run_level(level)) break;
     }
+    // The histograms' ends and the status. Before the distance rows where the
+    // planes fill the registers (fewer spills: 4 quads, 5 planes, 295 -> 285 us
+    // for 19,717 nodes), else after them, where no wavefront waits for it.
+    auto finish = [&] {
+        // (everything anew from the descriptor and LDS: held over the levels, it
+        // took scalar registers that the smaller shapes do not have)
+        int tid_now = (int)threadIdx.x;
+        asm volatile("" : "+v"(tid_now));
+        if (__builtin_amdgcn_readfirstlane(tid_now >> 6) == 0) {
+            const const_graph D = descriptor();
+            const int l = tid_now & 63, rows = D->K, mine = (int)batch[0][BW];
+            const uint32_t node = (l < mine) ? batch[0][l] & 0xFFFFu : 0u, z = (l < mine) ? batch[1][l] : 0u;
+            int32_t *const h = D->hist + (int64_t)node * rows;
+            if (l < mine)
+                for (int k = max(last, 1) + 1; k < rows; ++k) h[k] = 0;
+            // A source's leaves are not searched from and lie one further from what
+            // the source reaches last; counted here where that passes the rows' (or
+            // the library's) last distance, so that the status is final before
+            // anything reads the histograms.
+            int far = last;
+            if (last == rows - 1 || last == kMaxDist) {
+                const bool further = l < mine && last < rows && (z & 0xFFFFu) > (z >> 16) && h[last] != 0;
+                if (__ballot(further)) far = last + 1;
+            }
+            if (l == 0) {
+                atomicMax(&D->status[0], far);
+                if (overflow || far > kMaxDist) atomicOr(&D->status[1], 1);
+            }
+            unsigned long long *const visits = D->visits;
+            if (visits) {
+                // the search's work, as the levels cover it: every entry per
+                // pulled level (what the skipped rows leave out included), and the
+                // sources' own entries
+                uint32_t deg = z & 0xFFFFu;
+#pragma unroll
+                for (int off = 32; off > 0; off >>= 1) deg += (uint32_t)__shfl_xor((int)deg, off);
+                if (l == 0) {
+                    const unsigned long long v =
+                        (unsigned long long)pulled * (unsigned long long)D->nnz_bfs + deg;
+                    atomicAdd(&visits[0], v);
+                    atomicAdd(&visits[1], v * 4ull);
+                }
+            }
+        }
+    };
+    if constexpr (P > 0 && !kSeenReg) finish();
     if constexpr (P > 0) {
         // The distance rows. The planes go from the positions' owners to the
         // nodes' (quads of 4 consecutive nodes per lane) through the frontier's
@@ -713,46 +759,7 @@ __global__ __launch_bounds__(KT, KT == 1024 && NQ <= 2 && P == 0 ? 8 : 4) void k
             }
         }
     }
-    // (everything anew from the descriptor and LDS: held over the levels, it
-    // took scalar registers that the smaller shapes do not have)
-    int tid_now = (int)threadIdx.x;
-    asm volatile("" : "+v"(tid_now));
-    if (__builtin_amdgcn_readfirstlane(tid_now >> 6) == 0) {
-        const const_graph D = descriptor();
-        const int l = tid_now & 63, rows = D->K, mine = (int)batch[0][BW];
-        const uint32_t node = (l < mine) ? batch[0][l] & 0xFFFFu : 0u, z = (l < mine) ? batch[1][l] : 0u;
-        int32_t *const h = D->hist + (int64_t)node * rows;
-        if (l < mine)
-            for (int k = max(last, 1) + 1; k < rows; ++k) h[k] = 0;
-        // A source's leaves are not searched from and lie one further from what
-        // the source reaches last; counted here where that passes the rows' (or
-        // the library's) last distance, so that the status is final before
-        // anything reads the histograms.
-        int far = last;
-        if (last == rows - 1 || last == kMaxDist) {
-            const bool further = l < mine && last < rows && (z & 0xFFFFu) > (z >> 16) && h[last] != 0;
-            if (__ballot(further)) far = last + 1;
-        }
-        if (l == 0) {
-            atomicMax(&D->status[0], far);
-            if (overflow || far > kMaxDist) atomicOr(&D->status[1], 1);
-        }
-        unsigned long long *const visits = D->visits;
-        if (visits) {
-            // the search's work, as the levels cover it: every entry per
-            // pulled level (what the skipped rows leave out included), and the
-            // sources' own entries
-            uint32_t deg = z & 0xFFFFu;
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) deg += (uint32_t)__shfl_xor((int)deg, off);
-            if (l == 0) {
-                const unsigned long long v =
-                    (unsigned long long)pulled * (unsigned long long)D->nnz_bfs + deg;
-                atomicAdd(&visits[0], v);
-                atomicAdd(&visits[1], v * 4ull);
-            }
-        }
-    }
+    if constexpr (P == 0 || kSeenReg) finish();
 }
 
 }  // namespace qc
