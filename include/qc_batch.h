@@ -41,7 +41,8 @@ enum {
  *              once per switch).
  *              A graph appears at most once. The distances of every pair
  *              are counted into the histograms by the search itself, without
- *              a distance matrix; a graph with integer weights takes its
+ *              a distance matrix; a graph with integer weights (and each of a
+ *              batch of nothing but small graphs of many levels) takes its
  *              histograms from a matrix its handle owns
  *              (allocated here when the handle has none), never
  *              a caller's buffer an earlier qc_distances call was given; that

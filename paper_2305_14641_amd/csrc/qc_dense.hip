@@ -86,7 +86,9 @@ struct DenseAcc {
     // and weight of which the exponential and the two conversions take more
     // than half. A matrix with no-path entries in every batch keeps the
     // general form: 413 -> 417 us at 12,000^2 and 8 widths; a form of this one
-    // with a select per weight took 142 registers and 424.)
+    // with a select per weight took 142 registers and 424, and leaving the
+    // question out of the three batches after such an entry cost the matrices
+    // without any 364 -> 404 us, for 421 -> 419 with them.)
     template <int N>
     __device__ __forceinline__ void add_batch(const float (&d)[N], const DenseCoef &k)
     {
