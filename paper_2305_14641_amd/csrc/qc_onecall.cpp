@@ -1,6 +1,6 @@
 // Algorithm 4 in one call (see qc_onecall.h): one host-to-device copy of all
 // tables, three launches (search; potentials with the rows it leaves out; descent
-// and pointer jumping of every width, two where descends_in_lds says so), one
+// and pointer jumping of every width, two where descends_in_lds says no), one
 // 8-byte copy back.
 #include "qc_onecall.h"
 
