@@ -321,12 +321,13 @@ qc_status qc_cluster_real(int32_t n, int64_t nnz, const int32_t *row_ptr, const 
  *                (canonical and undirected, else QC_E_NOT_SYMMETRIC)
  *   sigmas, n_sigmas          host, as for qc_potential
  *   tie_mode     QC_TIE_STRICT or QC_TIE_MERGE
- *   dist_out     device, int8[n*n] row-major, 16-byte aligned, or NULL (the
- *                library then uses a matrix of its own for the call)
+ *   dist_out     device, int8[n*n] row-major, 16-byte aligned, or NULL (no
+ *                matrix is made then)
  *   psi_out, v_out  device, float[n_sigmas][n], or NULL
  *   labels_out   device, int32[n_sigmas][n] (sigma-major), required
  * Potentials are accumulated in FP64 (QC_PREC_FP64ACC). On QC_E_OVERFLOW the
- * outputs are undefined. Other errors as the calls it makes.
+ * outputs are as they were when dist_out is NULL, else undefined. Other errors
+ * as the calls it makes.
  */
 qc_status qc_cluster(int32_t n, int64_t nnz, const int32_t *row_ptr, const int32_t *col_idx,
                      const double *sigmas, int32_t n_sigmas, uint32_t tie_mode, int8_t *dist_out,
@@ -337,16 +338,15 @@ qc_status qc_cluster(int32_t n, int64_t nnz, const int32_t *row_ptr, const int32
  * (code under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc). Same arguments, outputs and errors as qc_cluster; the caller
  * still provides the output buffers. Every buffer the call needs besides
- * them (CSR, packed edges, histograms, resident potentials, parents, weight
- * tables, job tables, status words, and the distance matrix when dist_out is
- * NULL) is carved from one fixed array of QC_NOALLOC_SCRATCH_BYTES of device
+ * them (CSR or the search's tables, packed edges, histograms, resident
+ * potentials, parents, weight tables, job tables, status words) is carved from one fixed array of QC_NOALLOC_SCRATCH_BYTES of device
  * memory, a static device symbol of the library: each device the call runs
  * on holds its own copy until the process ends. The call never calls
  * hipMalloc or hipFree, and no stage timing is recorded for it.
- *   Size limit: the bytes it needs (about 4(n+1) + 4 nnz for the CSR, a
- *   sliced copy of the neighbour lists, 4 n K with K = 128 for histograms,
- *   20 n S for potentials and parents, plus n*n when dist_out is NULL) must
- *   not exceed QC_NOALLOC_SCRATCH_BYTES, else QC_E_TOO_LARGE before any
+ *   Size limit: the bytes of the form with a matrix (about 4(n+1) + 4 nnz for
+ *   the CSR, a sliced copy of the neighbour lists, 4 n K with K = 128 for
+ *   histograms, 20 n S for potentials and parents, plus n*n when dist_out is
+ *   NULL, also though no matrix is made then) must not exceed QC_NOALLOC_SCRATCH_BYTES, else QC_E_TOO_LARGE before any
  *   device work (e.g. n = 19,717 with 88,726 entries and one width fits only
  *   with a caller's dist_out).
  *   Sharing: every call on one device uses that device's array, which keeps
